@@ -93,13 +93,17 @@ __device__ __forceinline__ void block_colsum(int32_t* red, const int32_t (&acc)[
         for (int i = 0; i < 16; ++i) red[lane * width + cl * kBnChunk + i] = acc[i];
     }
     __syncthreads();
-    // every thread adds a strided subset of the lanes of one channel; the
-    // subsets' sums go through LDS once more (width <= 256 channels here:
-    // wider block columns have one lane, nothing to add)
+    // up to 256 channels: every thread adds a strided subset of the lanes of
+    // one channel and the subsets' sums go through LDS once more; a wider
+    // block column (257 .. 2048 channels, few lanes): a thread adds the lanes
+    // of every 256th channel
     const int64_t cbase = (int64_t)blockIdx.y * width;
-    if (g.lanes == 1) {
-        for (int k = threadIdx.x; k < width; k += kBnThreads)
-            if (cbase + k < C) part[(int64_t)blockIdx.x * C + cbase + k] = red[k];
+    if (width > kBnThreads) {
+        for (int k = threadIdx.x; k < width; k += kBnThreads) {
+            int32_t s = 0;
+            for (int l = 0; l < g.lanes; ++l) s += red[l * width + k];
+            if (cbase + k < C) part[(int64_t)blockIdx.x * C + cbase + k] = s;
+        }
         return;
     }
     const int J = kBnThreads / width, k = threadIdx.x % width, j = threadIdx.x / width;

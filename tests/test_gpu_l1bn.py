@@ -174,3 +174,12 @@ def test_quantize_from_ranges_arbitrary_slabs(sq):
     for name in ("q_fold", "q_t", "group", "layout"):
         assert torch.equal(getattr(a, name), getattr(c, name)), name
     assert torch.equal(a.scale, c.scale)
+
+
+# block columns wider than 256 channels that still hold several row lanes (257
+# to 2048 channels), and the widths on both sides of that range
+@pytest.mark.parametrize("M,C", [(500, 256), (500, 257), (333, 768), (1000, 1024), (129, 2033), (65, 2048), (97, 2049)])
+def test_l1bn_wide_block_columns(sq, M, C):
+    print(f"l1bn wide M={M} C={C}", flush=True)
+    X, gamma, beta, dy = _inputs(M, C, seed=M + C, relu=False)
+    _check_against_oracle(sq, X, gamma, beta, dy)
