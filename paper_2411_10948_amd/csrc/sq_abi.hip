@@ -302,10 +302,8 @@ sq_status sq_quantize_tensor(const float* T, int64_t rows, int64_t cols, int64_t
     const QuantCfg cfg = make_cfg(p);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t* partial = static_cast<uint32_t*>(workspace);
-    int64_t slabs = 0;
-    SQ_TRY(hip_status(launch_colmax(T, rows, cols, ld, partial, &slabs, s), "colmax"));
-    SQ_TRY(hip_status(launch_finalize_tensor(partial, slabs, cols, cfg.Q, partial + slabs * cols, scale, s),
-                      "finalize"));
+    SQ_TRY(hip_status(launch_colmax_finalize_tensor(T, rows, cols, ld, cfg.Q, partial, scale, s),
+                      "abs-max and finalize"));
     SQ_TRY(hip_status(launch_quantize(T, rows, cols, ld, nullptr, scale, cfg, transpose ? nullptr : q, ld_q,
                                       transpose ? q : nullptr, ld_q, nullptr, s, PadGrid(), transpose == 2),
                       "quantize"));
@@ -841,10 +839,8 @@ sq_status sq_quantize_input_conv(const float* X, int64_t N, int64_t H, int64_t W
     const QuantCfg cfg = make_cfg(p);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t* partial = static_cast<uint32_t*>(workspace);
-    int64_t slabs = 0;
-    SQ_TRY(hip_status(launch_colmax(X, M, C_in, ld_X, partial, &slabs, s), "colmax"));
-    SQ_TRY(hip_status(launch_finalize_tensor(partial, slabs, C_in, cfg.Q, partial + slabs * C_in, scale, s),
-                      "finalize"));
+    SQ_TRY(hip_status(launch_colmax_finalize_tensor(X, M, C_in, ld_X, cfg.Q, partial, scale, s),
+                      "abs-max and finalize"));
     // input pixel (n, ih, iw) at grid column n Hp Wp + (ih + PH) Wp + iw + PW
     PadGrid pg;
     pg.Wo = (uint32_t)W;
@@ -893,8 +889,8 @@ static sq_status quantize_grad_conv_impl(const float* dY, int64_t N, int64_t H, 
     const int64_t ext_max = fold_ext_max(C_out, cfg);
     if (ranges) {
         if (C_out > 0)
-            SQ_TRY(hip_status(launch_finalize_grad(ranges, range_slabs, C_out, cfg, partial, group, scale, layout,
-                                                   ext_max, s),
+            SQ_TRY(hip_status(launch_finalize_ranges(ranges, range_slabs, C_out, cfg, partial, group, scale, layout,
+                                                     ext_max, s),
                               "finalize"));
     } else {
         SQ_TRY(hip_status(launch_colmax_finalize_grad(dY, M, C_out, ld_dY, cfg, partial, group, scale, layout,
@@ -1052,7 +1048,7 @@ sq_status sq_quantize_grad_from_ranges(const float* dY, int64_t M, int64_t C_out
     uint32_t* rbits = static_cast<uint32_t*>(workspace);
     const int64_t ext_max = fold_ext_max(C_out, cfg);
     if (C_out > 0)
-        SQ_TRY(hip_status(launch_finalize_grad(ranges, range_slabs, C_out, cfg, rbits, group, scale, layout, ext_max, s),
+        SQ_TRY(hip_status(launch_finalize_ranges(ranges, range_slabs, C_out, cfg, rbits, group, scale, layout, ext_max, s),
                           "finalize"));
     SQ_TRY(hip_status(launch_quantize(dY, M, C_out, ld_dY, group, scale, cfg, q_fold, ld_fold, q_t, ld_t,
                                       layout + kLayoutHeader + ext_max, s, PadGrid(), tiled_of(p)),
@@ -1177,12 +1173,10 @@ sq_status sq_l1bn_backward(const float* dy, int64_t M, int64_t C, int64_t ld_dy,
     uint32_t* partial = reinterpret_cast<uint32_t*>(base + w.quant);
     int32_t* lay = reinterpret_cast<int32_t*>(base + w.layout);
     int8_t* codes = reinterpret_cast<int8_t*>(base + w.codes);
-    int64_t slabs = 0;
-    SQ_TRY(hip_status(launch_colmax(dy, M, C, ld_dy, partial, &slabs, s), "colmax"));
     // the groups and the scale do not depend on the fold (only the dgrad
     // operand does), so the finalize skips the fold plan: ext_max = 0
-    SQ_TRY(hip_status(launch_finalize_grad(partial, slabs, C, cfg, partial + slabs * C, group, gscale, lay, 0, s),
-                      "finalize"));
+    SQ_TRY(hip_status(launch_colmax_finalize_grad(dy, M, C, ld_dy, cfg, partial, group, gscale, lay, 0, s),
+                      "abs-max and finalize"));
     // canonical codes (no fold descriptor: every channel in its own column, unshifted)
     SQ_TRY(hip_status(launch_quantize(dy, M, C, ld_dy, group, gscale, cfg, codes, w.ldc, nullptr, 0, nullptr, s),
                       "quantize"));

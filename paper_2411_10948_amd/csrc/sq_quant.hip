@@ -7,12 +7,10 @@
 //                    channel per row slab (plain stores, no atomics) and one
 //                    per block
 //   finalize         r_max, group ids (power-of-two thresholds, Sec. 3.1),
-//                    scales, flags, and the fold layout for dgrad: one block
-//                    (k_finalize_grad) for few channels, else the group kernel
-//                    (k_final_groups_slabs, which also combines the slabs per
-//                    channel) and the placement kernel (k_final_place);
-//                    k_colmax_reduce + k_final_groups serve channel ranges
-//                    that come from the producer of dY
+//                    scales, flags, and the fold layout for dgrad:
+//                    k_final_groups over 64-channel groups and, with several
+//                    fold windows, k_final_place; k_colmax_reduce before them
+//                    for channel ranges that come from the producer of dY
 //   k_quantize       scale, round (ties-to-even or Philox stochastic rounding,
 //                    App. B Eq. "sq"), clamp; writes the shift-folded dgrad
 //                    operand row-major and the codes transposed
@@ -220,9 +218,14 @@ __device__ __forceinline__ uint32_t reduce_slabs(const uint32_t* __restrict__ pa
 // ---------------------------------------------------------------------------
 // Block-wide helpers (any multiple of 64 threads up to 1024).
 // ---------------------------------------------------------------------------
-__device__ uint32_t block_max_u32(uint32_t v, uint32_t* sh) {
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
+    return v;
+}
+
+__device__ uint32_t block_max_u32(uint32_t v, uint32_t* sh) {
+    v = wave_max(v);
     const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
     __syncthreads();
     if ((threadIdx.x & 63) == 0) sh[w] = v;
@@ -233,99 +236,54 @@ __device__ uint32_t block_max_u32(uint32_t v, uint32_t* sh) {
     return v;
 }
 
-// Second level for many channels: rbits[c] = max over slabs, and the block's
-// maximum in bmax[blockIdx.x].
-constexpr int kRedThreads = 256;
+// ---------------------------------------------------------------------------
+// Second level of the abs-max.  A block of 16 waves takes kFinCh = 64
+// consecutive channels, one per lane: wave w reads the slab maxima of slabs w,
+// w + 16, ... (coalesced 256-byte row segments, 8 in flight) and the waves
+// combine in LDS.  The result is valid in wave 0.
+// ---------------------------------------------------------------------------
+constexpr int kFinCh = 64, kFinWaves = 16, kFinThreads = 64 * kFinWaves;
 
-// kRedLanes threads per channel share its slabs (slab s goes to lane s mod
-// kRedLanes), combined in LDS: a block of kRedThreads channels uses
-// kRedLanes * kRedThreads threads.
-constexpr int kRedLanes = 4;
-__global__ __launch_bounds__(kRedThreads * kRedLanes) void k_colmax_reduce(const uint32_t* __restrict__ partial,
-                                                                           int64_t S, int64_t C,
-                                                                           uint32_t* __restrict__ rbits,
-                                                                           uint32_t* __restrict__ bmax) {
-    __shared__ uint32_t lanes[kRedLanes][kRedThreads];
-    __shared__ uint32_t shu[kRedThreads * kRedLanes / 64];
-    const int ch = threadIdx.x % kRedThreads, ln = threadIdx.x / kRedThreads;
-    const int64_t c = (int64_t)blockIdx.x * kRedThreads + ch;
-    uint32_t a[4] = {0u, 0u, 0u, 0u};
+__device__ __forceinline__ uint32_t slab_max64(const uint32_t* partial, int64_t S, int64_t C,
+                                               uint32_t (*lanes)[kFinCh]) {
+    const int ch = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t c = (int64_t)blockIdx.x * kFinCh + ch;
+    uint32_t a[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
     if (c < C) {
-        int64_t s = ln;
-        for (; s + 3 * kRedLanes < S; s += 4 * kRedLanes) {
+        int64_t sl = w;
+        for (; sl + 7 * kFinWaves < S; sl += 8 * kFinWaves) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] = max(a[u], partial[(s + u * kRedLanes) * C + c]);
+            for (int u = 0; u < 8; ++u) a[u] = max(a[u], partial[(sl + u * kFinWaves) * C + c]);
         }
-        for (; s < S; s += kRedLanes) a[0] = max(a[0], partial[s * C + c]);
+        // rest: the row index clamped to the last slab, so the loads issue
+        // back to back (a maximum does not mind a repeated row)
+        if (sl < S) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) a[u] = max(a[u], partial[min(sl + u * kFinWaves, S - 1) * C + c]);
+        }
     }
-    lanes[ln][ch] = max(max(a[0], a[1]), max(a[2], a[3]));
+    lanes[w][ch] = max(max(max(a[0], a[1]), max(a[2], a[3])), max(max(a[4], a[5]), max(a[6], a[7])));
     __syncthreads();
     uint32_t r = 0u;
-    if (ln == 0) {
+    if (w == 0) {
 #pragma unroll
-        for (int l = 0; l < kRedLanes; ++l) r = max(r, lanes[l][ch]);
-        if (c < C) rbits[c] = r;
+        for (int i = 0; i < kFinWaves; ++i) r = max(r, lanes[i][ch]);
     }
-    r = block_max_u32(r, shu);
-    if (threadIdx.x == 0) bmax[blockIdx.x] = r;
+    return r;
 }
 
-// Channel ranges for fewer channels than threads: W channel units x L slab
-// lanes, combined through LDS (lanes holds 4 * kFinThreads words).  A unit is
-// 4 channels read as one 16-byte load when C is a multiple of 4, else 1.
-// Thread tid < C returns r_{tid}; the others 0.
-constexpr int kFinThreads = 1024;
-
-__device__ uint32_t small_channel_ranges(const uint32_t* __restrict__ partial, int64_t S, int64_t C,
-                                         uint32_t* lanes) {
-    const int tid = threadIdx.x;
-    const bool v4 = (C & 3) == 0;
-    const int units = v4 ? (int)(C / 4) : (int)C;
-    int W = 1;
-    while (W < units) W <<= 1;
-    const int L = kFinThreads / W;
-    const int cl = tid % W, lane = tid / W;
-    uint32_t a[4] = {0u, 0u, 0u, 0u};
-    if (cl < units) {
-        if (v4) {
-            const uint32_t* base = partial + 4 * (int64_t)cl;
-            int64_t sl = lane;
-            for (; sl + 7 * (int64_t)L < S; sl += 8 * (int64_t)L) {
-                uint4 v[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const uint4*>(base + (sl + u * (int64_t)L) * C);
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    a[0] = max(a[0], v[u].x); a[1] = max(a[1], v[u].y);
-                    a[2] = max(a[2], v[u].z); a[3] = max(a[3], v[u].w);
-                }
-            }
-            for (; sl < S; sl += L) {
-                const uint4 v = *reinterpret_cast<const uint4*>(base + sl * C);
-                a[0] = max(a[0], v.x); a[1] = max(a[1], v.y); a[2] = max(a[2], v.z); a[3] = max(a[3], v.w);
-            }
-        } else {
-            uint32_t b[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-            int64_t sl = lane;
-            for (; sl + 7 * (int64_t)L < S; sl += 8 * (int64_t)L) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) b[u] = max(b[u], partial[(sl + u * (int64_t)L) * C + cl]);
-            }
-            for (; sl < S; sl += L) b[0] = max(b[0], partial[sl * C + cl]);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) a[0] = max(a[0], b[u]);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) lanes[4 * tid + k] = a[k];
-    __syncthreads();
-    uint32_t r = 0u;
-    if (tid < C) {
-        const int q = v4 ? tid / 4 : tid, k = v4 ? tid % 4 : 0;
-        for (int l = 0; l < L; ++l) r = max(r, lanes[4 * (l * W + q) + k]);
-    }
-    __syncthreads();
-    return r;
+// Channel ranges rbits[c] and each block's maximum bmax[blockIdx.x], for slab
+// maxima that come from the producer of dY (no block maxima with them).
+__global__ __launch_bounds__(kFinThreads) void k_colmax_reduce(const uint32_t* __restrict__ partial, int64_t S,
+                                                               int64_t C, uint32_t* __restrict__ rbits,
+                                                               uint32_t* __restrict__ bmax) {
+    __shared__ uint32_t lanes[kFinWaves][kFinCh];
+    uint32_t r = slab_max64(partial, S, C, lanes);
+    if (threadIdx.x >= 64) return;
+    const int64_t c = (int64_t)blockIdx.x * kFinCh + threadIdx.x;
+    if (c < C) rbits[c] = r;
+    r = wave_max(r);
+    if (threadIdx.x == 0) bmax[blockIdx.x] = r;
 }
 
 // Group of a channel: the smallest j < N_G - 1 with r_c * 2^(j+1) > r_max,
@@ -351,481 +309,242 @@ __device__ __forceinline__ sq_scale make_scale(uint32_t mb, float Qf) {
     return s;
 }
 
-// Shift windows of the fold (the layout is documented in sq_internal.h),
-// computed by one thread from the number of channels at each shift.
-struct FoldPlan {
-    int nr, main_r, D, H, F;
-    int win_of[kMaxRegions];      // region of each shift value
-    int base[kMaxRegions];        // lowest shift of each region
-    int cnt[kMaxRegions];         // channels of each region
-    int ext_start[kMaxRegions];   // first appended column (non-main regions)
-    int flat[kMaxRegions];        // first flat K column
-    int run[kMaxRegions];         // channels ranked so far
-};
-
-// The plan is computed by one thread in registers (every loop has a
-// compile-time bound of kMaxRegions shift values) and stored to LDS once.
-// Window of shift value s: key 0 for the main window [B*, B* + T], key j > 0
-// for [B* + j (T + 1), ...] above it, key -j for the j-th window below it
-// (its base clipped at 0).  Regions are the non-empty windows (and always the
-// main one) in descending key order, which is descending base.
-__device__ void make_fold_plan(const int* n_lds, int S, int T, int64_t C, FoldPlan& P) {
-    int n[kMaxRegions];
-#pragma unroll
-    for (int s = 0; s < kMaxRegions; ++s) n[s] = s <= S ? n_lds[s] : 0;
-    // the window [B, B + T] holding the most channels (lowest B on ties)
-    int bstar = 0, best = -1;
-#pragma unroll
-    for (int B = 0; B < kMaxRegions; ++B) {
-        if (B > (S - T > 0 ? S - T : 0)) break;
-        int c = 0;
-#pragma unroll
-        for (int s = 0; s < kMaxRegions; ++s) c += (s >= B && s <= B + T) ? n[s] : 0;
-        if (c > best) { best = c; bstar = B; }
-    }
-    auto key_of = [&](int s) { return s >= bstar ? (s - bstar) / (T + 1) : -1 - (bstar - 1 - s) / (T + 1); };
-    // channels per key, keys -7 .. 7
-    int kc[2 * kMaxRegions - 1];
-#pragma unroll
-    for (int k = 0; k < 2 * kMaxRegions - 1; ++k) kc[k] = 0;
-#pragma unroll
-    for (int s = 0; s < kMaxRegions; ++s) {
-        const int key = key_of(s) + (kMaxRegions - 1);
-#pragma unroll
-        for (int k = 0; k < 2 * kMaxRegions - 1; ++k) kc[k] += (k == key && s <= S) ? n[s] : 0;
-    }
-    // regions in descending key order
-    int nr = 0, main_r = 0, flat = 0, ext = 0, H = 0;
-    int region_of_key[2 * kMaxRegions - 1];
-#pragma unroll
-    for (int k = 2 * kMaxRegions - 2; k >= 0; --k) {
-        const int key = k - (kMaxRegions - 1);
-        region_of_key[k] = -1;
-        if (!(kc[k] > 0 || key == 0)) continue;
-        const int lo = key >= 0 ? bstar + key * (T + 1) : max(0, bstar + key * (T + 1));
-        const int r = nr++;
-        region_of_key[k] = r;
-        P.base[r] = lo;
-        P.cnt[r] = kc[k];
-        P.flat[r] = flat;
-        P.run[r] = 0;
-        if (key == 0) {
-            main_r = r;
-            P.ext_start[r] = -1;
-            H = ext;
-            flat += (int)round_up(C, kFoldPad);
-        } else {
-            P.ext_start[r] = ext;
-            ext += (int)round_up(kc[k], kFoldPad);
-            flat += (int)round_up(kc[k], kFoldPad);
-        }
-    }
-#pragma unroll
-    for (int s = 0; s < kMaxRegions; ++s) {
-        const int k = key_of(s) + (kMaxRegions - 1);
-        int r = 0;
-#pragma unroll
-        for (int kk = 0; kk < 2 * kMaxRegions - 1; ++kk) r = kk == k ? region_of_key[kk] : r;
-        P.win_of[s] = s <= S ? r : 0;
-    }
-    P.nr = nr;
-    P.main_r = main_r;
-    P.D = ext;
-    P.H = H;
-    P.F = P.base[nr - 1];
-}
-
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
 // ---------------------------------------------------------------------------
-// Finalize for the gradient quantizer (one block): r_max, scales and flags,
-// the group of every channel (channel c handled by thread c mod kFinThreads),
-// the shift windows of the fold, and each channel's place in q_fold.  The
-// appended columns of a region list its channels in ascending order; a
-// channel's rank comes from wave ballots plus per-wave totals in LDS.
+// Finalize of the gradient quantizer, over blocks of kFinCh channels:
+//   k_final_groups  r_max (the maximum of the abs-max pass's block maxima, or
+//     of the block's own channels when there is one block), the scale and
+//     flags, and the group of each of the block's channels; with one fold
+//     window the descriptors and the header too, else the block's count of
+//     channels per shift;
+//   k_final_place   (several windows) every wave plans the windows from the
+//     summed counts (the same plan everywhere), takes its region offsets from
+//     the counts of the 64-channel groups before it, and ranks its appended
+//     channels with wave ballots; block 0 writes the header and the padding.
+// Both are bound by latency: a launch of this size takes 2.5 to 4 us whatever
+// it does, so the work is spread until its own chain is shorter than that.
+// One block reading every slab maximum and planning on one thread took 17 to
+// 22 us (several windows, 768 channels x 169 slabs); these two take
+// 9.4 us (16384 x 768 activations: finalize 21.9 -> 9.4 us).
 // ---------------------------------------------------------------------------
-constexpr int kFinWaves = kFinThreads / 64;
-constexpr int kChunk = 16;   // rounds of kFinThreads channels whose loads are batched
-
-__global__ __launch_bounds__(kFinThreads) void k_finalize_grad(const uint32_t* __restrict__ partial, int64_t S,
-                                                               int64_t C, QuantCfg cfg,
-                                                               const uint32_t* __restrict__ rbits,
-                                                               const uint32_t* __restrict__ bmax, int64_t nb,
-                                                               uint8_t* __restrict__ group,
-                                                               sq_scale* __restrict__ scale,
-                                                               int32_t* __restrict__ layout, int64_t ext_max) {
-    __shared__ uint32_t shu[16];
-    __shared__ int cnt[kChunk][kFinWaves][kMaxRegions];
-    __shared__ int pre[kChunk][kFinWaves][kMaxRegions];
-    __shared__ int tot[kChunk][kMaxRegions];
-    __shared__ int roundpre[kChunk][kMaxRegions];
-    __shared__ uint32_t lanes[4 * kFinThreads];
-    __shared__ FoldPlan P;
-    __shared__ int nsh[kMaxRegions];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int Sh = cfg.num_groups - 1;   // largest shift
-
-    uint32_t mb = 0u, r_small = 0u;
-    if (C < kFinThreads) {
-        r_small = small_channel_ranges(partial, S, C, lanes);
-        mb = r_small;
-    } else {
-        for (int64_t i = tid; i < nb; i += kFinThreads) mb = max(mb, bmax[i]);
+__global__ __launch_bounds__(kFinThreads) void k_final_groups(const uint32_t* partial, int64_t S,
+                                                              const uint32_t* __restrict__ block_max, int64_t nbm,
+                                                              int64_t C, QuantCfg cfg, uint8_t* __restrict__ group,
+                                                              sq_scale* __restrict__ scale,
+                                                              int32_t* __restrict__ layout, int64_t ext_max,
+                                                              int32_t* hist, int hist_ld) {
+    __shared__ uint32_t lanes[kFinWaves][kFinCh];
+    __shared__ uint32_t wmax[kFinWaves];
+    const int tid = threadIdx.x, lane = tid & 63;
+    uint32_t mb = 0u;
+    if (gridDim.x > 1) {
+        for (int64_t i = tid; i < nbm; i += kFinThreads) mb = max(mb, block_max[i]);
+        mb = wave_max(mb);
+        if (lane == 0) wmax[tid >> 6] = mb;
     }
-    mb = block_max_u32(mb, shu);
+    const uint32_t rb = slab_max64(partial, S, C, lanes);   // ends in a barrier, which covers wmax too
+    if (tid >= 64) return;
+    if (gridDim.x > 1) mb = wave_max(lane < kFinWaves ? wmax[lane] : 0u);
+    else mb = wave_max(rb);
     const sq_scale sc = make_scale(mb, (float)cfg.Q);
-    if (tid == 0) *scale = sc;
-    const bool flagged = sc.flags != 0u;
-
-    int32_t* ext = layout + kLayoutHeader;
-    int32_t* desc = ext + ext_max;
-    if (ext_max == 0) {
-        // every shift fits int8 (N_G - 1 <= T): one window at base 0, the
-        // code of channel c stored as code << sh_c in its own column
-        for (int64_t c = tid; c < C; c += kFinThreads) {
-            const uint32_t rb = C < kFinThreads ? r_small : rbits[c];
-            const int g = flagged ? Sh : group_of(__uint_as_float(rb), sc.r_max, cfg.num_groups);
-            group[c] = (uint8_t)g;
-            desc[c] = Sh - g;
-        }
-        if (tid < kLayoutHeader) {
-            int v = 0;
-            if (tid == kLayNR) v = 1;
-            else if (tid == kLayBase) v = (int)fold_ext_base(C);
-            else if (tid > kLayStart && tid < kLayStart + kMaxRegions) v = 0x7FFFFFFF;
-            layout[tid] = v;
-        }
-        return;
-    }
-
-    // Channel c = k * kFinThreads + tid is handled by this thread in round k;
-    // rounds are processed in chunks of kChunk with their loads batched.
-    const int64_t rounds = (C + kFinThreads - 1) / kFinThreads;
-
-    // groups and the number of channels at each shift
-    int hist[kMaxRegions];
-#pragma unroll
-    for (int s = 0; s < kMaxRegions; ++s) hist[s] = 0;
-    for (int64_t k0 = 0; k0 < rounds; k0 += kChunk) {
-        uint32_t rb[kChunk];
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k) {
-            const int64_t c = (k0 + k) * kFinThreads + tid;
-            rb[k] = c < C ? (C < kFinThreads ? r_small : rbits[c]) : 0u;
-        }
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k) {
-            const int64_t c = (k0 + k) * kFinThreads + tid;
-            if (c >= C) continue;
-            const int g = flagged ? Sh : group_of(__uint_as_float(rb[k]), sc.r_max, cfg.num_groups);
-            group[c] = (uint8_t)g;
-#pragma unroll
-            for (int s = 0; s < kMaxRegions; ++s) hist[s] += (Sh - g) == s;
-        }
-    }
-#pragma unroll
-    for (int s = 0; s < kMaxRegions; ++s) {
-        const int v = wave_sum(hist[s]);
-        if (lane == 0) cnt[0][wave][s] = v;
-    }
-    __syncthreads();
-    if (tid < kMaxRegions) {
-        int v = 0;
-        for (int w = 0; w < kFinWaves; ++w) v += cnt[0][w][tid];
-        nsh[tid] = v;
-    }
-    __syncthreads();
-    if (tid == 0) make_fold_plan(nsh, Sh, cfg.T, C, P);
-    __syncthreads();
-
-    // place of every channel: descriptor ((pos + 1) << 4) | t, and the
-    // appended-column list.  Appended channels are ranked per round with wave
-    // ballots; cnt[k][w][q] counts those of region q in wave w of round k,
-    // and pre[k][w][q] is the number of region-q channels before that wave
-    // (earlier chunks, earlier rounds, earlier waves).
-    const int nr = P.nr, main_r = P.main_r;
-    const uint64_t below = (1ull << lane) - 1ull;
-    for (int64_t k0 = 0; k0 < rounds; k0 += kChunk) {
-        uint8_t gk[kChunk];
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k) {
-            const int64_t c = (k0 + k) * kFinThreads + tid;
-            gk[k] = c < C ? group[c] : (uint8_t)0;   // written by this thread above
-        }
-        int code_r[kChunk], rank[kChunk];
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k) {
-            const int64_t c = (k0 + k) * kFinThreads + tid;
-            int r = main_r;
-            if (c < C) r = P.win_of[Sh - (int)gk[k]];
-            code_r[k] = r;
-            const bool is_ext = c < C && r != main_r;
-            rank[k] = 0;
-            if (k0 + k >= rounds) continue;   // uniform: no channel of this round exists
-            for (int q = 0; q < nr; ++q) {
-                const uint64_t m = __ballot(is_ext && r == q);
-                if (is_ext && r == q) rank[k] = __popcll(m & below);
-                if (lane == 0) cnt[k][wave][q] = __popcll(m);
-            }
-        }
-        __syncthreads();
-        // thread (k, q): exclusive prefix over the waves of round k
-        if (tid < kChunk * kMaxRegions) {
-            const int k = tid / kMaxRegions, q = tid % kMaxRegions;
-            int acc = 0;
-            if (q < nr && k0 + k < rounds)
-                for (int w = 0; w < kFinWaves; ++w) {
-                    pre[k][w][q] = acc;
-                    acc += cnt[k][w][q];
-                }
-            tot[k][q] = acc;
-        }
-        __syncthreads();
-        // thread q: prefix over the rounds, plus the channels of earlier chunks
-        if (tid < nr) {
-            int acc = P.run[tid];
-            for (int k = 0; k < kChunk && k0 + k < rounds; ++k) {
-                roundpre[k][tid] = acc;
-                acc += tot[k][tid];
-            }
-            P.run[tid] = acc;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kChunk; ++k) {
-            const int64_t c = (k0 + k) * kFinThreads + tid;
-            if (c >= C) continue;
-            const int r = code_r[k];
-            const int t = (Sh - (int)gk[k]) - P.base[r];
-            int pos = -1;
-            if (r != main_r) {
-                pos = P.ext_start[r] + roundpre[k][r] + pre[k][wave][r] + rank[k];
-                ext[pos] = (int32_t)c;
-            }
-            desc[c] = ((pos + 1) << 4) | t;
-        }
-        __syncthreads();   // cnt / pre / roundpre free for the next chunk
-    }
-    for (int r = 0; r < nr; ++r) {
-        if (r == main_r) continue;
-        const int padded = (int)round_up(P.cnt[r], kFoldPad);
-        for (int i = P.cnt[r] + tid; i < padded; i += kFinThreads) ext[P.ext_start[r] + i] = -1;
-    }
-    if (tid < kLayoutHeader) {
-        int v = 0;
-        if (tid == kLayNR) v = nr;
-        else if (tid == kLayD) v = P.D;
-        else if (tid == kLayBase) v = (int)fold_ext_base(C);
-        else if (tid == kLayF) v = P.F;
-        else if (tid == kLayH) v = P.H;
-        else if (tid >= kLayStart && tid < kLayStart + kMaxRegions)
-            v = tid - kLayStart < nr ? P.flat[tid - kLayStart] : 0x7FFFFFFF;
-        else if (tid >= kLayShift && tid < kLayShift + kMaxRegions) {
-            const int r = tid - kLayShift;
-            v = (r > 0 && r < nr) ? P.base[r - 1] - P.base[r] : 0;
-        }
-        layout[tid] = v;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Finalize for many channels (C >= kFinThreads), spread over the blocks of
-// the second reduction level (kRedThreads channels each) in two kernels:
-//   k_final_groups: r_max from the per-block maxima (every block), the group
-//     of each of its channels, and the block's count of channels per shift;
-//     with one fold window the descriptors and the header too;
-//   k_final_place:  every block plans the windows from the summed counts
-//     (the same plan everywhere), takes its region offsets from the counts
-//     of the blocks before it, and ranks its appended channels with wave
-//     ballots; block 0 writes the header and the region padding.
-// ---------------------------------------------------------------------------
-// Groups of the block's channels (thread t < kRedThreads: channel
-// blockIdx.x * kRedThreads + t with range bits rb; the other threads pass
-// nothing), the descriptors and header with one fold window, else the
-// block's count of channels per shift.  Every thread of the block calls it.
-__device__ void final_groups_body(int64_t c, uint32_t rb, const sq_scale& sc, int64_t C, const QuantCfg& cfg,
-                                  uint8_t* __restrict__ group, int32_t* __restrict__ layout, int64_t ext_max,
-                                  int32_t* __restrict__ hist, int* cnt) {
-    const int tid = threadIdx.x;
-    const int Sh = cfg.num_groups - 1;
+    if (blockIdx.x == 0 && lane == 0) *scale = sc;
+    const int Sh = cfg.num_groups - 1;   // largest shift
+    const int64_t c = (int64_t)blockIdx.x * kFinCh + lane;
     int sh = -1;
-    if (tid < kRedThreads && c < C) {
+    if (c < C) {
         const int g = sc.flags ? Sh : group_of(__uint_as_float(rb), sc.r_max, cfg.num_groups);
         group[c] = (uint8_t)g;
         sh = Sh - g;
     }
     if (ext_max == 0) {
-        // one window at base 0: the code of channel c is stored as code << sh_c in its own column
-        int32_t* desc = layout + kLayoutHeader;
-        if (tid < kRedThreads && c < C) desc[c] = sh;
-        if (blockIdx.x == 0 && tid < kLayoutHeader) {
+        // every shift fits int8 (N_G - 1 <= T): one window at base 0, the
+        // code of channel c stored as code << sh_c in its own column
+        if (c < C) layout[kLayoutHeader + c] = sh;
+        if (blockIdx.x == 0 && lane < kLayoutHeader) {
             int v = 0;
-            if (tid == kLayNR) v = 1;
-            else if (tid == kLayBase) v = (int)fold_ext_base(C);
-            else if (tid > kLayStart && tid < kLayStart + kMaxRegions) v = 0x7FFFFFFF;
-            layout[tid] = v;
+            if (lane == kLayNR) v = 1;
+            else if (lane == kLayBase) v = (int)fold_ext_base(C);
+            else if (lane > kLayStart && lane < kLayStart + kMaxRegions) v = 0x7FFFFFFF;
+            layout[lane] = v;
         }
         return;
     }
-    if (tid < kMaxRegions) cnt[tid] = 0;
-    __syncthreads();
+    int n = 0;
 #pragma unroll
     for (int q = 0; q < kMaxRegions; ++q) {
-        const uint64_t m = __ballot(sh == q);
-        if ((tid & 63) == 0 && m) atomicAdd(&cnt[q], __popcll(m));
+        const int m = __popcll(__ballot(sh == q));
+        if (lane == q) n = m;
     }
-    __syncthreads();
-    if (tid < kMaxRegions) hist[blockIdx.x * kMaxRegions + tid] = cnt[tid];
+    if (lane < kMaxRegions) hist[(int64_t)blockIdx.x * hist_ld + lane] = n;
 }
 
-__global__ __launch_bounds__(kRedThreads) void k_final_groups(const uint32_t* __restrict__ rbits,
-                                                               const uint32_t* __restrict__ bmax, int64_t nb,
-                                                               int64_t C, QuantCfg cfg, uint8_t* __restrict__ group,
-                                                               sq_scale* __restrict__ scale, int32_t* __restrict__ layout,
-                                                               int64_t ext_max, int32_t* __restrict__ hist) {
-    __shared__ uint32_t shu[kRedThreads / 64];
-    __shared__ int cnt[kMaxRegions];
-    const int tid = threadIdx.x;
-    uint32_t mb = 0u;
-    for (int64_t i = tid; i < nb; i += kRedThreads) mb = max(mb, bmax[i]);
-    mb = block_max_u32(mb, shu);
-    const sq_scale sc = make_scale(mb, (float)cfg.Q);
-    if (blockIdx.x == 0 && tid == 0) *scale = sc;
-    const int64_t c = (int64_t)blockIdx.x * kRedThreads + tid;
-    final_groups_body(c, c < C ? rbits[c] : 0u, sc, C, cfg, group, layout, ext_max, hist, cnt);
-}
+// Shift windows of the fold (the layout is documented in sq_internal.h), held
+// across the lanes of a wave; every lane must call it.  Window of shift value
+// s: key 0 for the main window [B*, B* + T], key j > 0 for [B* + j (T + 1),
+// ...] above it, key -j for the j-th window below it (its base clipped at 0).
+// Regions are the non-empty windows (and always the main one) in descending
+// key order, which is descending base.  Lane k holds the window of key
+// k - kKey0; lane s < kMaxRegions the window lane `win` of shift s.
+constexpr int kKey0 = kMaxRegions - 1, kKeys = 2 * kMaxRegions - 1;
+struct WavePlan {
+    int win;                 // lane s: lane of the window of shift s
+    int cnt, width, base;    // channels, padded columns and lowest shift of this lane's window
+    int ext_start, flat;     // first appended column (other than the main window), first flat K column
+    int before;              // appended channels of this window in earlier 64-channel groups
+    uint32_t present;        // windows that are regions, a bit per lane (uniform)
+    int bstar;
+};
 
-// The same from the abs-max pass's outputs directly: r_max from its block
-// maxima, and each channel's range from its slab maxima (kRedLanes threads
-// per channel, as k_colmax_reduce), one launch fewer.
-__global__ __launch_bounds__(kRedThreads * kRedLanes) void k_final_groups_slabs(
-    const uint32_t* __restrict__ partial, int64_t S, const uint32_t* __restrict__ block_max, int64_t nbm, int64_t C,
-    QuantCfg cfg, uint8_t* __restrict__ group, sq_scale* __restrict__ scale, int32_t* __restrict__ layout,
-    int64_t ext_max, int32_t* __restrict__ hist) {
-    __shared__ uint32_t lanes[kRedLanes][kRedThreads];
-    __shared__ uint32_t shu[kRedThreads * kRedLanes / 64];
-    __shared__ int cnt[kMaxRegions];
-    const int tid = threadIdx.x;
-    const int ch = tid % kRedThreads, ln = tid / kRedThreads;
-    const int64_t c = (int64_t)blockIdx.x * kRedThreads + ch;
-    uint32_t a[4] = {0u, 0u, 0u, 0u};
-    if (c < C) {
-        int64_t s = ln;
-        for (; s + 3 * kRedLanes < S; s += 4 * kRedLanes) {
+__device__ __forceinline__ int lane_val(int v, int l) { return __builtin_amdgcn_readlane(v, l); }
+
+// n, nb: channels at shift `lane` in all groups and in the groups before the caller's
+__device__ __forceinline__ WavePlan wave_fold_plan(int n, int nb, int S, int T, int64_t C) {
+    const int lane = threadIdx.x & 63;
+    WavePlan P;
+    n = lane <= S ? n : 0;
+    // the window [B, B + T] holding the most channels (lowest B on ties)
+    int c = 0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] = max(a[u], partial[(s + u * kRedLanes) * C + c]);
-        }
-        for (; s < S; s += kRedLanes) a[0] = max(a[0], partial[s * C + c]);
+    for (int j = 0; j < kMaxRegions; ++j) {
+        const int v = __shfl(n, lane + j, 64);
+        c += j <= T && lane + j <= S ? v : 0;
     }
-    uint32_t mb = 0u;
-    for (int64_t i = tid; i < nbm; i += kRedThreads * kRedLanes) mb = max(mb, block_max[i]);
-    mb = block_max_u32(mb, shu);
-    lanes[ln][ch] = max(max(a[0], a[1]), max(a[2], a[3]));
-    __syncthreads();
-    uint32_t rb = 0u;
-    if (ln == 0) {
+    int best = lane <= max(S - T, 0) ? c * kMaxRegions + (kMaxRegions - 1 - lane) : -1;
 #pragma unroll
-        for (int l = 0; l < kRedLanes; ++l) rb = max(rb, lanes[l][ch]);
+    for (int o = 1; o < kMaxRegions; o <<= 1) best = max(best, __shfl_xor(best, o, 64));
+    P.bstar = kMaxRegions - 1 - (lane_val(best, 0) & (kMaxRegions - 1));
+    const int d = lane - P.bstar;
+    P.win = kKey0 + (d >= 0 ? (int)((uint32_t)d / (uint32_t)(T + 1)) : -1 - (int)((uint32_t)(-1 - d) / (uint32_t)(T + 1)));
+    P.cnt = P.before = 0;
+#pragma unroll
+    for (int s = 0; s < kMaxRegions; ++s) {
+        const bool in = s <= S && lane_val(P.win, s) == lane;
+        P.cnt += in ? lane_val(n, s) : 0;
+        P.before += in ? lane_val(nb, s) : 0;
     }
-    const sq_scale sc = make_scale(mb, (float)cfg.Q);
-    if (blockIdx.x == 0 && tid == 0) *scale = sc;
-    final_groups_body(c, rb, sc, C, cfg, group, layout, ext_max, hist, cnt);
+    const int key = lane - kKey0;
+    const bool here = lane < kKeys && (P.cnt > 0 || key == 0);
+    P.present = (uint32_t)__ballot(here);
+    P.base = max(0, P.bstar + key * (T + 1));
+    P.width = here ? (int)round_up(key == 0 ? C : P.cnt, kFoldPad) : 0;
+    P.ext_start = P.flat = 0;
+#pragma unroll
+    for (int k = 0; k < kKeys; ++k) {
+        const int w = lane_val(P.width, k);
+        P.flat += k > lane ? w : 0;
+        P.ext_start += k > lane && k != kKey0 ? w : 0;
+    }
+    return P;
 }
 
-__global__ __launch_bounds__(kRedThreads) void k_final_place(const uint8_t* __restrict__ group,
-                                                              const int32_t* __restrict__ hist, int64_t nb, int64_t C,
-                                                              QuantCfg cfg, int32_t* __restrict__ layout,
-                                                              int64_t ext_max) {
-    __shared__ int tot[kMaxRegions], before[kMaxRegions];
-    __shared__ int wcnt[kRedThreads / 64][kMaxRegions];
-    __shared__ FoldPlan P;
+constexpr int kPlaceThreads = 256;   // four 64-channel groups, one per wave
+
+__global__ __launch_bounds__(kPlaceThreads) void k_final_place(const uint8_t* __restrict__ group,
+                                                               const int32_t* __restrict__ hist, int hist_ld,
+                                                               int64_t nb, int64_t C, QuantCfg cfg,
+                                                               int32_t* __restrict__ layout, int64_t ext_max) {
+    __shared__ int tot[kPlaceThreads / 64][kMaxRegions], bef[kPlaceThreads / 64][kMaxRegions];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int Sh = cfg.num_groups - 1;
-    // channels per shift: all blocks, and the blocks before this one (thread
-    // t sums shift t % 8 over the blocks b = t / 8 (mod 32), then LDS atomics)
-    if (tid < kMaxRegions) { tot[tid] = 0; before[tid] = 0; }
-    __syncthreads();
-    {
-        const int s = tid % kMaxRegions;
-        int vt = 0, vb = 0;
-        for (int64_t b = tid / kMaxRegions; b < nb; b += kRedThreads / kMaxRegions) {
-            const int h = hist[b * kMaxRegions + s];
-            vt += h;
-            vb += b < (int64_t)blockIdx.x ? h : 0;
-        }
-        if (vt) atomicAdd(&tot[s], vt);
-        if (vb) atomicAdd(&before[s], vb);
+    const int64_t first = (int64_t)blockIdx.x * (kPlaceThreads / 64);   // this block's first 64-channel group
+    const int64_t c = first * kFinCh + tid;
+    const int g = c < C ? (int)group[c] : Sh;
+    // channels per shift: all groups, and the groups before this block's
+    // (thread t sums shift t % 8 over the groups t / 8 mod 32), then those of
+    // the earlier waves
+    int vt = 0, vb = 0;
+    for (int64_t b = tid / kMaxRegions; b < nb; b += kPlaceThreads / kMaxRegions) {
+        const int h = hist[b * hist_ld + tid % kMaxRegions];
+        vt += h;
+        vb += b < first ? h : 0;
+    }
+    int vw = 0;
+    for (int w = 0; w < wave; ++w)
+        if (lane < kMaxRegions && first + w < nb) vw += hist[(first + w) * hist_ld + lane];
+#pragma unroll
+    for (int o = kMaxRegions; o < 64; o <<= 1) {
+        vt += __shfl_xor(vt, o, 64);
+        vb += __shfl_xor(vb, o, 64);
+    }
+    if (lane < kMaxRegions) {
+        tot[wave][lane] = vt;
+        bef[wave][lane] = vb;
     }
     __syncthreads();
-    if (tid == 0) make_fold_plan(tot, Sh, cfg.T, C, P);
-    __syncthreads();
-    const int nr = P.nr, main_r = P.main_r;
+    vt = 0;
+    if (lane < kMaxRegions) {
+#pragma unroll
+        for (int w = 0; w < kPlaceThreads / 64; ++w) {
+            vt += tot[w][lane];
+            vw += bef[w][lane];
+        }
+    }
+    const WavePlan P = wave_fold_plan(vt, vw, Sh, cfg.T, C);
     int32_t* ext = layout + kLayoutHeader;
     int32_t* desc = ext + ext_max;
-    const int64_t c = (int64_t)blockIdx.x * kRedThreads + tid;
-    const int sh = c < C ? Sh - (int)group[c] : 0;
-    const int r = c < C ? P.win_of[sh] : main_r;
-    const bool is_ext = c < C && r != main_r;
+    const int sh = Sh - g;
+    const int k = __shfl(P.win, sh, 64);   // this channel's window
+    const bool is_ext = c < C && k != kKey0;
     int rank = 0;
-    const uint64_t below = (1ull << lane) - 1ull;
-    for (int q = 0; q < nr; ++q) {
-        const uint64_t m = __ballot(is_ext && r == q);
-        if (is_ext && r == q) rank = __popcll(m & below);
-        if (lane == 0) wcnt[wave][q] = __popcll(m);
+    for (uint32_t m = P.present & ~(1u << kKey0); m; m &= m - 1) {
+        const int q = __builtin_ctz(m);
+        const uint64_t same = __ballot(is_ext && k == q);
+        if (k == q) rank = __popcll(same & ((1ull << lane) - 1ull));
     }
-    __syncthreads();
+    const int base = __shfl(P.base, k, 64), start = __shfl(P.ext_start + P.before, k, 64);
     if (c < C) {
         int pos = -1;
         if (is_ext) {
-            // region offset: appended channels of region r in earlier blocks and waves
-            int off = 0;
-#pragma unroll
-            for (int s2 = 0; s2 < kMaxRegions; ++s2)
-                if (s2 <= Sh && P.win_of[s2] == r) off += before[s2];
-            for (int w = 0; w < wave; ++w) off += wcnt[w][r];
-            pos = P.ext_start[r] + off + rank;
+            pos = start + rank;
             ext[pos] = (int32_t)c;
         }
-        desc[c] = ((pos + 1) << 4) | (sh - P.base[r]);
+        desc[c] = ((pos + 1) << 4) | (sh - base);
     }
-    if (blockIdx.x != 0) return;
-    for (int q = 0; q < nr; ++q) {
-        if (q == main_r) continue;
-        const int padded = (int)round_up(P.cnt[q], kFoldPad);
-        for (int i = P.cnt[q] + tid; i < padded; i += kRedThreads) ext[P.ext_start[q] + i] = -1;
+    if (blockIdx.x != 0 || wave != 0) return;
+    // region padding (fewer than 64 columns each)
+    for (uint32_t m = P.present & ~(1u << kKey0); m; m &= m - 1) {
+        const int q = __builtin_ctz(m);
+        const int i = lane_val(P.cnt, q) + lane;
+        if (i < lane_val(P.width, q)) ext[lane_val(P.ext_start, q) + i] = -1;
     }
-    if (tid < kLayoutHeader) {
+    // header: words 0 .. 7, then region r's start and shift by its window's lane
+    const int nr = __popc(P.present);
+    int D = 0, H = 0;
+#pragma unroll
+    for (int q = 0; q < kKeys; ++q) {
+        const int w = lane_val(P.width, q);
+        D += q != kKey0 ? w : 0;
+        H += q > kKey0 ? w : 0;
+    }
+    const int F = lane_val(P.base, __builtin_ctz(P.present));
+    if (lane < kLayoutHeader) {
+        const bool in_start = lane >= kLayStart && lane < kLayStart + kMaxRegions;
         int v = 0;
-        if (tid == kLayNR) v = nr;
-        else if (tid == kLayD) v = P.D;
-        else if (tid == kLayBase) v = (int)fold_ext_base(C);
-        else if (tid == kLayF) v = P.F;
-        else if (tid == kLayH) v = P.H;
-        else if (tid >= kLayStart && tid < kLayStart + kMaxRegions)
-            v = tid - kLayStart < nr ? P.flat[tid - kLayStart] : 0x7FFFFFFF;
-        else if (tid >= kLayShift && tid < kLayShift + kMaxRegions) {
-            const int q = tid - kLayShift;
-            v = (q > 0 && q < nr) ? P.base[q - 1] - P.base[q] : 0;
-        }
-        layout[tid] = v;
+        if (lane == kLayNR) v = nr;
+        else if (lane == kLayD) v = D;
+        else if (lane == kLayBase) v = (int)fold_ext_base(C);
+        else if (lane == kLayF) v = F;
+        else if (lane == kLayH) v = H;
+        else if (in_start) v = 0x7FFFFFFF;
+        // region starts and shifts below nr are written by the window lanes
+        const bool mine = (in_start && lane - kLayStart < nr) || (lane > kLayShift && lane - kLayShift < nr);
+        if (!mine) layout[lane] = v;
+    }
+    const uint32_t above = lane < kKeys ? P.present >> (lane + 1) : 0u;   // regions before this lane's
+    const int prev = __shfl(P.base, above ? lane + 1 + __builtin_ctz(above) : lane, 64);
+    if (lane < kKeys && (P.present >> lane & 1u)) {
+        const int r = __popc(above);
+        layout[kLayStart + r] = P.flat;
+        if (r > 0) layout[kLayShift + r] = prev - P.base;
     }
 }
 
 // Finalize for per-tensor quantization (one block): the tensor's absolute
-// maximum is the maximum over all slab maxima.
-__global__ __launch_bounds__(kFinThreads) void k_finalize_tensor(const uint32_t* __restrict__ partial, int64_t S,
-                                                                 int64_t C, int Q, const uint32_t* __restrict__ bmax,
-                                                                 int64_t nb, sq_scale* __restrict__ scale) {
+// maximum is the maximum over the abs-max pass's block maxima.
+__global__ __launch_bounds__(kFinThreads) void k_finalize_tensor(const uint32_t* __restrict__ block_max, int64_t nbm,
+                                                                 int Q, sq_scale* __restrict__ scale) {
     __shared__ uint32_t shu[16];
-    __shared__ uint32_t lanes[4 * kFinThreads];
     uint32_t mb = 0u;
-    if (C < kFinThreads) mb = small_channel_ranges(partial, S, C, lanes);
-    else
-        for (int64_t i = threadIdx.x; i < nb; i += kFinThreads) mb = max(mb, bmax[i]);
+    for (int64_t i = threadIdx.x; i < nbm; i += kFinThreads) mb = max(mb, block_max[i]);
     mb = block_max_u32(mb, shu);
     if (threadIdx.x == 0) *scale = make_scale(mb, (float)Q);
 }
@@ -1340,17 +1059,29 @@ ColmaxPlan colmax_plan(int64_t M, int64_t C, bool vec) {
     return p;
 }
 
-int64_t colmax_reduce_blocks(int64_t C) { return C >= kFinThreads ? (C + kRedThreads - 1) / kRedThreads : 0; }
+// 64-channel groups of the finalize (at least one: the scale and header of an
+// empty tensor are written too)
+static int64_t fin_blocks(int64_t C) { return std::max<int64_t>(1, (C + kFinCh - 1) / kFinCh); }
 
 int64_t colmax_workspace_words(int64_t M, int64_t C) {
-    // worst case over both vector widths: slab maxima, channel ranges, the
-    // second level's block maxima and shift counts, the abs-max blocks' maxima
-    int64_t w = 0;
+    // with ranges from the producer: channel ranges and group maxima; else,
+    // worst case over both vector widths, the shift counts and the abs-max
+    // outputs (slab maxima, block maxima).  Never more than the finalize in
+    // blocks of 256 channels took for C >= 1024, so that the tensors a fixed
+    // scratch holds stay the same.
+    const int64_t nb = fin_blocks(C);
+    int64_t w = C + kMaxRegions + nb;
     for (const bool vec : {true, false}) {
         const ColmaxPlan p = colmax_plan(M, C, vec);
-        w = std::max(w, p.slabs * C + C + (1 + kMaxRegions) * colmax_reduce_blocks(C) + p.chunks * p.slabs);
+        const int64_t fin = std::max(kMaxRegions * nb, C + (C >= 1024 ? (1 + kMaxRegions) * ((C + 255) / 256) : 0));
+        w = std::max(w, p.slabs * C + fin + p.chunks * p.slabs);
     }
     return w;
+}
+
+// float4 loads of whole rows need 16-byte aligned rows
+static bool colmax_vec(const float* x, int64_t ld) {
+    return ((ld & 3) == 0) && ((reinterpret_cast<uintptr_t>(x) & 15) == 0);
 }
 
 hipError_t launch_colmax(const float* x, int64_t M, int64_t C, int64_t ld, uint32_t* partial, int64_t* slabs,
@@ -1358,7 +1089,7 @@ hipError_t launch_colmax(const float* x, int64_t M, int64_t C, int64_t ld, uint3
     *slabs = 0;
     if (n_block_max) *n_block_max = 0;
     if (M <= 0 || C <= 0) return hipSuccess;
-    const bool vec = ((ld & 3) == 0) && ((reinterpret_cast<uintptr_t>(x) & 15) == 0);
+    const bool vec = colmax_vec(x, ld);
     const ColmaxPlan p = colmax_plan(M, C, vec);
     *slabs = p.slabs;
     if (n_block_max) *n_block_max = p.chunks * p.slabs;
@@ -1382,72 +1113,53 @@ hipError_t launch_colmax(const float* x, int64_t M, int64_t C, int64_t ld, uint3
     return hipGetLastError();
 }
 
-static hipError_t launch_reduce(const uint32_t* partial, int64_t slabs, int64_t C, uint32_t* rbits, uint32_t* bmax,
-                                hipStream_t s) {
-    const int64_t nb = colmax_reduce_blocks(C);
-    if (nb == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_colmax_reduce, dim3((unsigned)nb), dim3(kRedThreads * kRedLanes), 0, s, partial, slabs, C,
-                       rbits, bmax);
+static hipError_t launch_groups_place(const uint32_t* partial, int64_t slabs, const uint32_t* block_max, int64_t nbm,
+                                      int64_t C, const QuantCfg& cfg, uint8_t* group, sq_scale* scale, int32_t* layout,
+                                      int64_t ext_max, int32_t* hist, int hist_ld, hipStream_t s) {
+    const int64_t nb = fin_blocks(C);
+    hipLaunchKernelGGL(k_final_groups, dim3((unsigned)nb), dim3(kFinThreads), 0, s, partial, slabs, block_max, nbm, C,
+                       cfg, group, scale, layout, ext_max, hist, hist_ld);
+    if (ext_max > 0)
+        hipLaunchKernelGGL(k_final_place, dim3((unsigned)((nb + 3) / 4)), dim3(kPlaceThreads), 0, s, group, hist,
+                           hist_ld, nb, C, cfg, layout, ext_max);
     return hipGetLastError();
 }
 
-hipError_t launch_finalize_grad(const uint32_t* partial, int64_t slabs, int64_t C, const QuantCfg& cfg,
-                                uint32_t* rbits, uint8_t* group, sq_scale* scale, int32_t* layout,
-                                int64_t ext_max, hipStream_t s) {
-    uint32_t* bmax = rbits + C;
-    const hipError_t e = launch_reduce(partial, slabs, C, rbits, bmax, s);
+hipError_t launch_finalize_ranges(const uint32_t* ranges, int64_t slabs, int64_t C, const QuantCfg& cfg, uint32_t* ws,
+                                  uint8_t* group, sq_scale* scale, int32_t* layout, int64_t ext_max, hipStream_t s) {
+    // ws: channel ranges, group maxima.  A group's shift counts take the place
+    // of its own channel ranges, which its block has read by then.
+    const int64_t nb = fin_blocks(C);
+    uint32_t* bmax = ws + C + kMaxRegions;
+    int32_t* hist = reinterpret_cast<int32_t*>(ws);
+    if (nb == 1)   // the group kernel's one block sees every channel
+        return launch_groups_place(ranges, slabs, nullptr, 0, C, cfg, group, scale, layout, ext_max, hist, kFinCh, s);
+    hipLaunchKernelGGL(k_colmax_reduce, dim3((unsigned)nb), dim3(kFinThreads), 0, s, ranges, slabs, C, ws, bmax);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t nb = colmax_reduce_blocks(C);
-    if (nb > 0) {
-        // many channels: groups and placement spread over nb blocks
-        int32_t* hist = reinterpret_cast<int32_t*>(bmax + nb);
-        hipLaunchKernelGGL(k_final_groups, dim3((unsigned)nb), dim3(kRedThreads), 0, s, rbits, bmax, nb, C, cfg, group,
-                           scale, layout, ext_max, hist);
-        if (ext_max > 0)
-            hipLaunchKernelGGL(k_final_place, dim3((unsigned)nb), dim3(kRedThreads), 0, s, group, hist, nb, C, cfg,
-                               layout, ext_max);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_finalize_grad, dim3(1), dim3(kFinThreads), 0, s, partial, slabs, C, cfg, rbits, bmax, nb, group,
-                       scale, layout, ext_max);
-    return hipGetLastError();
+    return launch_groups_place(ws, 1, bmax, nb, C, cfg, group, scale, layout, ext_max, hist, kFinCh, s);
 }
 
 hipError_t launch_colmax_finalize_grad(const float* x, int64_t M, int64_t C, int64_t ld, const QuantCfg& cfg,
                                        uint32_t* ws, uint8_t* group, sq_scale* scale, int32_t* layout,
                                        int64_t ext_max, hipStream_t s) {
-    const int64_t nb = colmax_reduce_blocks(C);
-    if (nb == 0 || M <= 0) {
-        int64_t slabs = 0;
-        hipError_t e = launch_colmax(x, M, C, ld, ws, &slabs, s);
-        if (e != hipSuccess) return e;
-        return launch_finalize_grad(ws, slabs, C, cfg, ws + slabs * C, group, scale, layout, ext_max, s);
-    }
-    // many channels: the abs-max pass also leaves its blocks' maxima, and the
-    // group kernel reduces the slab maxima itself (no k_colmax_reduce)
-    const ColmaxPlan p = colmax_plan(M, C, ((ld & 3) == 0) && ((reinterpret_cast<uintptr_t>(x) & 15) == 0));
-    uint32_t* rbits = ws + p.slabs * C;
-    int32_t* hist = reinterpret_cast<int32_t*>(rbits + C + nb);
-    uint32_t* bm = rbits + C + (1 + kMaxRegions) * nb;
+    // ws: shift counts, slab maxima, block maxima
+    int32_t* hist = reinterpret_cast<int32_t*>(ws);
+    uint32_t* partial = ws + kMaxRegions * fin_blocks(C);
     int64_t slabs = 0, nbm = 0;
-    hipError_t e = launch_colmax(x, M, C, ld, ws, &slabs, s, bm, &nbm);
+    uint32_t* bm = partial + colmax_plan(M, C, colmax_vec(x, ld)).slabs * C;
+    const hipError_t e = launch_colmax(x, M, C, ld, partial, &slabs, s, bm, &nbm);
     if (e != hipSuccess) return e;
-    if (slabs != p.slabs) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_final_groups_slabs, dim3((unsigned)nb), dim3(kRedThreads * kRedLanes), 0, s, ws, slabs, bm,
-                       nbm, C, cfg, group, scale, layout, ext_max, hist);
-    if (ext_max > 0)
-        hipLaunchKernelGGL(k_final_place, dim3((unsigned)nb), dim3(kRedThreads), 0, s, group, hist, nb, C, cfg,
-                           layout, ext_max);
-    return hipGetLastError();
+    return launch_groups_place(partial, slabs, bm, nbm, C, cfg, group, scale, layout, ext_max, hist, kMaxRegions, s);
 }
 
-hipError_t launch_finalize_tensor(const uint32_t* partial, int64_t slabs, int64_t C, int Q, uint32_t* rbits,
-                                  sq_scale* scale, hipStream_t s) {
-    uint32_t* bmax = rbits + C;
-    const hipError_t e = launch_reduce(partial, slabs, C, rbits, bmax, s);
+hipError_t launch_colmax_finalize_tensor(const float* x, int64_t M, int64_t C, int64_t ld, int Q, uint32_t* ws,
+                                         sq_scale* scale, hipStream_t s) {
+    int64_t slabs = 0, nbm = 0;
+    uint32_t* bm = ws + colmax_plan(M, C, colmax_vec(x, ld)).slabs * C;
+    const hipError_t e = launch_colmax(x, M, C, ld, ws, &slabs, s, bm, &nbm);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_finalize_tensor, dim3(1), dim3(kFinThreads), 0, s, partial, slabs, C, Q, bmax,
-                       colmax_reduce_blocks(C), scale);
+    hipLaunchKernelGGL(k_finalize_tensor, dim3(1), dim3(kFinThreads), 0, s, bm, nbm, Q, scale);
     return hipGetLastError();
 }
 
