@@ -491,14 +491,16 @@ sq_status sq_gemm_dgrad_ranged(const int8_t* q_fold, int64_t ld_fold, const int3
  *   sq_quantize_tensor (Sec. 5.1: activations quantized per tensor) written
  *   straight onto the padded input grid xs, optionally also
  *   row-major into xq [N H W, ld_xq >= C_in] (the forward's layout; NULL to
- *   skip).  xs's padding is never written, so the caller zero-fills that
- *   buffer once; then no pack is needed.  Workspace:
+ *   skip).  xs's padding is written with nothing but zeros, and not all of
+ *   it, so the caller zero-fills that buffer once; then no pack is needed.
+ *   Workspace:
  *   sq_quantize_tensor_workspace_size(N H W, C_in).  Errors as
  *   sq_quantize_tensor, plus SQ_ERR_UNSUPPORTED beyond 2^32 grid pixels.
  * sq_quantize_grad_conv is sq_quantize_grad for the conv's gradient
  *   dY [N Ho Wo, ld_dY] (same codes, groups, scale, layout, q_fold, workspace)
  *   that writes the transposed codes straight onto the padded grid: q_tp's
- *   padding is never written, so the caller zero-fills that buffer once.
+ *   padding is written with nothing but zeros, and not all of it, so the
+ *   caller zero-fills that buffer once.
  * sq_quantize_grad_conv_from_ranges is the same with the channel ranges
  *   given as partial maxima (see sq_quantize_grad_from_ranges), e.g. the
  *   dX_ranges of sq_conv_dgrad_ranged of the layer above.

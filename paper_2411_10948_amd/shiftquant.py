@@ -739,7 +739,7 @@ def conv_pack_input(xq_t: torch.Tensor, N: int, H: int, W: int, KH: int, KW: int
 def quantize_input_conv(X: torch.Tensor, N: int, H: int, W: int, KH: int, KW: int, PH: int, PW: int,
                         bits: int = 8, want_rows: bool = False, stream=None):
     """Per-tensor codes of the conv input X [N*H*W, C_in] on the padded grid of
-    sq_conv_wgrad (a zero-filled buffer: the padding is never written), and,
+    sq_conv_wgrad (a zero-filled buffer: not all of the padding is written), and,
     with want_rows, row-major as well: (xs, xq or None, scale)."""
     C_in = X.shape[1]
     dev = X.device
@@ -868,12 +868,12 @@ class ConvBackwardPlan(BackwardPlan):
         if implicit_wgrad:
             self.ws_w = _workspace(sq_conv_wgrad_workspace_size(N, H, W, C_out, C_in_ch, KH, KW, PH, PW, params), dev)
             _, _, qld = sq_conv_wgrad_layout(N, H, W, C_in_ch, KH, KW, PH, PW)
-            # the quantizer never writes the padding of the grid: zero it once
+            # the quantizer does not write all of the grid's padding: zero it once
             self.q_tp = torch.zeros((C_out, qld), dtype=torch.int8, device=dev)
             self.q_t = None
             # the input codes on the grid (written whole by pack_input; the
-            # input quantizer writes the pixels only, so the padding is zeroed
-            # once)
+            # input quantizer does not write all of the padding, so it is
+            # zeroed once)
             xrows, xld, _ = sq_conv_wgrad_layout(N, H, W, C_in_ch, KH, KW, PH, PW)
             self.x_grid = torch.zeros((max(xrows, 1), xld), dtype=torch.int8, device=dev)[:xrows]
             self.x_scale = new_scale(dev)
