@@ -302,11 +302,9 @@ sq_status sq_quantize_tensor(const float* T, int64_t rows, int64_t cols, int64_t
     const QuantCfg cfg = make_cfg(p);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t* partial = static_cast<uint32_t*>(workspace);
-    SQ_TRY(hip_status(launch_colmax_finalize_tensor(T, rows, cols, ld, cfg.Q, partial, scale, s),
-                      "abs-max and finalize"));
-    SQ_TRY(hip_status(launch_quantize(T, rows, cols, ld, nullptr, scale, cfg, transpose ? nullptr : q, ld_q,
-                                      transpose ? q : nullptr, ld_q, nullptr, s, PadGrid(), transpose == 2),
-                      "quantize"));
+    SQ_TRY(hip_status(launch_quantize_tensor(T, rows, cols, ld, cfg, partial, scale, transpose ? nullptr : q, ld_q,
+                                             transpose ? q : nullptr, ld_q, s, PadGrid(), transpose == 2),
+                      "quantize_tensor"));
     return SQ_OK;
 }
 
@@ -839,8 +837,6 @@ sq_status sq_quantize_input_conv(const float* X, int64_t N, int64_t H, int64_t W
     const QuantCfg cfg = make_cfg(p);
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint32_t* partial = static_cast<uint32_t*>(workspace);
-    SQ_TRY(hip_status(launch_colmax_finalize_tensor(X, M, C_in, ld_X, cfg.Q, partial, scale, s),
-                      "abs-max and finalize"));
     // input pixel (n, ih, iw) at grid column n Hp Wp + (ih + PH) Wp + iw + PW
     PadGrid pg;
     pg.Wo = (uint32_t)W;
@@ -848,8 +844,8 @@ sq_status sq_quantize_input_conv(const float* X, int64_t N, int64_t H, int64_t W
     pg.Wp = (uint32_t)g.Wp;
     pg.HpWp = (uint32_t)(g.Hp * g.Wp);
     pg.off = (uint32_t)(PH * g.Wp + PW);
-    SQ_TRY(hip_status(launch_quantize(X, M, C_in, ld_X, nullptr, scale, cfg, xq, ld_xq, xs, ld_xs, nullptr, s, pg),
-                      "quantize"));
+    SQ_TRY(hip_status(launch_quantize_tensor(X, M, C_in, ld_X, cfg, partial, scale, xq, ld_xq, xs, ld_xs, s, pg),
+                      "quantize_input_conv"));
     return SQ_OK;
 }
 

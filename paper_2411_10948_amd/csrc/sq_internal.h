@@ -95,9 +95,6 @@ hipError_t launch_colmax_finalize_grad(const float* x, int64_t M, int64_t C, int
 // finalize alone, from the producer's partial maxima ranges [slabs, C]
 hipError_t launch_finalize_ranges(const uint32_t* ranges, int64_t slabs, int64_t C, const QuantCfg& cfg, uint32_t* ws,
                                   uint8_t* group, sq_scale* scale, int32_t* layout, int64_t ext_max, hipStream_t s);
-// abs-max pass + scale of the per-tensor quantizer
-hipError_t launch_colmax_finalize_tensor(const float* x, int64_t M, int64_t C, int64_t ld, int Q, uint32_t* ws,
-                                         sq_scale* scale, hipStream_t s);
 // Padded pixel grid of the transposed codes (conv wgrad): row m = (n, oh, ow)
 // of an Ho x Wo output grid goes to column n HpWp + oh Wp + ow; Wo = 0: plain
 // (column m).  Every value below 2^32.
@@ -105,6 +102,13 @@ hipError_t launch_colmax_finalize_tensor(const float* x, int64_t M, int64_t C, i
 // Ho x Wo image goes to column n HpWp + oh Wp + ow + off (Wo == 0: no grid).
 struct PadGrid {
     uint32_t Wo = 0, HoWo = 0, Wp = 0, HpWp = 0, off = 0;
+};
+// Per-tensor mode: the abs-max pass's block maxima and where the scale goes
+// (block_max == nullptr: the scale is read from launch_quantize's argument).
+struct TensorMax {
+    const uint32_t* block_max = nullptr;
+    int64_t n = 0;
+    sq_scale* scale = nullptr;
 };
 // group == nullptr: every channel in group 0 with shift 0 (per-tensor mode);
 // desc: the channel descriptors of the fold layout (nullptr: all main, t = 0).
@@ -114,7 +118,14 @@ struct PadGrid {
 hipError_t launch_quantize(const float* x, int64_t M, int64_t C, int64_t ld, const uint8_t* group,
                            const sq_scale* scale, const QuantCfg& cfg,
                            int8_t* q_fold, int64_t ld_fold, int8_t* q_t, int64_t ld_t,
-                           const int32_t* desc, hipStream_t s, PadGrid pg = PadGrid(), bool tiled = false);
+                           const int32_t* desc, hipStream_t s, PadGrid pg = PadGrid(), bool tiled = false,
+                           TensorMax tm = TensorMax());
+// The per-tensor quantizer: abs-max pass over the scratch ws
+// (colmax_workspace_words(M, C) words), then the quantize pass, which takes
+// the scale from the block maxima itself.
+hipError_t launch_quantize_tensor(const float* x, int64_t M, int64_t C, int64_t ld, const QuantCfg& cfg, uint32_t* ws,
+                                  sq_scale* scale, int8_t* q, int64_t ld_q, int8_t* q_t, int64_t ld_t, hipStream_t s,
+                                  PadGrid pg = PadGrid(), bool tiled = false);
 
 // Per-channel weight quantization: axis 0 one scale per row, axis 1 one per
 // column (partial: colmax scratch, axis 1 only).

@@ -215,24 +215,9 @@ __device__ __forceinline__ uint32_t reduce_slabs(const uint32_t* __restrict__ pa
     return a[0];
 }
 
-// ---------------------------------------------------------------------------
-// Block-wide helpers (any multiple of 64 threads up to 1024).
-// ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
-    return v;
-}
-
-__device__ uint32_t block_max_u32(uint32_t v, uint32_t* sh) {
-    v = wave_max(v);
-    const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[w] = v;
-    __syncthreads();
-    v = 0u;
-    for (int i = 0; i < nw; ++i) v = max(v, sh[i]);
-    __syncthreads();
     return v;
 }
 
@@ -538,16 +523,30 @@ __global__ __launch_bounds__(kPlaceThreads) void k_final_place(const uint8_t* __
     }
 }
 
-// Finalize for per-tensor quantization (one block): the tensor's absolute
-// maximum is the maximum over the abs-max pass's block maxima.
-__global__ __launch_bounds__(kFinThreads) void k_finalize_tensor(const uint32_t* __restrict__ block_max, int64_t nbm,
-                                                                 int Q, sq_scale* __restrict__ scale) {
-    __shared__ uint32_t shu[16];
-    uint32_t mb = 0u;
-    for (int64_t i = threadIdx.x; i < nbm; i += kFinThreads) mb = max(mb, block_max[i]);
-    mb = block_max_u32(mb, shu);
-    if (threadIdx.x == 0) *scale = make_scale(mb, (float)Q);
+// Scale of a per-tensor quantization, taken by every block of the quantize
+// pass from the abs-max pass's block maxima (at most about 520 words, unless
+// there are more than 130,000 channels); block 0 writes it out.  A launch of
+// its own for this took 2.1 to 3.9 us and a gap.  In two parts, so that the
+// block maxima are loaded first and combined while the tile's rows are in
+// flight.  sh: 4 words of LDS.
+__device__ __forceinline__ uint32_t tensor_max_load(const TensorMax& tm) {
+    const int64_t last = tm.n - 1;
+    uint32_t mb = max(tm.block_max[min((int64_t)threadIdx.x, last)], tm.block_max[min((int64_t)threadIdx.x + 256, last)]);
+    for (int64_t i = threadIdx.x + 512; i < tm.n; i += 256) mb = max(mb, tm.block_max[i]);
+    return mb;
 }
+
+__device__ __forceinline__ sq_scale tensor_scale(const TensorMax& tm, uint32_t mb, float Qf, uint32_t* sh) {
+    mb = wave_max(mb);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = mb;
+    __syncthreads();
+    const sq_scale sc = make_scale(max(max(sh[0], sh[1]), max(sh[2], sh[3])), Qf);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *tm.scale = sc;
+    return sc;
+}
+
+// An empty tensor, which has no quantize pass.
+__global__ void k_empty_scale(int Q, sq_scale* __restrict__ scale) { *scale = make_scale(0u, (float)Q); }
 
 // ---------------------------------------------------------------------------
 // Quantize.  A block quantizes tiles of TR rows x TC channels (64 or 128 each,
@@ -571,7 +570,7 @@ __global__ __launch_bounds__(kBlock) void k_quantize(const float* __restrict__ x
                                                      int8_t* __restrict__ q_fold, int64_t ld_fold,
                                                      int8_t* __restrict__ q_t, int64_t ld_t,
                                                      const int32_t* __restrict__ desc, int64_t ext_base,
-                                                     PadGrid pg, int tiled) {
+                                                     PadGrid pg, int tiled, TensorMax tm) {
     constexpr int QD = TC / 4;            // channel quads per tile
     constexpr int RQ = kBlock / QD;       // row quads per pass
     constexpr int RP = 4 * RQ;            // rows per pass
@@ -581,9 +580,10 @@ __global__ __launch_bounds__(kBlock) void k_quantize(const float* __restrict__ x
     const int tid = threadIdx.x, cq = tid % QD, rq = tid / QD;
     const int64_t ctiles = (C + TC - 1) / TC, rtiles = (M + kTR - 1) / kTR;
 
-    const sq_scale sc = *scale;
-    const bool zero = sc.flags != 0u;
     const float Qf = (float)cfg.Q;
+    __shared__ uint32_t sh_max[4];
+    const sq_scale sc = tm.block_max ? tensor_scale(tm, tensor_max_load(tm), Qf, sh_max) : *scale;
+    const bool zero = sc.flags != 0u;
     // C a multiple of 8: the channel quads 2k and 2k + 1 of a row share one
     // Philox block; the two lanes (adjacent) each run it for two of their four
     // rows and swap the halves the other needs
@@ -880,9 +880,12 @@ __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ 
                                                       int8_t* __restrict__ q_fold, int64_t ld_fold,
                                                       int8_t* __restrict__ q_t, int64_t ld_t,
                                                       const int32_t* __restrict__ desc, int64_t ext_base,
-                                                      int meta_vec) {
+                                                      int meta_vec, TensorMax tm) {
     constexpr int TR = 128, TC = 64, TW = TR / 4 + 1;   // LDS words per channel row (padded)
     __shared__ uint32_t tq[TC * TW];
+    __shared__ uint32_t sh_max[4];
+    sq_scale sc;
+    const uint32_t tmax = tm.block_max ? tensor_max_load(tm) : 0u;
     const int tid = threadIdx.x, g8 = tid & 7, rq = tid >> 3;
     const int64_t ctiles = (C + TC - 1) / TC, rtiles = (M + TR - 1) / TR;
     // q_t rows written: the codes, and with the tile-major layout their zero
@@ -901,7 +904,7 @@ __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ 
             a[i] = *reinterpret_cast<const float4*>(src);
             b[i] = *reinterpret_cast<const float4*>(src + 4);
         }
-        const sq_scale sc = *scale;
+        if (tile == blockIdx.x) sc = tm.block_max ? tensor_scale(tm, tmax, (float)cfg.Q, sh_max) : *scale;
         const Chan8 ch = load_chan8(group, desc, c0, cin, meta_vec, sc.inv);
         bool ok[4];
 #pragma unroll
@@ -984,10 +987,13 @@ __global__ __launch_bounds__(kBlock) void k_quantize_grid(const float* __restric
                                                           int8_t* __restrict__ q_fold, int64_t ld_fold,
                                                           int8_t* __restrict__ q_t, int64_t ld_t,
                                                           const int32_t* __restrict__ desc, int64_t ext_base,
-                                                          int meta_vec, PadGrid pg, GridTiles gt) {
+                                                          int meta_vec, PadGrid pg, GridTiles gt, TensorMax tm) {
     constexpr int TC = 64, TW = 33, kFront = 4, kBack = 8;   // words; a chunk may start up to 15 pixels before its row
     __shared__ uint32_t tile_w[kFront + TC * TW + kBack];
     uint32_t* tq = tile_w + kFront;
+    __shared__ uint32_t sh_max[4];
+    sq_scale sc;
+    const uint32_t tmax = tm.block_max ? tensor_max_load(tm) : 0u;
     const int tid = threadIdx.x, g8 = tid & 7, rq = tid >> 3;
     const uint32_t ctiles = (uint32_t)((C + TC - 1) / TC);
     const uint32_t tiles = (gt.NH + gt.rows - 1) / gt.rows * gt.segs;
@@ -1011,7 +1017,7 @@ __global__ __launch_bounds__(kBlock) void k_quantize_grid(const float* __restric
             a[i] = *reinterpret_cast<const float4*>(src);
             b[i] = *reinterpret_cast<const float4*>(src + 4);
         }
-        const sq_scale sc = *scale;
+        if (tile == blockIdx.x) sc = tm.block_max ? tensor_scale(tm, tmax, (float)cfg.Q, sh_max) : *scale;
         const Chan8 ch = load_chan8(group, desc, c0, cin, meta_vec, sc.inv);
         bool in[4], ok[4];
 #pragma unroll
@@ -1230,14 +1236,21 @@ hipError_t launch_colmax_finalize_grad(const float* x, int64_t M, int64_t C, int
     return launch_groups_place(partial, slabs, bm, nbm, C, cfg, group, scale, layout, ext_max, hist, kMaxRegions, s);
 }
 
-hipError_t launch_colmax_finalize_tensor(const float* x, int64_t M, int64_t C, int64_t ld, int Q, uint32_t* ws,
-                                         sq_scale* scale, hipStream_t s) {
-    int64_t slabs = 0, nbm = 0;
+hipError_t launch_quantize_tensor(const float* x, int64_t M, int64_t C, int64_t ld, const QuantCfg& cfg, uint32_t* ws,
+                                  sq_scale* scale, int8_t* q, int64_t ld_q, int8_t* q_t, int64_t ld_t, hipStream_t s,
+                                  PadGrid pg, bool tiled) {
+    if (M <= 0 || C <= 0) {
+        hipLaunchKernelGGL(k_empty_scale, dim3(1), dim3(1), 0, s, cfg.Q, scale);
+        return hipGetLastError();
+    }
+    int64_t slabs = 0;
+    TensorMax tm;
     uint32_t* bm = ws + colmax_plan(M, C, colmax_vec(x, ld)).slabs * C;
-    const hipError_t e = launch_colmax(x, M, C, ld, ws, &slabs, s, bm, &nbm);
+    const hipError_t e = launch_colmax(x, M, C, ld, ws, &slabs, s, bm, &tm.n);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_finalize_tensor, dim3(1), dim3(kFinThreads), 0, s, bm, nbm, Q, scale);
-    return hipGetLastError();
+    tm.block_max = bm;
+    tm.scale = scale;
+    return launch_quantize(x, M, C, ld, nullptr, scale, cfg, q, ld_q, q_t, ld_t, nullptr, s, pg, tiled, tm);
 }
 
 constexpr int64_t kQuantMaxBlocks = 4096;   // grid-stride beyond this
@@ -1272,7 +1285,8 @@ static bool grid_tiles(int64_t M, const PadGrid& pg, GridTiles& gt) {
 
 hipError_t launch_quantize(const float* x, int64_t M, int64_t C, int64_t ld, const uint8_t* group,
                            const sq_scale* scale, const QuantCfg& cfg, int8_t* q_fold, int64_t ld_fold,
-                           int8_t* q_t, int64_t ld_t, const int32_t* desc, hipStream_t s, PadGrid pg, bool tiled) {
+                           int8_t* q_t, int64_t ld_t, const int32_t* desc, hipStream_t s, PadGrid pg, bool tiled,
+                           TensorMax tm) {
     if (M <= 0 || C <= 0) return hipSuccess;
     if (tiled && (pg.Wo || (q_fold && ld_fold % 64) || (q_t && ld_t % 64))) return hipErrorInvalidValue;
     const bool vec = ((ld & 3) == 0) && ((reinterpret_cast<uintptr_t>(x) & 15) == 0);
@@ -1293,34 +1307,34 @@ hipError_t launch_quantize(const float* x, int64_t M, int64_t C, int64_t ld, con
         const int64_t tiles = (int64_t)((gt.NH + gt.rows - 1) / gt.rows) * gt.segs * ((C + 63) / 64);
         const dim3 gg((unsigned)std::min<int64_t>(tiles, kQuantMaxBlocks));
         if (sr) hipLaunchKernelGGL(k_quantize_grid<true>, gg, dim3(kBlock), 0, s, x, M, C, ld, group, scale, cfg, q_fold,
-                                   ld_fold, q_t, ld_t, desc, eb, mv, pg, gt);
+                                   ld_fold, q_t, ld_t, desc, eb, mv, pg, gt, tm);
         else hipLaunchKernelGGL(k_quantize_grid<false>, gg, dim3(kBlock), 0, s, x, M, C, ld, group, scale, cfg, q_fold,
-                                ld_fold, q_t, ld_t, desc, eb, mv, pg, gt);
+                                ld_fold, q_t, ld_t, desc, eb, mv, pg, gt, tm);
         return hipGetLastError();
     }
     if (vec && C % 8 == 0 && !pg.Wo) {
         const dim3 g8((unsigned)std::min<int64_t>(((C + 63) / 64) * ((M + 127) / 128), kQuantMaxBlocks));
         if (sr && tiled) hipLaunchKernelGGL((k_quantize8<true, true>), g8, dim3(kBlock), 0, s, x, M, C, ld, group, scale,
-                                            cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, mv);
+                                            cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, mv, tm);
         else if (sr) hipLaunchKernelGGL((k_quantize8<true, false>), g8, dim3(kBlock), 0, s, x, M, C, ld, group, scale,
-                                        cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, mv);
+                                        cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, mv, tm);
         else if (tiled) hipLaunchKernelGGL((k_quantize8<false, true>), g8, dim3(kBlock), 0, s, x, M, C, ld, group,
-                                           scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, mv);
+                                           scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, mv, tm);
         else hipLaunchKernelGGL((k_quantize8<false, false>), g8, dim3(kBlock), 0, s, x, M, C, ld, group, scale, cfg,
-                                q_fold, ld_fold, q_t, ld_t, desc, eb, mv);
+                                q_fold, ld_fold, q_t, ld_t, desc, eb, mv, tm);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)std::min<int64_t>(n_tiles(tc, tr), kQuantMaxBlocks));
 #define SQ_LAUNCH_QUANT(TC, TR)                                                                                  \
     do {                                                                                                         \
         if (vec && sr) hipLaunchKernelGGL((k_quantize<TC, TR, 4, true>), grid, dim3(kBlock), 0, s, x, M, C, ld,  \
-                                          group, scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, pg, (int)tiled);              \
+                                          group, scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, pg, (int)tiled, tm);          \
         else if (vec) hipLaunchKernelGGL((k_quantize<TC, TR, 4, false>), grid, dim3(kBlock), 0, s, x, M, C, ld,  \
-                                         group, scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, pg, (int)tiled);               \
+                                         group, scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, pg, (int)tiled, tm);           \
         else if (sr) hipLaunchKernelGGL((k_quantize<TC, TR, 1, true>), grid, dim3(kBlock), 0, s, x, M, C, ld,    \
-                                        group, scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, pg, (int)tiled);                \
+                                        group, scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, pg, (int)tiled, tm);            \
         else hipLaunchKernelGGL((k_quantize<TC, TR, 1, false>), grid, dim3(kBlock), 0, s, x, M, C, ld, group,    \
-                                scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, pg, (int)tiled);                               \
+                                scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, pg, (int)tiled, tm);                           \
     } while (0)
     if (tc == 64 && tr == 64) SQ_LAUNCH_QUANT(64, 64);
     else if (tc == 64) SQ_LAUNCH_QUANT(64, 128);
