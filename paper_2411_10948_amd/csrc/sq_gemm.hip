@@ -753,9 +753,16 @@ __global__ __launch_bounds__(T::kThreads) void k_gemm_pipe(GemmArgs p, int64_t t
         }
     }
 
-    // ---- epilogue (as in the register-staged kernel; the fold's final shift
-    // is applied per element) ----
+    // ---- epilogue ----
+    // An MFMA leaves a lane 4 consecutive columns of one row, so a direct store
+    // would cover 16 rows x 64 bytes: half lines.  Each 16-row fragment row of
+    // the wave therefore goes through LDS (the ring, free after the last
+    // barrier; a region per wave, whose LDS operations complete in order) and
+    // leaves as whole 128-byte lines (16384 x 3072 outputs, K = 768: 93.9 -> 90.5
+    // us; the 8192 x 11008 x 4096 step, whose dW stores are nontemporal: 715.9
+    // -> 698.9 us).
     const int fsh = HORNER ? fv.fshift : 0;
+    const bool nt = p.epi_mode == 1;   // dW: see store_f4
     float base = 0.0f, alpha = 0.0f, gstep = 0.0f;
     if (p.out && !p.part) {
         const sq_scale gs = *p.gs, os = *p.os;
@@ -763,115 +770,126 @@ __global__ __launch_bounds__(T::kThreads) void k_gemm_pipe(GemmArgs p, int64_t t
         base = __fmul_rn(gs.step, os.step);
         alpha = __fmul_rn(base, pow2f(-(p.num_groups - 1)));
     }
-    const bool vec_acc = p.acc && ((p.ld_acc & 3) == 0) && ((reinterpret_cast<uintptr_t>(p.acc) & 15) == 0);
-    const bool vec_out = p.out && ((p.ld_out & 3) == 0) && ((reinterpret_cast<uintptr_t>(p.out) & 15) == 0);
-    const bool vec_part = p.part && ((p.Ng & 3) == 0) && ((reinterpret_cast<uintptr_t>(p.part) & 15) == 0);
-    constexpr int kQuads = T::NACC / 4;
-    // epi_mode 2: this lane's output columns are the same for every row
-    float cs[T::FN][kQuads][4];
+    static_assert(T::MF == 16 && T::TN % 32 == 0, "16-row fragments, whole lines");
+    constexpr int kLd = T::TN + 4;                   // words per row: 16 bytes of padding spread the rows over the banks
+    static_assert(T::kWaves * 16 * kLd * 4 <= T::kSmem, "a fragment row per wave fits the ring");
+    uint32_t* tr = reinterpret_cast<uint32_t*>(smem) + wave * 16 * kLd;
+    const int er = lane % 16, eq = lane / 16;        // fragment row and column quad of this lane's results
+    const int64_t n_w = n0 + wn * T::TN;             // first column of the wave
+    float cs[T::FN][4];                              // epi_mode 2: scales of this lane's columns
 #pragma unroll
     for (int j = 0; j < T::FN; ++j)
 #pragma unroll
-        for (int q = 0; q < kQuads; ++q) {
-            const int64_t jj = n0 + wn * T::TN + j * T::MF + (T::MF == 32 ? q * 8 + (lane / 32) * 4 : (lane / 16) * 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                cs[j][q][e] = (p.epi_mode == 2 && p.out && !p.part && jj + e < p.Ng) ? col_scale(p, gstep, jj + e) : 0.0f;
+        for (int e = 0; e < 4; ++e) {
+            const int64_t jj = n_w + j * 16 + eq * 4 + e;
+            cs[j][e] = (p.epi_mode == 2 && p.out && !p.part && jj < p.Ng) ? col_scale(p, gstep, jj) : 0.0f;
         }
-    // RANGES: channel maxima of |out| per 32-row slab (two 16-row fragments;
-    // every wave's rows are whole slabs), bit patterns with the sign cleared
-    static_assert(!RANGES || (T::MF == 16 && T::TM % 32 == 0), "ranges need 16-row fragments and whole slabs");
+    // rows [m, m + 16) of the wave's columns from LDS to dst (row stride ld words)
+    auto rows_out = [&](uint32_t* dst, int64_t ld, int64_t m, bool vec, bool stream) {
+        const int r0 = lane >> 3, q0 = 4 * (lane & 7);   // 8 rows x one 128-byte line per instruction
+        const uint32_t* src = tr + r0 * kLd + q0;
+        uint32_t* d0 = dst + (m + r0) * ld + n_w + q0;
+#pragma unroll
+        for (int k = 0; k < T::TN / 16; ++k) {
+            const int dr = 8 * (k & 1), dc = 32 * (k >> 1);
+            const uint4 v = *reinterpret_cast<const uint4*>(src + dr * kLd + dc);
+            const int64_t row = m + r0 + dr, col = n_w + q0 + dc;
+            if (row >= p.Mg || col >= p.Ng) continue;
+            uint32_t* d = d0 + dr * ld + dc;
+            if (vec && col + 4 <= p.Ng) {
+                typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+                if (stream) __builtin_nontemporal_store(v4u{v.x, v.y, v.z, v.w}, reinterpret_cast<v4u*>(d));
+                else *reinterpret_cast<uint4*>(d) = v;
+            } else {
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < p.Ng) d[e] = w[e];
+            }
+        }
+    };
+    auto aligned4 = [](const void* q, int64_t ld) { return (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+    const bool vec_acc = aligned4(p.acc, p.ld_acc), vec_out = aligned4(p.out, p.ld_out), vec_part = aligned4(p.part, p.Ng);
+    static_assert(!RANGES || T::TM % 32 == 0, "ranges need whole 32-row slabs per wave");
     uint32_t rm[RANGES ? T::FN : 1][4];
 #pragma unroll
     for (int j = 0; j < (RANGES ? T::FN : 1); ++j)
 #pragma unroll
         for (int e = 0; e < 4; ++e) rm[j][e] = 0u;
+    if (!p.part) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __builtin_amdgcn_s_barrier();   // every wave is done with the ring
+    }
 #pragma unroll
     for (int i = 0; i < T::FM; ++i) {
-        const int64_t ii = m0 + wm * T::TM + i * T::MF + lane % T::MF;
-        if (ii < p.Mg) {
-        float sc = alpha;
-        if (p.out && !p.part && p.epi_mode == 1) sc = __fmul_rn(base, pow2f(-(int)p.group[ii]));
+        const int64_t m_i = m0 + wm * T::TM + i * 16, ii = m_i + er;
+        if (p.part) {
+            // split-K partials, dense [splits, Mg, Ng]: read again at once, from
+            // the caches, so half lines cost nothing and the detour 3 us
+            if (ii >= p.Mg) continue;
+            int32_t* row = p.part + (split * p.Mg + ii) * p.Ng;
 #pragma unroll
-        for (int j = 0; j < T::FN; ++j) {
+            for (int j = 0; j < T::FN; ++j) {
+                const int64_t jj = n_w + j * 16 + eq * 4;
+                const acc_t v = acc[i][j] << fsh;
+                if (vec_part && jj + 4 <= p.Ng) {
+                    *reinterpret_cast<int4*>(row + jj) = make_int4(v[0], v[1], v[2], v[3]);
+                } else {
 #pragma unroll
-            for (int q = 0; q < kQuads; ++q) {
-                const int64_t jj = n0 + wn * T::TN + j * T::MF +
-                                   (T::MF == 32 ? q * 8 + (lane / 32) * 4 : (lane / 16) * 4);
-                if (jj >= p.Ng) continue;
-                const int v0 = acc[i][j][q * 4 + 0] << fsh, v1 = acc[i][j][q * 4 + 1] << fsh;
-                const int v2 = acc[i][j][q * 4 + 2] << fsh, v3 = acc[i][j][q * 4 + 3] << fsh;
-                const int vv[4] = {v0, v1, v2, v3};
-                const bool full = jj + 4 <= p.Ng;
-                if (p.part) {
-                    int32_t* dst = p.part + split * p.Mg * p.Ng + ii * p.Ng + jj;
-                    if (vec_part && full) {
-                        *reinterpret_cast<int4*>(dst) = make_int4(v0, v1, v2, v3);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (jj + e < p.Ng) dst[e] = vv[e];
-                    }
-                    continue;
-                }
-                if (p.acc) {
-                    int32_t* dst = p.acc + ii * p.ld_acc + jj;
-                    if (vec_acc && full) {
-                        *reinterpret_cast<int4*>(dst) = make_int4(v0, v1, v2, v3);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (jj + e < p.Ng) dst[e] = vv[e];
-                    }
-                }
-                if (p.out) {
-                    float* dst = p.out + ii * p.ld_out + jj;
-                    float s4[4] = {sc, sc, sc, sc};
-                    if (p.epi_mode == 2)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) s4[e] = cs[j][q][e];
-                    const float f0 = __fmul_rn((float)v0, s4[0]), f1 = __fmul_rn((float)v1, s4[1]);
-                    const float f2 = __fmul_rn((float)v2, s4[2]), f3 = __fmul_rn((float)v3, s4[3]);
-                    if (vec_out && full) {
-                        store_f4(dst, f0, f1, f2, f3, p.epi_mode == 1);
-                    } else {
-                        const float ff[4] = {f0, f1, f2, f3};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (jj + e < p.Ng) store_f1(dst + e, ff[e], p.epi_mode == 1);
-                    }
-                    if (RANGES) {
-                        const float ff[4] = {f0, f1, f2, f3};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (jj + e < p.Ng)
-                                rm[RANGES ? j : 0][e] = max(rm[RANGES ? j : 0][e], __float_as_uint(ff[e]) & 0x7FFFFFFFu);
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        if (jj + e < p.Ng) row[jj + e] = v[e];
                 }
             }
+            continue;
         }
+        if (p.acc) {
+#pragma unroll
+            for (int j = 0; j < T::FN; ++j) {
+                const acc_t v = acc[i][j] << fsh;
+                *reinterpret_cast<uint4*>(tr + er * kLd + j * 16 + eq * 4) =
+                    make_uint4((uint32_t)v[0], (uint32_t)v[1], (uint32_t)v[2], (uint32_t)v[3]);
+            }
+            rows_out(reinterpret_cast<uint32_t*>(p.acc), p.ld_acc, m_i, vec_acc, false);
         }
-        if (RANGES && (i & 1)) {
+        if (!p.out) continue;
+        float sc = alpha;
+        if (p.epi_mode == 1) sc = __fmul_rn(base, pow2f(-(int)p.group[min(ii, p.Mg - 1)]));
+#pragma unroll
+        for (int j = 0; j < T::FN; ++j) {
+            uint32_t f[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                f[e] = __float_as_uint(__fmul_rn((float)(acc[i][j][e] << fsh), p.epi_mode == 2 ? cs[j][e] : sc));
+            *reinterpret_cast<uint4*>(tr + er * kLd + j * 16 + eq * 4) = make_uint4(f[0], f[1], f[2], f[3]);
+            if constexpr (RANGES) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) rm[j][e] = max(rm[j][e], ii < p.Mg ? f[e] & 0x7FFFFFFFu : 0u);
+            }
+        }
+        rows_out(reinterpret_cast<uint32_t*>(p.out), p.ld_out, m_i, vec_out, nt);
+        if constexpr (RANGES) {
+            if (i & 1) {
             // end of a 32-row slab: maximum over the 16 lanes of each column
             // group (same lane / 16), then the group's first lane writes
             const int64_t slab = (m0 + wm * T::TM) / 32 + i / 2;
 #pragma unroll
-            for (int j = 0; j < (RANGES ? T::FN : 1); ++j)
+            for (int j = 0; j < T::FN; ++j)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) rm[j][e] = row16_max(rm[j][e]);
-            if ((lane & 15) == 0 && slab * 32 < p.Mg) {
+            if (er == 0 && slab * 32 < p.Mg) {
 #pragma unroll
-                for (int j = 0; j < (RANGES ? T::FN : 1); ++j) {
-                    const int64_t jj = n0 + wn * T::TN + j * T::MF + (lane / 16) * 4;
+                for (int j = 0; j < T::FN; ++j) {
+                    const int64_t jj = n_w + j * 16 + eq * 4;
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (jj + e < p.Ng) p.ranges[slab * p.Ng + jj + e] = rm[j][e];
                 }
             }
 #pragma unroll
-            for (int j = 0; j < (RANGES ? T::FN : 1); ++j)
+            for (int j = 0; j < T::FN; ++j)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) rm[j][e] = 0u;
+            }
         }
     }
 #endif
