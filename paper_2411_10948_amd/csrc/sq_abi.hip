@@ -363,9 +363,9 @@ sq_status gemm_dgrad_impl(const int8_t* q_fold, int64_t ld_fold, const int32_t* 
     a.out = dX; a.ld_out = ld_dX;
     a.epi_mode = 0;
     a.gs = gscale; a.os = wscale; a.group = group; a.num_groups = cfg.num_groups;
-    if (ranges && !gemm_pipe_ok(a)) {
-        // the register-staged kernel (C_out not a multiple of 64, or operands
-        // past 31-bit offsets) stores dX, then one pass takes its slab maxima
+    if (ranges && (a.K % 64 || !gemm_pipe_ok(a))) {
+        // C_out not a multiple of 64, or operands past 31-bit offsets: the
+        // GEMM stores dX, then one pass takes its slab maxima
         if ((M + 31) / 32 > 65535) return fail(SQ_ERR_UNSUPPORTED, "dX ranges support at most 2^21 rows here");
         SQ_TRY(hip_status(launch_gemm(a, s), "gemm_dgrad"));
         return hip_status(launch_slab_colmax(dX, M, C_in, ld_dX, ranges, s), "dX ranges");

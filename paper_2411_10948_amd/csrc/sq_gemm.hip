@@ -421,8 +421,7 @@ __global__ __launch_bounds__(T::kThreads) void k_gemm(GemmArgs p, int64_t tiles_
 // HORNER = false compiles out the accumulator shifts of the fold (wgrad, and
 // dgrads whose fold has one window), which lets the accumulators live in the
 // matrix-core registers for the whole loop.
-// Requirements (checked by the launcher): every K segment a multiple of 64,
-// lda/ldb multiples of 16, 16-byte aligned operands, offsets below 2^31.
+// Requirements (checked by the launcher): lda/ldb multiples of 16, 16-byte aligned operands, offsets below 2^31.
 // ---------------------------------------------------------------------------
 template <int BM_, int BN_, int WM_, int WN_, int MF_, int STAGES_>
 struct PipeCfg {
@@ -444,7 +443,6 @@ struct PipeCfg {
 };
 
 using PipeLarge = PipeCfg<256, 256, 4, 2, 16, 4>;   // 128 KB of LDS, one block per CU
-using PipeWide = PipeCfg<256, 256, 2, 2, 16, 4>;    // 4 waves of 128 x 128: half the LDS reads per MFMA
 using PipeSmall = PipeCfg<128, 128, 2, 2, 16, 4>;   // 64 KB of LDS
 using PipeSkinny = PipeCfg<64, 192, 2, 2, 16, 4>;   // at most 64 output rows (wgrad of narrow layers)
 using PipeTall = PipeCfg<128, 384, 2, 4, 16, 4>;    // 8 waves of 64 x 96: more tiles where 256 x 256 leaves CUs idle
@@ -472,7 +470,7 @@ __device__ __forceinline__ void wait_vm() {
     return v;
 }
 
-template <class T, bool HORNER, bool CONV = false, bool RANGES = false>
+template <class T, bool HORNER, bool CONV = false, bool RANGES = false, bool TAIL = false>
 __global__ __launch_bounds__(T::kThreads) void k_gemm_pipe(GemmArgs p, int64_t tiles_m, int64_t tiles_n,
                                                            int64_t k_per_split) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources exist in the device pass only
@@ -512,7 +510,11 @@ __global__ __launch_bounds__(T::kThreads) void k_gemm_pipe(GemmArgs p, int64_t t
     if (p.kseg) { koff = p.kseg[0]; Kd = p.kseg[1]; }
     const int64_t kbeg = split * k_per_split;
     const int64_t kend = min(Kd, kbeg + k_per_split);
-    const int n_main = kend > kbeg ? (int)((kend - kbeg) / T::BK) : 0;
+    const int n_main = kend > kbeg ? (int)((kend - kbeg + T::BK - 1) / T::BK) : 0;
+    // TAIL: K is not a multiple of the K tile.  The last main tile then reads
+    // past column K (row padding, the next row, or past the buffer's end,
+    // which reads as 0) and the A fragments are cleared there.
+    const int tail = kend == Kd && n_main > 0 ? fv.h_tiles + n_main - 1 : -1;
     // a convolution visits the flat fold sequence once per tap: tile t is
     // flat tile t / taps of tap t % taps
     const int taps = CONV ? p.taps : 1;
@@ -715,6 +717,19 @@ __global__ __launch_bounds__(T::kThreads) void k_gemm_pipe(GemmArgs p, int64_t t
             for (int i = 0; i < T::FM; ++i)
 #pragma unroll
                 for (int j = 0; j < T::FN; ++j) acc[i][j] = acc[i][j] << sft;
+        }
+        if constexpr (TAIL) {
+            if (t == tail) {
+                constexpr int buf = decltype(CUR)::value;
+                const int nv = min(16, max(0, (int)(Kd % T::BK) - 16 * lc));   // bytes of this lane's chunk below K
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const int keep = min(4, max(0, nv - 4 * w));
+                    const int m = keep == 4 ? -1 : (1 << (8 * keep)) - 1;
+#pragma unroll
+                    for (int i = 0; i < T::FM; ++i) fa[buf][0][i][w] &= m;
+                }
+            }
         }
         read_frags_at(STG_NXT, NXT);
         mfmas(CUR);
@@ -1413,7 +1428,7 @@ hipError_t launch_cfg(const GemmArgs& a, int splits, int64_t k_per_split, hipStr
     return hipGetLastError();
 }
 
-template <class T, bool HORNER, bool CONV = false, bool RANGES = false>
+template <class T, bool HORNER, bool CONV = false, bool RANGES = false, bool TAIL = false>
 hipError_t launch_pipe(const GemmArgs& a, int splits, int64_t k_per_split, hipStream_t s) {
     const int64_t tiles_m = (a.Mg + T::BM - 1) / T::BM, tiles_n = (a.Ng + T::BN - 1) / T::BN;
     if (tiles_m * tiles_n * splits > 0x7FFFFFFF || splits > 65535) return hipErrorInvalidValue;
@@ -1421,24 +1436,32 @@ hipError_t launch_pipe(const GemmArgs& a, int splits, int64_t k_per_split, hipSt
     // on one XCD); a.splits must equal splits for that decoding
     if (splits > 1 && a.splits != splits) return hipErrorInvalidValue;
     const dim3 grid = splits > 1 ? dim3((unsigned)(tiles_m * tiles_n * splits)) : dim3((unsigned)(tiles_m * tiles_n));
-    hipLaunchKernelGGL((k_gemm_pipe<T, HORNER, CONV, RANGES>), grid, dim3(T::kThreads), 0, s, a, tiles_m, tiles_n,
+    hipLaunchKernelGGL((k_gemm_pipe<T, HORNER, CONV, RANGES, TAIL>), grid, dim3(T::kThreads), 0, s, a, tiles_m, tiles_n,
                        k_per_split);
     return hipGetLastError();
 }
 
-// The direct-load pipeline needs 64-byte K tiles that never cross the end of a
-// segment, 16-byte aligned rows, and byte offsets (rows * ld + K) that fit
-// the 31 bits of its buffer loads.
+// One tile shape: with the fold's shifts or without, K whole tiles or not.
+template <class T>
+hipError_t launch_tile(const GemmArgs& a, int splits, int64_t k_per_split, hipStream_t s) {
+    if (a.K % T::BK)
+        return a.extA ? launch_pipe<T, true, false, false, true>(a, splits, k_per_split, s)
+                      : launch_pipe<T, false, false, false, true>(a, splits, k_per_split, s);
+    return a.extA ? launch_pipe<T, true>(a, splits, k_per_split, s) : launch_pipe<T, false>(a, splits, k_per_split, s);
+}
+
+// The direct-load pipeline needs 16-byte aligned rows and byte offsets (rows *
+// ld + K) that fit the 31 bits of its buffer loads.
 bool pipe_ok(const GemmArgs& a) {
     auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
     auto fits = [&](int64_t rows, int64_t ld, int64_t cols) {
         return (a.tiled ? round_up(rows, 16) : rows) * ld + cols < ((int64_t)1 << 31);
     };
-    if (a.K % 64 != 0 || a.lda % 16 != 0 || a.ldb % 16 != 0 || !al16(a.A) || !al16(a.B)) return false;
-    if (a.tiled && (a.lda % 64 != 0 || a.ldb % 64 != 0 || (a.extA && (a.ld_extA % 64 || a.ld_extB % 64 ||
+    if (a.lda % 16 != 0 || a.ldb % 16 != 0 || !al16(a.A) || !al16(a.B)) return false;
+    if (a.tiled && (a.K % 64 != 0 || a.lda % 64 != 0 || a.ldb % 64 != 0 || (a.extA && (a.ld_extA % 64 || a.ld_extB % 64 ||
                                                                      a.ext_koff % 64))))
         return false;
-    if (!fits(a.Mg, a.lda, a.K) || !fits(a.Ng, a.ldb, a.K)) return false;
+    if (!fits(a.Mg, a.lda, round_up(a.K, 64)) || !fits(a.Ng, a.ldb, round_up(a.K, 64))) return false;
     if (a.extA) {
         if (a.ld_extA % 16 != 0 || a.ld_extB % 16 != 0 || !al16(a.extA) || !al16(a.extB)) return false;
         if (!fits(a.Mg, a.ld_extA, 0) || !fits(a.Ng, a.ld_extB, 0)) return false;
@@ -1608,7 +1631,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     if (splits > 1 && (ktiles + per - 1) / per != splits) return hipErrorInvalidValue;   // wgrad_splits() avoids this
     if (a.ranges) {
         // dX with its channel maxima (producer-side ranges): pipelined kernel, no split
-        if (!pipe || splits > 1 || !a.out || a.part) return hipErrorInvalidValue;
+        if (!pipe || a.K % 64 || splits > 1 || !a.out || a.part) return hipErrorInvalidValue;
         if (p == Pick::kLarge)
             return a.extA ? launch_pipe<PipeLarge, true, false, true>(a, 1, per * 64, s)
                           : launch_pipe<PipeLarge, false, false, true>(a, 1, per * 64, s);
@@ -1619,18 +1642,13 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
         return a.extA ? launch_pipe<PipeSmall, true, false, true>(a, 1, per * 64, s)
                       : launch_pipe<PipeSmall, false, false, true>(a, 1, per * 64, s);
     }
-    if (p == Pick::kTall && pipe)
-        return a.extA ? launch_pipe<PipeTall, true>(a, splits, per * 64, s)
-                      : launch_pipe<PipeTall, false>(a, splits, per * 64, s);
-    if (p == Pick::kLarge || p == Pick::kTall) {
-        if (!pipe) return launch_cfg<CfgLarge>(a, splits, per * 64, s);
-        return a.extA ? launch_pipe<PipeLarge, true>(a, splits, per * 64, s)
-                      : launch_pipe<PipeLarge, false>(a, splits, per * 64, s);
-    }
-    if (!pipe) return launch_cfg<CfgSmall>(a, splits, per * 64, s);
-    if (p == Pick::kSkinny) return launch_pipe<PipeSkinny, false>(a, splits, per * 64, s);
-    return a.extA ? launch_pipe<PipeSmall, true>(a, splits, per * 64, s)
-                  : launch_pipe<PipeSmall, false>(a, splits, per * 64, s);
+    if (!pipe)
+        return p == Pick::kLarge || p == Pick::kTall ? launch_cfg<CfgLarge>(a, splits, per * 64, s)
+                                                     : launch_cfg<CfgSmall>(a, splits, per * 64, s);
+    if (p == Pick::kLarge) return launch_tile<PipeLarge>(a, splits, per * 64, s);
+    if (p == Pick::kTall) return launch_tile<PipeTall>(a, splits, per * 64, s);
+    if (p == Pick::kSkinny) return launch_tile<PipeSkinny>(a, splits, per * 64, s);
+    return launch_tile<PipeSmall>(a, splits, per * 64, s);
 }
 
 // Padded pixel grids of the conv wgrad: a thread writes one aligned 16-byte
