@@ -116,6 +116,11 @@ sq_status check_dims(int64_t rows, int64_t cols, const char* what) {
 size_t quant_ws_bytes(int64_t M, int64_t C) { return (size_t)round_up(std::max<int64_t>(colmax_workspace_words(M, C), 1) * 4, 256); }
 
 
+// split-K partials of the weight gradient
+size_t wgrad_ws_bytes(int splits, int64_t C_out, int64_t C_in) {
+    return splits > 1 ? (size_t)round_up((int64_t)splits * C_out * C_in * 4, 256) : 0;
+}
+
 // Scratch of sq_quantize_grad_noalloc: a fixed device array instead of a
 // caller-provided workspace, for callers that cannot allocate.  Each GPU the
 // library runs on holds its own copy until the process ends; host code uses
@@ -251,8 +256,11 @@ sq_status sq_gemm_wgrad_workspace_size(int64_t M, int64_t C_out, int64_t C_in, c
     SQ_TRY(check_dims(M, C_out, "gradient"));
     SQ_TRY(check_dims(C_in, C_in, "activation"));
     if (!bytes) return fail(SQ_ERR_INVALID_ARGUMENT, "bytes is NULL");
-    const int splits = (M > 0 && C_out > 0 && C_in > 0) ? wgrad_splits(M, C_out, C_in) : 1;
-    *bytes = splits > 1 ? (size_t)round_up((int64_t)splits * C_out * C_in * 4, 256) : 0;
+    // a product always reports some workspace, whether this version splits it
+    // or not; sq_gemm_wgrad asks for what it uses
+    *bytes = 0;
+    if (M > 0 && C_out > 0 && C_in > 0)
+        *bytes = std::max<size_t>(256, wgrad_ws_bytes(wgrad_splits(M, C_out, C_in), C_out, C_in));
     return SQ_OK;
 }
 
@@ -699,9 +707,8 @@ sq_status sq_gemm_wgrad(const int8_t* q_t, int64_t ld_t, const uint8_t* group, c
     }
     if (acc) SQ_TRY(check_f32(acc, ld_acc, C_in, "acc"));
     if (dW) SQ_TRY(check_f32(dW, ld_dW, C_in, "dW"));
-    size_t need = 0;
-    SQ_TRY(sq_gemm_wgrad_workspace_size(M, C_out, C_in, p, &need));
     const int splits = (M > 0) ? wgrad_splits(M, C_out, C_in) : 1;
+    const size_t need = wgrad_ws_bytes(splits, C_out, C_in);
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     GemmArgs a{};

@@ -21,6 +21,7 @@
 // end (Horner's rule), so the result equals sum_c code * w << (N_G - 1 - g_c)
 // exactly.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "sq_internal.h"
@@ -442,10 +443,13 @@ struct PipeCfg {
     static_assert(STAGES >= 3 && STAGES <= 4 && (STAGES - 2) * kLoads <= 63, "vmcnt range");
 };
 
-using PipeLarge = PipeCfg<256, 256, 4, 2, 16, 4>;   // 128 KB of LDS, one block per CU
-using PipeSmall = PipeCfg<128, 128, 2, 2, 16, 4>;   // 64 KB of LDS
-using PipeSkinny = PipeCfg<64, 192, 2, 2, 16, 4>;   // at most 64 output rows (wgrad of narrow layers)
-using PipeTall = PipeCfg<128, 384, 2, 4, 16, 4>;    // 8 waves of 64 x 96: more tiles where 256 x 256 leaves CUs idle
+using PipeLarge = PipeCfg<256, 256, 4, 2, 16, 4>;   // 8 waves of 64 x 128, 128 KB of LDS: one block per CU
+using PipeTall = PipeCfg<128, 384, 2, 4, 16, 4>;    // 8 waves of 64 x 96, 128 KB: one
+using PipeDuo = PipeCfg<256, 128, 2, 2, 16, 3>;     // 4 waves of 128 x 64, 72 KB: two blocks per CU
+using PipeMid = PipeCfg<128, 192, 2, 2, 16, 4>;     // 4 waves of 64 x 96, 80 KB: two
+using PipeSmall = PipeCfg<128, 128, 2, 2, 16, 4>;   // 4 waves of 64 x 64, 64 KB: two
+using PipeFlat = PipeCfg<64, 128, 1, 4, 16, 4>;     // 4 waves of 64 x 32, 48 KB: three
+using PipeTiny = PipeCfg<64, 64, 2, 2, 16, 4>;      // 4 waves of 32 x 32, 32 KB: five
 using PipeNarrow = PipeCfg<256, 64, 4, 1, 16, 4>;   // at most 64 output columns (conv dgrad), 80 KB of LDS
 
 typedef __attribute__((address_space(3))) void lds_void_t;
@@ -471,7 +475,7 @@ __device__ __forceinline__ void wait_vm() {
 }
 
 template <class T, bool HORNER, bool CONV = false, bool RANGES = false, bool TAIL = false>
-__global__ __launch_bounds__(T::kThreads) void k_gemm_pipe(GemmArgs p, int64_t tiles_m, int64_t tiles_n,
+__global__ __launch_bounds__(T::kThreads, 2) void k_gemm_pipe(GemmArgs p, int64_t tiles_m, int64_t tiles_n,
                                                            int64_t k_per_split) {
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer resources exist in the device pass only
     __shared__ __attribute__((aligned(1024))) int8_t smem[T::kSmem];
@@ -754,17 +758,28 @@ __global__ __launch_bounds__(T::kThreads) void k_gemm_pipe(GemmArgs p, int64_t t
         wait_tile(min(T::STAGES - 2, n_tiles - 1));
         __builtin_amdgcn_s_barrier();
         read_frags(0, std::integral_constant<int, 0>());
-        // unrolled over the 4 stages (tile t + 1 sits in stage (t + 1) % 4)
+        // unrolled over the stages and the two operand buffers (tile t + 1 sits
+        // in stage (t + 1) % STAGES)
         using I0 = std::integral_constant<int, 0>;
         using I1 = std::integral_constant<int, 1>;
         using I2 = std::integral_constant<int, 2>;
         using I3 = std::integral_constant<int, 3>;
-        static_assert(T::STAGES == 4, "loop unrolled over 4 stages");
-        for (int t = 0; t < n_tiles; t += 4) {
-            step(t, I0(), I1(), I1());
-            if (t + 1 < n_tiles) step(t + 1, I1(), I0(), I2());
-            if (t + 2 < n_tiles) step(t + 2, I0(), I1(), I3());
-            if (t + 3 < n_tiles) step(t + 3, I1(), I0(), I0());
+        if constexpr (T::STAGES == 4) {
+            for (int t = 0; t < n_tiles; t += 4) {
+                step(t, I0(), I1(), I1());
+                if (t + 1 < n_tiles) step(t + 1, I1(), I0(), I2());
+                if (t + 2 < n_tiles) step(t + 2, I0(), I1(), I3());
+                if (t + 3 < n_tiles) step(t + 3, I1(), I0(), I0());
+            }
+        } else {
+            for (int t = 0; t < n_tiles; t += 6) {
+                step(t, I0(), I1(), I1());
+                if (t + 1 < n_tiles) step(t + 1, I1(), I0(), I2());
+                if (t + 2 < n_tiles) step(t + 2, I0(), I1(), I0());
+                if (t + 3 < n_tiles) step(t + 3, I1(), I0(), I1());
+                if (t + 4 < n_tiles) step(t + 4, I0(), I1(), I2());
+                if (t + 5 < n_tiles) step(t + 5, I1(), I0(), I0());
+            }
         }
     }
 
@@ -1469,70 +1484,80 @@ bool pipe_ok(const GemmArgs& a) {
     return true;
 }
 
-// Tile shape of a product: large tiles where there are enough of them (alone,
-// or with K split into slices of at least 16 tiles) to fill most of the chip
-// and K is long, a 64-row tile for products with at most 64 output rows,
-// 128 x 128 otherwise.
-enum class Pick { kLarge, kTall, kSmall, kSkinny };
-
-int64_t tiles_of(const GemmArgs& a, int bm, int bn) { return ((a.Mg + bm - 1) / bm) * ((a.Ng + bn - 1) / bn); }
-
-constexpr int64_t kLargeFill = 128;      // large tiles per launch that count as filling the chip
+// Tile shape and K split of a product: the least time by a model of the
+// pipelined kernel.  Per round of blocks a CU takes K tiles x max(lat, n thr)
+// with n blocks on it (lat: one block's K tile, bound by its chain of barrier,
+// LDS reads and MFMAs; thr: its share of the CU's LDS and matrix cores), plus
+// `round` for prologue and epilogue; the output leaves at `mb` us per MB.
+// Split K adds the int32 partials, written and summed, and a launch.  The
+// constants were fitted to whole backward steps of 60 linear layers and to 432
+// products alone, each with every tile and split: a pick costs 0.8 % of a step
+// (1.5 % of a product) more than the best of them.  Rules on the number of
+// 256 x 256 tiles, with 128 x 128 tiles below 128 of them, cost 16 % of a
+// product (K = 4096, 256 x 1024: 20.6 us, now 11.8; 16384 x 3072, K = 768:
+// 79.2 us, now 68.8) and 28 % of a split one (768 x 768, K = 3152: 18.0 us, now
+// 11.7).  Constants fitted to the products alone, hot in the caches, picked
+// small tiles for long products that read HBM (MLP wgrad 45 -> 54 us).
+enum class Pick { kLarge, kTall, kDuo, kMid, kSmall, kFlat, kTiny };
+struct TileCost {
+    int bm, bn, per_cu;
+    float lat, thr, round, mb;
+};
+constexpr TileCost kTileCost[] = {{256, 256, 1, 0.59f, 0.59f, 5.2f, 0.130f}, {128, 384, 1, 0.49f, 0.49f, 2.6f, 0.140f},
+                                  {256, 128, 2, 0.42f, 0.32f, 2.6f, 0.130f}, {128, 192, 2, 0.28f, 0.265f, 3.7f, 0.088f},
+                                  {128, 128, 2, 0.22f, 0.20f, 2.0f, 0.110f}, {64, 128, 3, 0.24f, 0.13f, 0.6f, 0.130f},
+                                  {64, 64, 5, 0.16f, 0.084f, 2.0f, 0.080f}};
+constexpr int kTiles = sizeof(kTileCost) / sizeof(kTileCost[0]);
 constexpr int64_t kCUs = 256;
-constexpr int64_t kMinSplitKTiles = 16;  // K tiles per split of a large-tile split-K
 
-// Split factor that brings large tiles of a short-and-narrow product with a
-// long K to at most one block per CU (0: large tiles do not suit this product).
-int64_t large_splits(const GemmArgs& a) {
-    const int64_t tiles = tiles_of(a, PipeLarge::BM, PipeLarge::BN);
-    if (tiles >= kLargeFill) return 1;
-    // split only dense tilings (most of each tile inside the product)
-    if (a.extA || 4 * a.Mg * a.Ng < 3 * tiles * PipeLarge::BM * PipeLarge::BN) return 0;
-    const int64_t ktiles = (a.K + 63) / 64;
-    int64_t s = std::min(kCUs / tiles, ktiles / kMinSplitKTiles);
-    if (s < 2) return 0;
-    const int64_t per = (ktiles + s - 1) / s;   // equal slices, none empty
-    s = (ktiles + per - 1) / per;
-    return s >= 2 && tiles * s >= kLargeFill ? s : 0;
+double tiles_of(int i, int64_t Mg, int64_t Ng) {
+    return std::ceil((double)Mg / kTileCost[i].bm) * std::ceil((double)Ng / kTileCost[i].bn);
+}
+// int32 partials of `splits` K slices (mb MB each), written and summed
+float split_cost(double mb, int splits) { return 5.0f + (float)mb * (0.36f * (float)splits + 0.06f); }
+
+// us of a launch beyond its fixed cost, `tiles` the output tiles of shape i (a
+// whole number below 2^53; doubles, since this runs on every call and 64-bit
+// integer divisions took longer than the launch)
+float tile_cost(int i, double tiles, double mb, int64_t ktiles, int splits) {
+    const TileCost& c = kTileCost[i];
+    const double slots = (double)(kCUs * c.per_cu), blocks = tiles * splits;
+    const double rounds = std::floor(blocks / slots);
+    const float n = (float)std::ceil((blocks - rounds * slots) * (1.0 / kCUs));   // blocks on the last round's fullest CU
+    const float kt = splits > 1 ? std::ceil((float)ktiles / (float)splits) : (float)ktiles;
+    const float t = kt * ((float)rounds * std::max(c.lat, (float)c.per_cu * c.thr) + (n > 0 ? std::max(c.lat, n * c.thr) : 0.0f)) +
+                    c.round * ((float)rounds + (n > 0 ? 1.0f : 0.0f));
+    return t + (splits > 1 ? split_cost(mb, splits) : (float)mb * c.mb);
 }
 
-// An unsplit product whose 256 x 256 tiles leave CUs idle takes 128 x 384
-// tiles when those fill more CUs (at most one tile per CU, most of each tile
-// inside the product): the MLP layer's 16384 x 768 input gradient has 192
-// large tiles but 256 tall ones.
-bool tall_fits(const GemmArgs& a) {
-    const int64_t large = tiles_of(a, PipeLarge::BM, PipeLarge::BN), tall = tiles_of(a, PipeTall::BM, PipeTall::BN);
-    return large < kCUs && tall > large && tall <= kCUs &&
-           4 * a.Mg * a.Ng >= 3 * tall * PipeTall::BM * PipeTall::BN;
+// best tile for a fixed number of splits
+Pick best_tile(int64_t Mg, int64_t Ng, int64_t K, int splits, float* cost = nullptr) {
+    const int64_t ktiles = (K + 63) / 64;
+    const double mb = 4e-6 * (double)Mg * (double)Ng;
+    int best = 0;
+    float t = 0.0f;
+    for (int i = 0; i < kTiles; ++i) {
+        const float ti = tile_cost(i, tiles_of(i, Mg, Ng), mb, ktiles, splits);
+        if (i == 0 || ti < t) { best = i; t = ti; }
+    }
+    if (cost) *cost = t;
+    return (Pick)best;
 }
 
-// The same split of K over 128 x 384 tiles (0 when it does not apply).  A
-// product with few large tiles takes these when they need fewer splits: fewer
-// int32 partials to write and sum (the MLP layer's wgrad, 3072 x 768 x 16384:
-// 5 splits of 48 tall tiles instead of 7 of 36 large ones, 50.9 -> 47.8 us,
-// the partial sums 13.3 -> 10.2 us).
-int64_t tall_splits(const GemmArgs& a) {
-    const int64_t tiles = tiles_of(a, PipeTall::BM, PipeTall::BN);
-    if (tiles >= kCUs || a.extA || 4 * a.Mg * a.Ng < 3 * tiles * PipeTall::BM * PipeTall::BN) return 0;
-    const int64_t ktiles = (a.K + 63) / 64;
-    int64_t s = std::min(kCUs / tiles, ktiles / kMinSplitKTiles);
-    if (s < 2) return 0;
-    const int64_t per = (ktiles + s - 1) / s;
-    return (ktiles + per - 1) / per;
-}
-bool tall_split_better(const GemmArgs& a) {
-    if (a.K < 1024) return false;
-    const int64_t ls = large_splits(a), ts = tall_splits(a);
-    return ls > 1 && ts >= 2 && ts < ls;
-}
-
-Pick pick(const GemmArgs& a) {
-    if (a.splits > 1 && tall_split_better(a) && a.splits == tall_splits(a)) return Pick::kTall;
-    const int64_t ls = a.K >= 1024 ? large_splits(a) : 0;
-    if (ls == 1 && a.splits <= 1 && tall_fits(a)) return Pick::kTall;
-    if (ls > 0 && std::max(a.splits, 1) == ls) return Pick::kLarge;
-    if (a.Mg <= 64 && !a.extA) return Pick::kSkinny;
-    return Pick::kSmall;
+// Rows of an unsplit product to run with 256 x 256 tiles, the rest going to a
+// second launch with its own tile (0: one launch): where a last round of large
+// tiles would leave many CUs idle.
+int64_t large_rows(int64_t Mg, int64_t Ng, int64_t K) {
+    const int64_t tn = (Ng + PipeLarge::BN - 1) / PipeLarge::BN;
+    const int64_t tiles = tn * ((Mg + PipeLarge::BM - 1) / PipeLarge::BM);
+    const int64_t rows = (tiles / kCUs * kCUs / tn) * PipeLarge::BM;
+    if (rows <= 0 || rows >= Mg) return 0;
+    float one = 0.0f, rest = 0.0f;
+    best_tile(Mg, Ng, K, 1, &one);
+    best_tile(Mg - rows, Ng, K, 1, &rest);
+    constexpr float kLaunch = 4.0f;
+    const float main = tile_cost(0, tiles_of(0, rows, Ng), 4e-6 * (double)rows * (double)Ng, (K + 63) / 64, 1);
+    return main + rest + kLaunch < one ? rows : 0;
 }
 
 }  // namespace
@@ -1559,29 +1584,26 @@ hipError_t launch_slab_colmax(const float* x, int64_t M, int64_t N, int64_t ld, 
     return hipGetLastError();
 }
 
-// Split-K factor of the weight-gradient product: large tiles with the split
-// that fills the chip where that works (large_splits), else enough smaller
-// tiles for about one block per CU with at least 8 K tiles per split and no
-// empty split.  The partial tiles do not depend on the tile shape.
+// Split-K factor of the weight-gradient product, at least 4 K tiles per split
+// and none empty.
 int wgrad_splits(int64_t M, int64_t C_out, int64_t C_in) {
-    GemmArgs probe{};
-    probe.Mg = C_out; probe.Ng = C_in; probe.K = M; probe.splits = 1;
     const int64_t ktiles = (M + 63) / 64;
-    if (M >= 1024) {
-        if (tall_split_better(probe)) return (int)tall_splits(probe);
-        const int64_t ls = large_splits(probe);
-        if (ls > 0) return (int)ls;
+    static const int kTry[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32, 48, 64};
+    const double mb = 4e-6 * (double)C_out * (double)C_in;
+    double tiles[kTiles];
+    for (int i = 0; i < kTiles; ++i) tiles[i] = tiles_of(i, C_out, C_in);
+    int best = 1;
+    float t = 0.0f;
+    for (const int want : kTry) {
+        if (want > 1 && (4 * (int64_t)want > ktiles || split_cost(mb, want) >= t)) break;
+        const int64_t per = (ktiles + want - 1) / want;
+        const int s = per > 0 ? (int)((ktiles + per - 1) / per) : 1;
+        for (int i = 0; i < kTiles; ++i) {
+            const float ts = tile_cost(i, tiles[i], mb, ktiles, s);
+            if ((want == 1 && i == 0) || ts < t) { best = s; t = ts; }
+        }
     }
-    const bool skinny = C_out <= 64;
-    const int64_t tiles = skinny ? tiles_of(probe, PipeSkinny::BM, PipeSkinny::BN)
-                                 : tiles_of(probe, PipeSmall::BM, PipeSmall::BN);
-    // about one block per CU: more splits only add partial tiles (measured on
-    // the ResNet layers: 256 blocks beat 512 and 768 slightly, 128 clearly)
-    int64_t splits = (256 + tiles - 1) / tiles;
-    splits = std::min(splits, std::max<int64_t>(1, ktiles / 8));
-    splits = std::max<int64_t>(1, std::min<int64_t>(splits, 65535));
-    const int64_t per = (ktiles + splits - 1) / splits;
-    return (int)((ktiles + per - 1) / per);
+    return best;
 }
 
 namespace {
@@ -1608,21 +1630,15 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     // tile-major operands: the pipelined kernel only, no convolution
     if (a.tiled && (!pipe || a.taps || a.kseg)) return hipErrorInvalidValue;
     if (a.kseg && (!pipe || a.splits > 1 || a.layout)) return hipErrorInvalidValue;   // pipelined kernel only
-    const Pick p = pick(a);
-    if (p == Pick::kLarge && pipe && a.splits <= 1 && !a.ranges && !a.part && !a.taps && !a.kseg) {
-        // A last round of large tiles that would leave a quarter or more of
-        // the CUs idle: the rows of the full rounds take the large tiles and
-        // the remaining rows one round of smaller tiles (two launches).
-        const int64_t tn = (a.Ng + PipeLarge::BN - 1) / PipeLarge::BN;
-        const int64_t tiles = tn * ((a.Mg + PipeLarge::BM - 1) / PipeLarge::BM);
-        const int64_t rounds = tiles / kCUs, rem = tiles - rounds * kCUs;
-        const int64_t rows_main = (rounds * kCUs / tn) * PipeLarge::BM;
-        if (rounds >= 1 && rem > 0 && 4 * rem <= 3 * kCUs && rows_main > 0 && rows_main < a.Mg) {
+    const Pick p = best_tile(a.Mg, a.Ng, a.K, std::max(1, a.splits));
+    if (pipe && a.splits <= 1 && !a.ranges && !a.part && !a.taps && !a.kseg) {
+        const int64_t rows = large_rows(a.Mg, a.Ng, a.K);
+        if (rows > 0) {
             GemmArgs m = a;
-            m.Mg = rows_main;
+            m.Mg = rows;
             const hipError_t e = launch_gemm(m, s);
             if (e != hipSuccess) return e;
-            return launch_gemm(rows_from(a, rows_main), s);
+            return launch_gemm(rows_from(a, rows), s);
         }
     }
     const int64_t ktiles = (a.K + 63) / 64;   // every configuration has 64-byte K tiles
@@ -1632,23 +1648,27 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     if (a.ranges) {
         // dX with its channel maxima (producer-side ranges): pipelined kernel, no split
         if (!pipe || a.K % 64 || splits > 1 || !a.out || a.part) return hipErrorInvalidValue;
-        if (p == Pick::kLarge)
+        if (p == Pick::kLarge || p == Pick::kTall || p == Pick::kDuo)
             return a.extA ? launch_pipe<PipeLarge, true, false, true>(a, 1, per * 64, s)
                           : launch_pipe<PipeLarge, false, false, true>(a, 1, per * 64, s);
-        if (p == Pick::kTall)
-            return a.extA ? launch_pipe<PipeTall, true, false, true>(a, 1, per * 64, s)
-                          : launch_pipe<PipeTall, false, false, true>(a, 1, per * 64, s);
-        if (p == Pick::kSkinny) return launch_pipe<PipeSkinny, false, false, true>(a, 1, per * 64, s);
+        if (p == Pick::kMid)
+            return a.extA ? launch_pipe<PipeMid, true, false, true>(a, 1, per * 64, s)
+                          : launch_pipe<PipeMid, false, false, true>(a, 1, per * 64, s);
         return a.extA ? launch_pipe<PipeSmall, true, false, true>(a, 1, per * 64, s)
                       : launch_pipe<PipeSmall, false, false, true>(a, 1, per * 64, s);
     }
     if (!pipe)
-        return p == Pick::kLarge || p == Pick::kTall ? launch_cfg<CfgLarge>(a, splits, per * 64, s)
-                                                     : launch_cfg<CfgSmall>(a, splits, per * 64, s);
-    if (p == Pick::kLarge) return launch_tile<PipeLarge>(a, splits, per * 64, s);
-    if (p == Pick::kTall) return launch_tile<PipeTall>(a, splits, per * 64, s);
-    if (p == Pick::kSkinny) return launch_tile<PipeSkinny>(a, splits, per * 64, s);
-    return launch_tile<PipeSmall>(a, splits, per * 64, s);
+        return p == Pick::kLarge ? launch_cfg<CfgLarge>(a, splits, per * 64, s)
+                                 : launch_cfg<CfgSmall>(a, splits, per * 64, s);
+    switch (p) {
+        case Pick::kLarge: return launch_tile<PipeLarge>(a, splits, per * 64, s);
+        case Pick::kTall: return launch_tile<PipeTall>(a, splits, per * 64, s);
+        case Pick::kDuo: return launch_tile<PipeDuo>(a, splits, per * 64, s);
+        case Pick::kMid: return launch_tile<PipeMid>(a, splits, per * 64, s);
+        case Pick::kSmall: return launch_tile<PipeSmall>(a, splits, per * 64, s);
+        case Pick::kFlat: return launch_tile<PipeFlat>(a, splits, per * 64, s);
+        default: return launch_tile<PipeTiny>(a, splits, per * 64, s);
+    }
 }
 
 // Padded pixel grids of the conv wgrad: a thread writes one aligned 16-byte
