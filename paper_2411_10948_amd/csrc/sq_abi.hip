@@ -1095,7 +1095,8 @@ BnBwdWs bn_bwd_ws(int64_t M, int64_t C, const QuantCfg& cfg) {
     // window, descriptors for C channels)
     w.codes = w.layout + (size_t)round_up((kLayoutHeader + C) * 4, 256);
     w.part = w.codes + (size_t)round_up(M * w.ldc, 256);
-    w.coef = w.part + (size_t)round_up(std::max<int64_t>(l1bn_part_words(M, C), 1) * 4, 256);
+    const int64_t part_words = std::max(l1bn_part_words(M, C), 2 * quantize_bn_blocks(M) * C);
+    w.coef = w.part + (size_t)round_up(std::max<int64_t>(part_words, 1) * 4, 256);
     w.total = w.coef + (size_t)round_up(std::max<int64_t>(C, 1) * 16, 256);
     return w;
 }
@@ -1180,11 +1181,21 @@ sq_status sq_l1bn_backward(const float* dy, int64_t M, int64_t C, int64_t ld_dy,
     // operand does), so the finalize skips the fold plan: ext_max = 0
     SQ_TRY(hip_status(launch_colmax_finalize_grad(dy, M, C, ld_dy, cfg, partial, group, gscale, lay, 0, s),
                       "abs-max and finalize"));
-    // canonical codes (no fold descriptor: every channel in its own column, unshifted)
-    SQ_TRY(hip_status(launch_quantize(dy, M, C, ld_dy, group, gscale, cfg, codes, w.ldc, nullptr, 0, nullptr, s),
-                      "quantize"));
+    // canonical codes (no fold: every channel in its own column, unshifted),
+    // with the channel sums in the same pass where the quantizer's 8-channel
+    // form applies
+    int32_t* part = reinterpret_cast<int32_t*>(base + w.part);
+    int64_t part_blocks = 0;
+    if (quantize_bn_ok(dy, C, ld_dy)) {
+        part_blocks = quantize_bn_blocks(M);
+        SQ_TRY(hip_status(launch_quantize_bn(dy, M, C, ld_dy, group, gscale, cfg, codes, w.ldc, xq, ld_x, chan, part, s),
+                          "quantize and sums"));
+    } else {
+        SQ_TRY(hip_status(launch_quantize(dy, M, C, ld_dy, group, gscale, cfg, codes, w.ldc, nullptr, 0, nullptr, s),
+                          "quantize"));
+    }
     return hip_status(launch_l1bn_backward(codes, w.ldc, xq, ld_x, M, C, chan, layer, group, gscale, dx, ld_dx, dgamma,
-                                           dbeta, dx_ranges, reinterpret_cast<int32_t*>(base + w.part),
+                                           dbeta, dx_ranges, part, part_blocks,
                                            reinterpret_cast<float*>(base + w.coef), s),
                       "l1bn backward");
 }

@@ -127,6 +127,15 @@ hipError_t launch_quantize_tensor(const float* x, int64_t M, int64_t C, int64_t 
                                   sq_scale* scale, int8_t* q, int64_t ld_q, int8_t* q_t, int64_t ld_t, hipStream_t s,
                                   PadGrid pg = PadGrid(), bool tiled = false);
 
+// L1BNQ: gradient codes q [M, ldc] and the backward's channel sums of them
+// with the input codes xq, part [2][quantize_bn_blocks(M)][C] (k_quantize_bn);
+// for 16-byte aligned dy rows and C a multiple of 8 (quantize_bn_ok).
+bool quantize_bn_ok(const float* dy, int64_t C, int64_t ld);
+int64_t quantize_bn_blocks(int64_t M);
+hipError_t launch_quantize_bn(const float* dy, int64_t M, int64_t C, int64_t ld, const uint8_t* group,
+                              const sq_scale* scale, const QuantCfg& cfg, int8_t* q, int64_t ldc, const int8_t* xq,
+                              int64_t ld_x, const sq_l1bn_channel* chan, int32_t* part, hipStream_t s);
+
 // Per-channel weight quantization: axis 0 one scale per row, axis 1 one per
 // column (partial: colmax scratch, axis 1 only).
 hipError_t launch_quantize_channels(const float* x, int64_t rows, int64_t cols, int64_t ld, int bits, int axis,
@@ -254,12 +263,13 @@ int64_t l1bn_part_words(int64_t M, int64_t C);
 hipError_t launch_l1bn_forward(const int8_t* xq, int64_t M, int64_t C, int64_t ld_x, const sq_scale* xs,
                                const float* gamma, const float* beta, float* y, int64_t ld_y, sq_l1bn_channel* ch,
                                sq_l1bn_layer* layer, int32_t* part, hipStream_t s);
-// After the gradient codes qg [M, ldg] are formed: sums, constants
-// (coef [C, 4] scratch), dx and its ranges.
+// After the gradient codes qg [M, ldg] are formed: sums (part_blocks > 0: part
+// already holds them, [2][part_blocks][C]), constants (coef [C, 4] scratch), dx
+// and its ranges.
 hipError_t launch_l1bn_backward(const int8_t* qg, int64_t ldg, const int8_t* xq, int64_t ld_x, int64_t M, int64_t C,
                                 const sq_l1bn_channel* ch, const sq_l1bn_layer* layer, const uint8_t* group,
                                 const sq_scale* gscale, float* dx, int64_t ld_dx, float* dgamma, float* dbeta,
-                                uint32_t* ranges, int32_t* part, float* coef, hipStream_t s);
+                                uint32_t* ranges, int32_t* part, int64_t part_blocks, float* coef, hipStream_t s);
 
 // ---- device helpers ----
 // 2^k as a float, exact for -126 <= k <= 127 (from its bit pattern).

@@ -82,126 +82,123 @@ __device__ __forceinline__ int64_t div_round_even(int64_t num, int64_t den) {
     return q;
 }
 
-// Block-level sum of one per-thread accumulator array over the lanes that
-// share a chunk; writes part[c] for the block's channels.
-__device__ __forceinline__ void block_colsum(int32_t* red, const int32_t (&acc)[16], bool active, int lane, int cl,
-                                             const BnGeom& g, int64_t C, int32_t* __restrict__ part) {
-    const int width = g.cis * kBnChunk;
-    __syncthreads();
-    if (active) {
+// Block-level sums of NS per-thread accumulator arrays over the lanes that
+// share a chunk; writes part[k nb C + blockIdx.x C + c] for the block's channels.
+// Accumulator i of thread t sits at word i (kBnThreads + 1) + t, which keeps both
+// the stores and the channel-order reads free of bank conflicts.
+constexpr int kRedLd = kBnThreads + 1, kRedWords = kBnChunk * kRedLd;
+
+template <int NS>
+__device__ __forceinline__ void block_colsum(int32_t (*red)[kRedWords], const int32_t (&acc)[NS][16], const BnGeom& g,
+                                             int64_t C, int32_t* __restrict__ part) {
+    const int tid = threadIdx.x, width = g.cis * kBnChunk;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) red[lane * width + cl * kBnChunk + i] = acc[i];
-    }
+    for (int n = 0; n < NS; ++n)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) red[n][i * kRedLd + tid] = acc[n][i];
     __syncthreads();
-    // up to 256 channels: every thread adds a strided subset of the lanes of
-    // one channel and the subsets' sums go through LDS once more; a wider
-    // block column (257 .. 2048 channels, few lanes): a thread adds the lanes
-    // of every 256th channel
+    // up to 128 channels: J threads per channel add a strided subset of its
+    // lanes each, and the subsets' sums go through LDS once more
     const int64_t cbase = (int64_t)blockIdx.y * width;
-    if (width > kBnThreads) {
-        for (int k = threadIdx.x; k < width; k += kBnThreads) {
-            int32_t s = 0;
-            for (int l = 0; l < g.lanes; ++l) s += red[l * width + k];
-            if (cbase + k < C) part[(int64_t)blockIdx.x * C + cbase + k] = s;
-        }
-        return;
+    const int J = std::max(1, kBnThreads / width);
+    int32_t sub[NS];
+    for (int k = tid % (width * J <= kBnThreads ? width : kBnThreads), j = tid / width; k < width; k += kBnThreads) {
+        const int first = (k % kBnChunk) * kRedLd + k / kBnChunk;
+#pragma unroll
+        for (int n = 0; n < NS; ++n) sub[n] = 0;
+        if (J == 1 || j < J)
+            for (int l = J == 1 ? 0 : j; l < g.lanes; l += J)
+#pragma unroll
+                for (int n = 0; n < NS; ++n) sub[n] += red[n][first + l * g.cis];
+        if (J == 1 && cbase + k < C)
+#pragma unroll
+            for (int n = 0; n < NS; ++n) part[((int64_t)n * g.nb + blockIdx.x) * C + cbase + k] = sub[n];
     }
-    const int J = kBnThreads / width, k = threadIdx.x % width, j = threadIdx.x / width;
-    int32_t sub = 0;
-    if (j < J)
-        for (int l = j; l < g.lanes; l += J) sub += red[l * width + k];
+    if (J == 1) return;
     __syncthreads();
-    if (j < J) red[j * width + k] = sub;
+    if (tid < width * J)
+#pragma unroll
+        for (int n = 0; n < NS; ++n) red[n][tid] = sub[n];   // tid = j width + k
     __syncthreads();
-    if (threadIdx.x < width && cbase + threadIdx.x < C) {
-        int32_t s = 0;
-        for (int i = 0; i < J; ++i) s += red[i * width + threadIdx.x];
-        part[(int64_t)blockIdx.x * C + cbase + threadIdx.x] = s;
+    if (tid < width && cbase + tid < C) {
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+            int32_t t = 0;
+            for (int i = 0; i < J; ++i) t += red[n][i * width + tid];
+            part[((int64_t)n * g.nb + blockIdx.x) * C + cbase + tid] = t;
+        }
     }
 }
 
 // OP 0: S = sum q.  OP 1: A = sum |q - m|, P = sum sgn(q - m).
-// OP 2: G1 = sum qg, G2 = sum qg (q - m)  (a = qg codes, x = input codes).
+// OP 2: G1 = sum qg, G2 = sum qg (q - m)  (a = qg codes, x = input codes), for
+// layers k_quantize_bn does not take.
 // part: [2][nb][C] int32.
 template <int OP>
 __global__ __launch_bounds__(kBnThreads) void k_bn_colsum(const int8_t* __restrict__ a, int64_t lda,
                                                           const int8_t* __restrict__ x, int64_t ldx,
                                                           const sq_l1bn_channel* __restrict__ ch, int64_t M,
                                                           int64_t C, BnGeom g, int32_t* __restrict__ part) {
-    __shared__ int32_t red[kBnThreads * kBnChunk];
+    constexpr int NS = OP == 0 ? 1 : 2;
+    __shared__ int32_t red[NS][kRedWords];
     const int tid = threadIdx.x, cl = tid % g.cis, lane = tid / g.cis;
     const int64_t chunk = (int64_t)blockIdx.y * g.cis + cl, c0 = chunk * kBnChunk;
     const bool active = lane < g.lanes && chunk < g.chunks;
     const int64_t r0 = (int64_t)blockIdx.x * g.rpb, r1 = std::min<int64_t>(M, r0 + g.rpb);
-    int32_t s0[16], s1[16];
+    int32_t acc[NS][16];
     int mu[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
-        s0[i] = 0;
-        s1[i] = 0;
+#pragma unroll
+        for (int n = 0; n < NS; ++n) acc[n][i] = 0;
         // clamped index, select after the load (no branch per channel)
         mu[i] = OP >= 1 ? ch[std::min<int64_t>(c0 + i, C - 1)].mu : 0;
     }
     if (active) {
-        constexpr int U = 4;   // rows in flight per thread
-        int64_t m = r0 + lane;
-        for (; m + (U - 1) * (int64_t)g.lanes < r1; m += U * (int64_t)g.lanes) {
+        constexpr int U = OP == 2 ? 4 : 8;   // rows in flight per thread
+        auto add_row = [&](const int4 va, const int4 vx) {
+            int qa[16], qx[16];
+            unpack16(va, qa);
+            if (OP == 2) unpack16(vx, qx);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                if (OP == 0) {
+                    acc[0][i] += qa[i];
+                } else if (OP == 1) {
+                    const int d = qa[i] - mu[i];
+                    acc[0][i] += d < 0 ? -d : d;
+                    acc[NS - 1][i] += min(max(d, -1), 1);
+                } else {
+                    acc[0][i] += qa[i];
+                    acc[NS - 1][i] += qa[i] * (qx[i] - mu[i]);
+                }
+            }
+        };
+        // row indices clamped, so that a batch's loads issue back to back
+        for (int64_t m = r0 + lane; m < r1; m += U * (int64_t)g.lanes) {
             int4 va[U], vx[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int64_t mm = m + u * (int64_t)g.lanes;
+                const int64_t mm = std::min<int64_t>(m + u * (int64_t)g.lanes, r1 - 1);
                 va[u] = *reinterpret_cast<const int4*>(a + mm * lda + c0);
                 if (OP == 2) vx[u] = *reinterpret_cast<const int4*>(x + mm * ldx + c0);
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                int qa[16], qx[16];
-                unpack16(va[u], qa);
-                if (OP == 2) unpack16(vx[u], qx);
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    if (OP == 0) {
-                        s0[i] += qa[i];
-                    } else if (OP == 1) {
-                        const int d = qa[i] - mu[i];
-                        s0[i] += d < 0 ? -d : d;
-                        s1[i] += sgn(d);
-                    } else {
-                        s0[i] += qa[i];
-                        s1[i] += qa[i] * (qx[i] - mu[i]);
-                    }
-                }
-            }
-        }
-        for (; m < r1; m += g.lanes) {
-            int qa[16], qx[16];
-            unpack16(*reinterpret_cast<const int4*>(a + m * lda + c0), qa);
-            if (OP == 2) unpack16(*reinterpret_cast<const int4*>(x + m * ldx + c0), qx);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                if (OP == 0) {
-                    s0[i] += qa[i];
-                } else if (OP == 1) {
-                    const int d = qa[i] - mu[i];
-                    s0[i] += d < 0 ? -d : d;
-                    s1[i] += sgn(d);
-                } else {
-                    s0[i] += qa[i];
-                    s1[i] += qa[i] * (qx[i] - mu[i]);
-                }
-            }
+            for (int u = 0; u < U; ++u)
+                if (m + u * (int64_t)g.lanes < r1) add_row(va[u], OP == 2 ? vx[u] : va[u]);
         }
     }
-    block_colsum(red, s0, active, lane, cl, g, C, part);
-    if (OP >= 1) block_colsum(red, s1, active, lane, cl, g, C, part + g.nb * C);
+    block_colsum<NS>(red, acc, g, C, part);
 }
 
-// Per-channel totals of the block partials: a block of 16 waves takes 64
-// consecutive channels (one per lane, so every load is a coalesced 256-byte
-// row segment of the partials), the waves split the partial rows, and LDS
-// adds the 16 wave sums.
+// Per-channel totals of the block partials: a block of 16 waves takes
+// kChanPer = 16 consecutive channels, 64 partial rows at a time (a wave reads
+// 4 rows of 64 bytes, 8 loads in flight per thread); lanes of a channel add up
+// by shuffles, waves in LDS.  Bound by latency; with 64 channels per block (one
+// block for the 64-channel layer, 512 partial rows) MEASURED_CHAN.
 //   OP 0: mean code.  OP 1: deviation and sign sums.
 //   OP 2: backward constants (a, b, e), dgamma, dbeta.
+constexpr int kChanPer = 16;
 template <int OP>
 __global__ __launch_bounds__(64 * kBnWaves) void k_bn_chan(const int32_t* __restrict__ part, int64_t nb, int64_t M,
                                                            int64_t C, sq_l1bn_channel* __restrict__ ch,
@@ -210,37 +207,44 @@ __global__ __launch_bounds__(64 * kBnWaves) void k_bn_chan(const int32_t* __rest
                                                            const sq_scale* __restrict__ gscale,
                                                            float* __restrict__ coef, float* __restrict__ dgamma,
                                                            float* __restrict__ dbeta) {
-    __shared__ int64_t sh0[kBnWaves][64], sh1[kBnWaves][64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+    __shared__ int64_t sh0[kBnWaves][kChanPer], sh1[kBnWaves][kChanPer];
+    const int k = threadIdx.x % kChanPer, row = threadIdx.x / kChanPer, w = threadIdx.x >> 6;
+    const int64_t c = (int64_t)blockIdx.x * kChanPer + k;
     const int64_t cc = std::min<int64_t>(c, C - 1);
-    constexpr int U = 8;
+    constexpr int U = 8, kRows = 64 * kBnWaves / kChanPer;
     int64_t t0 = 0, t1 = 0;
-    for (int64_t b0 = w; b0 < nb; b0 += (int64_t)kBnWaves * U) {
+    for (int64_t b0 = row; b0 < nb; b0 += (int64_t)kRows * U) {
         int32_t v0[U], v1[U];
         // clamped row, select after the load: the loads issue back to back
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t b = std::min<int64_t>(b0 + (int64_t)kBnWaves * u, nb - 1);
+            const int64_t b = std::min<int64_t>(b0 + (int64_t)kRows * u, nb - 1);
             v0[u] = part[b * C + cc];
             v1[u] = OP >= 1 ? part[(nb + b) * C + cc] : 0;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const bool in = b0 + (int64_t)kBnWaves * u < nb;
+            const bool in = b0 + (int64_t)kRows * u < nb;
             t0 += in ? v0[u] : 0;
             t1 += in ? v1[u] : 0;
         }
     }
-    sh0[w][lane] = t0;
-    sh1[w][lane] = t1;
+#pragma unroll
+    for (int o = kChanPer; o < 64; o <<= 1) {
+        t0 += __shfl_xor(t0, o, 64);
+        if (OP >= 1) t1 += __shfl_xor(t1, o, 64);
+    }
+    if ((threadIdx.x & 63) < kChanPer) {
+        sh0[w][k] = t0;
+        sh1[w][k] = t1;
+    }
     __syncthreads();
-    if (w != 0 || c >= C) return;
+    if (threadIdx.x >= kChanPer || c >= C) return;
     t0 = t1 = 0;
 #pragma unroll
     for (int i = 0; i < kBnWaves; ++i) {
-        t0 += sh0[i][lane];
-        t1 += sh1[i][lane];
+        t0 += sh0[i][k];
+        t1 += sh1[i][k];
     }
     if (OP == 0) {
         sq_l1bn_channel v{};
@@ -500,7 +504,7 @@ hipError_t launch_l1bn_forward(const int8_t* xq, int64_t M, int64_t C, int64_t l
     if (C <= 0) return hipSuccess;
     const BnGeom gs = sum_geom(M, C);
     const QuadGeom ga = quad_geom(M, C);
-    const dim3 sum_grid((unsigned)gs.nb, (unsigned)gs.slabs), chan_grid((unsigned)((C + 63) / 64));
+    const dim3 sum_grid((unsigned)gs.nb, (unsigned)gs.slabs), chan_grid((unsigned)((C + kChanPer - 1) / kChanPer));
     hipLaunchKernelGGL(k_bn_colsum<0>, sum_grid, dim3(kBnThreads), 0, s, xq, ld_x, nullptr, 0, ch, M, C, gs, part);
     hipLaunchKernelGGL(k_bn_chan<0>, chan_grid, dim3(64 * kBnWaves), 0, s, part, gs.nb, M, C, ch, nullptr, nullptr,
                        nullptr, nullptr, nullptr, nullptr);
@@ -517,14 +521,17 @@ hipError_t launch_l1bn_forward(const int8_t* xq, int64_t M, int64_t C, int64_t l
 hipError_t launch_l1bn_backward(const int8_t* qg, int64_t ldg, const int8_t* xq, int64_t ld_x, int64_t M, int64_t C,
                                 const sq_l1bn_channel* ch, const sq_l1bn_layer* layer, const uint8_t* group,
                                 const sq_scale* gscale, float* dx, int64_t ld_dx, float* dgamma, float* dbeta,
-                                uint32_t* ranges, int32_t* part, float* coef, hipStream_t s) {
+                                uint32_t* ranges, int32_t* part, int64_t part_blocks, float* coef, hipStream_t s) {
     if (C <= 0) return hipSuccess;
-    const BnGeom gs = sum_geom(M, C);
     const QuadGeom ga = quad_geom(M, C);
-    hipLaunchKernelGGL(k_bn_colsum<2>, dim3((unsigned)gs.nb, (unsigned)gs.slabs), dim3(kBnThreads), 0, s, qg, ldg, xq,
-                       ld_x, ch, M, C, gs, part);
-    hipLaunchKernelGGL(k_bn_chan<2>, dim3((unsigned)((C + 63) / 64)), dim3(64 * kBnWaves), 0, s, part,
-                       gs.nb, M, C, const_cast<sq_l1bn_channel*>(ch), layer, group, gscale, coef, dgamma, dbeta);
+    if (part_blocks <= 0) {
+        const BnGeom gs = sum_geom(M, C);
+        part_blocks = gs.nb;
+        hipLaunchKernelGGL(k_bn_colsum<2>, dim3((unsigned)gs.nb, (unsigned)gs.slabs), dim3(kBnThreads), 0, s, qg, ldg, xq,
+                           ld_x, ch, M, C, gs, part);
+    }
+    hipLaunchKernelGGL(k_bn_chan<2>, dim3((unsigned)((C + kChanPer - 1) / kChanPer)), dim3(64 * kBnWaves), 0, s, part,
+                       part_blocks, M, C, const_cast<sq_l1bn_channel*>(ch), layer, group, gscale, coef, dgamma, dbeta);
     const bool vec = (ld_dx % 4 == 0) && (reinterpret_cast<uintptr_t>(dx) % 16 == 0);
     hipLaunchKernelGGL(k_bn_apply<true>, dim3((unsigned)ga.nb, (unsigned)ga.slabs), dim3(kBnThreads), 0, s, qg, ldg,
                        xq, ld_x, ch, coef, M, C, ga, dx, ld_dx, vec, ranges);

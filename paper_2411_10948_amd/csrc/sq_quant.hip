@@ -1071,6 +1071,110 @@ __global__ __launch_bounds__(kBlock) void k_quantize_grid(const float* __restric
     }
 }
 
+// Gradient codes of an L1BNQ layer together with the channel sums its backward
+// needs of them: codes q [M, ldc] (no fold) and, per row block and channel,
+// part[0][block][c] = sum q and part[1][block][c] = sum q (x - mu) with the
+// layer's input codes x.  A block of 512 threads takes 64 channels of its
+// rows, 256 at a time: quant8 leaves a thread the codes of 4 rows of a channel
+// in one word, so with x moved to the same order (byte permutes) each channel's
+// products are one 4-way dot.  Bound by memory (4 + 1 B read, 1 B written per
+// element).  As a quantize pass and a pass over both codes: MEASURED_BNQ.
+constexpr int kBnQThreads = 512, kBnQRows = kBnQThreads / 8 * 4;
+
+// bytes of 4 row words (columns 0 .. 3 each) to 4 column words (rows 0 .. 3 each)
+__device__ __forceinline__ void transpose4x4(const uint32_t (&r)[4], uint32_t (&c)[4]) {
+    const uint32_t a = __builtin_amdgcn_perm(r[1], r[0], 0x05010400u);   // r0.0 r1.0 r0.1 r1.1
+    const uint32_t b = __builtin_amdgcn_perm(r[1], r[0], 0x07030602u);   // r0.2 r1.2 r0.3 r1.3
+    const uint32_t d = __builtin_amdgcn_perm(r[3], r[2], 0x05010400u);
+    const uint32_t e = __builtin_amdgcn_perm(r[3], r[2], 0x07030602u);
+    c[0] = __builtin_amdgcn_perm(d, a, 0x05040100u);
+    c[1] = __builtin_amdgcn_perm(d, a, 0x07060302u);
+    c[2] = __builtin_amdgcn_perm(e, b, 0x05040100u);
+    c[3] = __builtin_amdgcn_perm(e, b, 0x07060302u);
+}
+
+template <bool SR>
+__global__ __launch_bounds__(kBnQThreads) void k_quantize_bn(const float* __restrict__ dy, int64_t M, int64_t C,
+                                                             int64_t ld, const uint8_t* __restrict__ group,
+                                                             const sq_scale* __restrict__ scale, QuantCfg cfg,
+                                                             int8_t* __restrict__ q, int64_t ldc,
+                                                             const int8_t* __restrict__ xq, int64_t ld_x,
+                                                             const sq_l1bn_channel* __restrict__ chan,
+                                                             int64_t rows_per_block, int32_t* __restrict__ part) {
+    __shared__ int32_t red[2][kBnQThreads / 64][64];
+    const int tid = threadIdx.x, g8 = tid & 7, rq = tid >> 3;
+    const int64_t c0 = (int64_t)blockIdx.y * 64 + 8 * g8;
+    const bool cin = c0 < C;
+    const int64_t cs = cin ? c0 : 0;
+    const int64_t r_end = min(M, ((int64_t)blockIdx.x + 1) * rows_per_block);
+    int g1[8], g2[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) g1[j] = g2[j] = 0;
+    for (int64_t r0 = (int64_t)blockIdx.x * rows_per_block; r0 < r_end; r0 += kBnQRows) {
+        const int64_t m0 = r0 + 4 * rq;
+        float4 a[4], b[4];
+        uint2 xw[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t m = min(m0 + i, M - 1);
+            const float* src = dy + m * ld + cs;
+            a[i] = *reinterpret_cast<const float4*>(src);
+            b[i] = *reinterpret_cast<const float4*>(src + 4);
+            xw[i] = *reinterpret_cast<const uint2*>(xq + m * ld_x + cs);
+        }
+        const sq_scale sc = *scale;
+        const Chan8 ch = load_chan8(group, nullptr, c0, cin, (reinterpret_cast<uintptr_t>(group) & 7) == 0, sc.inv);
+        bool ok[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ok[i] = cin && sc.flags == 0u && m0 + i < r_end;
+        uint32_t colw[8];
+        uint2 fold[4];
+        quant8<SR>(a, b, ok, m0 * C + c0, C, ch, cfg, colw, fold);
+        if (cin) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (m0 + i < r_end) *reinterpret_cast<uint2*>(q + (m0 + i) * ldc + c0) = fold[i];
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t rows[4] = {h ? xw[0].y : xw[0].x, h ? xw[1].y : xw[1].x, h ? xw[2].y : xw[2].x,
+                                      h ? xw[3].y : xw[3].x};
+            uint32_t cols[4];
+            transpose4x4(rows, cols);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                g1[4 * h + j] = __builtin_amdgcn_sdot4((int)colw[4 * h + j], 0x01010101, g1[4 * h + j], false);
+                g2[4 * h + j] = __builtin_amdgcn_sdot4((int)colw[4 * h + j], (int)cols[j], g2[4 * h + j], false);
+            }
+        }
+    }
+    // the 8 row lanes of a wave, then the waves through LDS
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+#pragma unroll
+        for (int o = 8; o < 64; o <<= 1) {
+            g1[j] += __shfl_xor(g1[j], o, 64);
+            g2[j] += __shfl_xor(g2[j], o, 64);
+        }
+        if ((tid & 63) < 8) {
+            red[0][tid >> 6][8 * g8 + j] = g1[j];
+            red[1][tid >> 6][8 * g8 + j] = g2[j];
+        }
+    }
+    __syncthreads();
+    const int64_t c = (int64_t)blockIdx.y * 64 + tid;
+    if (tid < 64 && c < C) {
+        int32_t s1 = 0, s2 = 0;
+#pragma unroll
+        for (int w = 0; w < kBnQThreads / 64; ++w) {
+            s1 += red[0][w][tid];
+            s2 += red[1][w][tid];
+        }
+        part[(int64_t)blockIdx.x * C + c] = s1;
+        part[((int64_t)gridDim.x + blockIdx.x) * C + c] = s2 - chan[c].mu * s1;
+    }
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -1341,6 +1445,34 @@ hipError_t launch_quantize(const float* x, int64_t M, int64_t C, int64_t ld, con
     else if (tr == 64) SQ_LAUNCH_QUANT(128, 64);
     else SQ_LAUNCH_QUANT(128, 128);
 #undef SQ_LAUNCH_QUANT
+    return hipGetLastError();
+}
+
+// At most kBnQBlocks row blocks of whole 256-row steps: with M <= 2^24 a block
+// holds at most 16384 rows, and its int32 sums stay below 2^30.
+constexpr int64_t kBnQBlocks = 1024;
+static int64_t bn_rows_per_block(int64_t M) {
+    return round_up((M + kBnQBlocks - 1) / kBnQBlocks, kBnQRows);
+}
+int64_t quantize_bn_blocks(int64_t M) {
+    const int64_t rows = bn_rows_per_block(std::max<int64_t>(M, 1));
+    return (M + rows - 1) / rows;
+}
+
+bool quantize_bn_ok(const float* dy, int64_t C, int64_t ld) { return C % 8 == 0 && C <= 64 * 65535 && colmax_vec(dy, ld); }
+
+hipError_t launch_quantize_bn(const float* dy, int64_t M, int64_t C, int64_t ld, const uint8_t* group,
+                              const sq_scale* scale, const QuantCfg& cfg, int8_t* q, int64_t ldc, const int8_t* xq,
+                              int64_t ld_x, const sq_l1bn_channel* chan, int32_t* part, hipStream_t s) {
+    if (M <= 0 || C <= 0) return hipSuccess;
+    if (!quantize_bn_ok(dy, C, ld) || ldc % 8 || ld_x % 8) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)quantize_bn_blocks(M), (unsigned)((C + 63) / 64));
+    if (cfg.round_mode == SQ_ROUND_STOCHASTIC)
+        hipLaunchKernelGGL(k_quantize_bn<true>, grid, dim3(kBnQThreads), 0, s, dy, M, C, ld, group, scale, cfg, q, ldc, xq,
+                           ld_x, chan, bn_rows_per_block(M), part);
+    else
+        hipLaunchKernelGGL(k_quantize_bn<false>, grid, dim3(kBnQThreads), 0, s, dy, M, C, ld, group, scale, cfg, q, ldc,
+                           xq, ld_x, chan, bn_rows_per_block(M), part);
     return hipGetLastError();
 }
 
