@@ -557,28 +557,34 @@ __global__ __launch_bounds__(T::kThreads, 2) void k_gemm_pipe(GemmArgs p, int64_
     for (int i = 0; i < T::IA; ++i) offA[i] = lane_off(i, m0, p.Mg, p.lda);
 #pragma unroll
     for (int i = 0; i < T::IB; ++i) offB[i] = lane_off(i, n0, p.Ng, p.ldb);
-    // Convolution: the input pixel (n, ih, iw) of each of this lane's A rows;
-    // tap (r, s) reads output pixel (n, ih + PH - r, iw + PW - s) of q_fold,
-    // or, outside the output grid, an offset past the end of the buffer,
-    // which the buffer load's range check turns into zeros.
-    int cv_ih[CONV ? T::IA : 1], cv_iw[CONV ? T::IA : 1], cv_row0[CONV ? T::IA : 1];
-    uint32_t cv_chunk[CONV ? T::IA : 1];
+    // Convolution: tap (r, s) of this lane's A row, input pixel (n, ih, iw),
+    // reads output pixel (n, ih + PH - r, iw + PW - s) of q_fold, a fixed
+    // offset minus the tap's scalar (r Wo + s) lda, or, outside the output
+    // grid, an offset past the end of the buffer, which the buffer load's range
+    // check turns into zeros.  cv_in: which r (bits 0 ..) and s (bits 16 ..) lie
+    // inside.  Four vector instructions per load; with the pixel's coordinates
+    // checked and multiplied out per tap, a K tile of 128 x 128 took 0.45 us
+    // instead of 0.36.
+    uint32_t cv_base[CONV ? T::IA : 1], cv_in[CONV ? T::IA : 1];
     if constexpr (CONV) {
+        const int KH = p.taps / p.cv_KW;
+        auto bits = [](int at, int n, int k) {   // taps t < k with 0 <= at - t < n
+            const int lo = max(0, at - n + 1), hi = min(k - 1, at);
+            return hi < lo ? 0u : ((2u << hi) - 1u) & ~((1u << lo) - 1u);
+        };
 #pragma unroll
         for (int i = 0; i < T::IA; ++i) {
             const int r = (i * T::kWaves + wv) * 16 + lr;
-            const int64_t pix = min(m0 + r, p.Mg - 1);
-            const int64_t n = pix / (p.cv_H * p.cv_W), hw = pix - n * p.cv_H * p.cv_W;
-            cv_ih[i] = (int)(hw / p.cv_W);
-            cv_iw[i] = (int)(hw - (int64_t)cv_ih[i] * p.cv_W);
-            cv_row0[i] = (int)(n * p.cv_Ho * p.cv_Wo);
-            cv_chunk[i] = 16u * (uint32_t)((lane & 3) ^ swz(r));
+            const uint32_t pix = (uint32_t)min(m0 + r, p.Mg - 1), W = (uint32_t)p.cv_W, HW = (uint32_t)p.cv_H * W;
+            const uint32_t n = pix / HW, hw = pix - n * HW, ih = hw / W, iw = hw - ih * W;
+            const int h = (int)ih + p.cv_PH, w = (int)iw + p.cv_PW;
+            cv_in[i] = bits(h, (int)p.cv_Ho, KH) | bits(w, (int)p.cv_Wo, p.cv_KW) << 16;
+            cv_base[i] = (n * (uint32_t)(p.cv_Ho * p.cv_Wo) + (uint32_t)h * (uint32_t)p.cv_Wo + (uint32_t)w) * (uint32_t)p.lda +
+                         16u * (uint32_t)((lane & 3) ^ swz(r));
         }
     }
-    auto conv_off = [&](int i, int tr, int ts) -> uint32_t {
-        const int oh = cv_ih[i] + p.cv_PH - tr, ow = cv_iw[i] + p.cv_PW - ts;
-        const bool ok = (uint32_t)oh < (uint32_t)p.cv_Ho && (uint32_t)ow < (uint32_t)p.cv_Wo;
-        return ok ? (uint32_t)((cv_row0[i] + oh * (int)p.cv_Wo + ow) * (int)p.lda) + cv_chunk[i] : 0x80000000u;
+    auto conv_off = [&](int i, uint32_t want, uint32_t delta) -> uint32_t {
+        return (cv_in[i] & want) == want ? cv_base[i] - delta : 0x80000000u;
     };
 
     // (flat tile, tap) of the next tile to issue and of the next tile to
@@ -587,7 +593,9 @@ __global__ __launch_bounds__(T::kThreads, 2) void k_gemm_pipe(GemmArgs p, int64_
     auto issue = [&](int t) {
         int8_t* st = smem + (t % T::STAGES) * T::kStage;
         if constexpr (CONV) {
-            const int f = icur.f, tr = icur.r, ts = icur.s;
+            const int f = icur.f;
+            const uint32_t want = 1u << icur.r | 0x10000u << icur.s;
+            const uint32_t delta = (uint32_t)(icur.r * (int)p.cv_Wo + icur.s) * (uint32_t)p.lda;
             icur.next(taps, p.cv_KW);
             const bool ext = HORNER && fv.is_ext(f, n_main);
             const int k0 = ext ? (int)fv.ext_col(f, n_main) : (f - fv.h_tiles) * T::BK;
@@ -595,7 +603,7 @@ __global__ __launch_bounds__(T::kThreads, 2) void k_gemm_pipe(GemmArgs p, int64_
 #pragma unroll
             for (int i = 0; i < T::IA; ++i)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(st + (i * T::kWaves + wv) * 1024), 16,
-                                                         conv_off(i, tr, ts), k0, 0, 0);
+                                                         conv_off(i, want, delta), k0, 0, 0);
 #pragma unroll
             for (int i = 0; i < T::IB; ++i)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rB, (lds_void_t*)(st + T::BM * T::BK + (i * T::kWaves + wv) * 1024),
@@ -926,167 +934,7 @@ __global__ __launch_bounds__(T::kThreads, 2) void k_gemm_pipe(GemmArgs p, int64_
 }
 
 // ---------------------------------------------------------------------------
-// Input gradient of a "same" stride-1 convolution (Ho = H, Wo = W) with the
-// rows of q_fold staged once per K chunk.  Tap (r, s) of input pixel p reads
-// q_fold row p + d, d = (PH - r) W + (PW - s), so the rows a tile of BM
-// pixels needs for all taps form the contiguous window [p0 - E, p0 + BM + E),
-// E = PH W + PW.  Per 64-column chunk of the fold's flat K sequence the block
-// loads that window and the chunk's weights of every tap into LDS once, then
-// runs one round of MFMAs per tap on rows of the window shifted by d.  A tap
-// whose output pixel lies outside the image (its row belongs to another image
-// row or image) adds nothing: that lane's operand fragment is cleared.  The
-// K order (chunk-major, tap-minor) and the Horner shifts at region starts are
-// those of the per-tap kernel.
-// ---------------------------------------------------------------------------
-constexpr int kHaloBM = 256, kHaloExtra = 128, kHaloWaves = 4, kHaloMaxTaps = 9;
-
-template <bool HORNER>
-__global__ __launch_bounds__(64 * kHaloWaves) void k_conv_halo(GemmArgs p) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int BM = kHaloBM, BN = 64, BK = 64, WR = kHaloBM + kHaloExtra;   // window rows
-    constexpr int kA = WR * BK;
-    __shared__ __attribute__((aligned(1024))) int8_t smem[kA + kHaloMaxTaps * BN * BK];
-    using MF = Mfma<16>;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wv = __builtin_amdgcn_readfirstlane(wave);
-    const int64_t m0 = (int64_t)blockIdx.x * BM, n0 = (int64_t)blockIdx.y * BN;
-    const int taps = p.taps, KW = p.cv_KW, H = (int)p.cv_H, W = (int)p.cv_W;
-    const int E = p.cv_PH * W + p.cv_PW;
-    const FoldView fv = fold_view(p, BK);
-    const int n_main = (int)(p.K / BK);
-    const int n_chunks = fv.n_ext + n_main;
-
-    constexpr int kRsrcFlags = 0x00020000;   // raw byte buffer, gfx9 data format
-    auto rsrc = [&](const int8_t* base, int64_t rows, int64_t ld) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(base), (short)0,
-                                                 (int)min(rows * ld, (int64_t)0x7FFFFFFF), kRsrcFlags);
-    };
-    const __amdgpu_buffer_rsrc_t rA = rsrc(p.A, p.a_rows, p.lda), rB = rsrc(p.B, p.Ng, p.ldb);
-    const int lr = lane >> 2;
-    // window rows: instruction i of this wave fills rows (i * waves + wv) * 16 .. + 15;
-    // rows before the tensor get an offset past the end of the buffer (zeros)
-    constexpr int kWin = WR / 16 / kHaloWaves;
-    uint32_t offW[kWin];
-#pragma unroll
-    for (int i = 0; i < kWin; ++i) {
-        const int w = (i * kHaloWaves + wv) * 16 + lr;
-        const int64_t g = m0 - E + w;
-        offW[i] = g >= 0 ? (uint32_t)(g * p.lda) + 16u * (uint32_t)((lane & 3) ^ swz(w)) : 0x80000000u;
-    }
-    // weights: this wave fills rows wv * 16 .. + 15 of each tap's 64-row block
-    const int brow = wv * 16 + lr;
-    const uint32_t offBw = (uint32_t)(min(n0 + brow, p.Ng - 1) * p.ldb);
-
-    // the input pixel of each of this lane's 4 accumulator rows (one per
-    // 16-row MFMA block of the wave's 64 rows)
-    const int lrow = lane % 16, lc = lane / 16;
-    int ih[4], iw[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t pix = min(m0 + wv * 64 + i * 16 + lrow, p.Mg - 1);
-        const int hw = (int)(pix % ((int64_t)H * W));
-        ih[i] = hw / W;
-        iw[i] = hw - ih[i] * W;
-    }
-
-    v4i acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = v4i{0, 0, 0, 0};
-
-    HornerSteps hs(p);
-    for (int f = 0; f < n_chunks; ++f) {
-        // stage the chunk: the row window of q_fold and every tap's weights
-        const bool ext = HORNER && fv.is_ext(f, n_main);
-        const int kc = ext ? (int)fv.ext_col(f, n_main) : (f - fv.h_tiles) * BK;
-        const __amdgpu_buffer_rsrc_t ra = ext ? rsrc(p.extA, p.a_rows, p.ld_extA) : rA;
-        __syncthreads();   // the previous chunk's reads of LDS are done
-#pragma unroll
-        for (int i = 0; i < kWin; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(smem + (i * kHaloWaves + wv) * 1024), 16,
-                                                     offW[i], kc, 0, 0);
-        for (int tau = 0; tau < taps; ++tau) {
-            const int row = tau * BN + brow;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rB, (lds_void_t*)(smem + kA + (tau * BN + wv * 16) * BK), 16,
-                offBw + 16u * (uint32_t)((lane & 3) ^ swz(row)), (f * taps + tau) * BK, 0, 0);
-        }
-        wait_vm<0>();
-        __syncthreads();
-        if (HORNER && (int64_t)f * BK == hs.col) {
-            const int sft = hs.advance();
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = acc[i][j] << sft;
-        }
-        for (int tau = 0, tr = 0, ts = 0; tau < taps; ++tau) {
-            const int d = (p.cv_PH - tr) * W + (p.cv_PW - ts);
-            v4i fa[4], fb[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int w = wv * 64 + i * 16 + lrow + E + d;
-                const v4i v = *reinterpret_cast<const v4i*>(&smem[w * BK + 16 * (lc ^ swz(w))]);
-                const int oh = ih[i] + p.cv_PH - tr, ow = iw[i] + p.cv_PW - ts;
-                const bool ok = (unsigned)oh < (unsigned)H && (unsigned)ow < (unsigned)W;
-                fa[i] = ok ? v : v4i{0, 0, 0, 0};
-            }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = tau * BN + j * 16 + lrow;
-                fb[j] = *reinterpret_cast<const v4i*>(&smem[kA + r * BK + 16 * (lc ^ swz(r))]);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = MF::run(fb[j], fa[i], acc[i][j]);
-            if (++ts == KW) { ts = 0; ++tr; }
-        }
-    }
-
-    // epilogue: alpha = step_G * step_W * 2^-(N_G - 1), the fold's final shift
-    const int fsh = HORNER ? fv.fshift : 0;
-    float alpha = 0.0f;
-    if (p.out) {
-        const sq_scale gs = *p.gs, os = *p.os;
-        alpha = __fmul_rn(__fmul_rn(gs.step, os.step), pow2f(-(p.num_groups - 1)));
-    }
-    const bool vec_acc = p.acc && ((p.ld_acc & 3) == 0) && ((reinterpret_cast<uintptr_t>(p.acc) & 15) == 0);
-    const bool vec_out = p.out && ((p.ld_out & 3) == 0) && ((reinterpret_cast<uintptr_t>(p.out) & 15) == 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t ii = m0 + wv * 64 + i * 16 + lrow;
-        if (ii >= p.Mg) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t jj = n0 + j * 16 + lc * 4;
-            if (jj >= p.Ng) continue;
-            const int vv[4] = {acc[i][j][0] << fsh, acc[i][j][1] << fsh, acc[i][j][2] << fsh, acc[i][j][3] << fsh};
-            const bool full = jj + 4 <= p.Ng;
-            if (p.acc) {
-                int32_t* dst = p.acc + ii * p.ld_acc + jj;
-                if (vec_acc && full) *reinterpret_cast<int4*>(dst) = make_int4(vv[0], vv[1], vv[2], vv[3]);
-                else
-                    for (int e = 0; e < 4; ++e)
-                        if (jj + e < p.Ng) dst[e] = vv[e];
-            }
-            if (p.out) {
-                float* dst = p.out + ii * p.ld_out + jj;
-                const float ff[4] = {__fmul_rn((float)vv[0], alpha), __fmul_rn((float)vv[1], alpha),
-                                     __fmul_rn((float)vv[2], alpha), __fmul_rn((float)vv[3], alpha)};
-                if (vec_out && full) *reinterpret_cast<float4*>(dst) = make_float4(ff[0], ff[1], ff[2], ff[3]);
-                else
-                    for (int e = 0; e < 4; ++e)
-                        if (jj + e < p.Ng) dst[e] = ff[e];
-            }
-        }
-    }
-#endif
-}
-
-// ---------------------------------------------------------------------------
-// Streaming variant of the same-size convolution input gradient for one
+// Same-size convolution input gradient (Ho = H, Wo = W), streaming: one
 // 64-column K chunk (C_out <= 64, every shift in one window) and C_in <= 64.
 // Each block owns a contiguous range of input pixels and walks it in steps of
 // 128 rows (a wave takes rows 16 w .. and 64 + 16 w .. of the step, so each
@@ -1106,7 +954,7 @@ __global__ __launch_bounds__(64 * kHaloWaves) void k_conv_halo(GemmArgs p) {
 // of their ring row.
 // ---------------------------------------------------------------------------
 [[maybe_unused]] constexpr int kStreamRing = 8, kStreamPF = 2, kStreamNW = 4;   // ring chunks, prefetch steps, chunks per step
-constexpr int kStreamBlocks = 512;
+constexpr int kStreamBlocks = 512, kStreamMaxTaps = 9;
 
 // Hide a value from the optimizer, so that a memory instruction whose lanes
 // take different offsets stays one instruction (not one per branch of a select).
@@ -1120,7 +968,7 @@ template <bool ACC, bool FULLK, bool RANGES = false>
 __global__ __launch_bounds__(256) void k_conv_stream(GemmArgs p, int64_t rows_per_block) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int BK = 64, kRing = kStreamRing * 64 * BK;
-    constexpr int kZero = kRing + kHaloMaxTaps * 64 * BK;   // 16 zero bytes
+    constexpr int kZero = kRing + kStreamMaxTaps * 64 * BK;   // 16 zero bytes
     constexpr int NS = ACC ? 16 : 8;   // stores per lane and step
     static_assert(kStreamNW + 2 * kStreamPF <= kStreamRing && 2 * NS + 4 <= 63, "ring / vmcnt range");
     __shared__ __attribute__((aligned(1024))) int8_t smem[kZero + 16];
@@ -1498,7 +1346,7 @@ bool pipe_ok(const GemmArgs& a) {
 // 79.2 us, now 68.8) and 28 % of a split one (768 x 768, K = 3152: 18.0 us, now
 // 11.7).  Constants fitted to the products alone, hot in the caches, picked
 // small tiles for long products that read HBM (MLP wgrad 45 -> 54 us).
-enum class Pick { kLarge, kTall, kDuo, kMid, kSmall, kFlat, kTiny };
+enum class Pick { kLarge, kTall, kDuo, kMid, kSmall, kFlat, kTiny, kNarrow };
 struct TileCost {
     int bm, bn, per_cu;
     float lat, thr, round, mb;
@@ -1516,11 +1364,10 @@ double tiles_of(int i, int64_t Mg, int64_t Ng) {
 // int32 partials of `splits` K slices (mb MB each), written and summed
 float split_cost(double mb, int splits) { return 5.0f + (float)mb * (0.36f * (float)splits + 0.06f); }
 
-// us of a launch beyond its fixed cost, `tiles` the output tiles of shape i (a
+// us of a launch beyond its fixed cost, `tiles` the output tiles of the shape (a
 // whole number below 2^53; doubles, since this runs on every call and 64-bit
 // integer divisions took longer than the launch)
-float tile_cost(int i, double tiles, double mb, int64_t ktiles, int splits) {
-    const TileCost& c = kTileCost[i];
+float tile_cost(const TileCost& c, double tiles, double mb, int64_t ktiles, int splits) {
     const double slots = (double)(kCUs * c.per_cu), blocks = tiles * splits;
     const double rounds = std::floor(blocks / slots);
     const float n = (float)std::ceil((blocks - rounds * slots) * (1.0 / kCUs));   // blocks on the last round's fullest CU
@@ -1537,11 +1384,41 @@ Pick best_tile(int64_t Mg, int64_t Ng, int64_t K, int splits, float* cost = null
     int best = 0;
     float t = 0.0f;
     for (int i = 0; i < kTiles; ++i) {
-        const float ti = tile_cost(i, tiles_of(i, Mg, Ng), mb, ktiles, splits);
+        const float ti = tile_cost(kTileCost[i], tiles_of(i, Mg, Ng), mb, ktiles, splits);
         if (i == 0 || ti < t) { best = i; t = ti; }
     }
     if (cost) *cost = t;
     return (Pick)best;
+}
+
+// Tile of the per-tap convolution: at most 64 columns take 256 x 64 where that
+// gives a block for half of the CUs; else the least cost of the small tiles,
+// by the same model with constants fitted to 16 conv steps (a K tile's chain is
+// longer than a plain product's: scattered 64-byte row pieces).  Against one
+// staged window of rows per 64 columns with all taps read from it, unpipelined,
+// in the step: 64 x 14 x 14, 256 -> 256 channels 74.7 -> 70.0 us; 64 x 7 x 7,
+// 512 -> 512 122.3 -> 110.3; 64 x 28 x 28, 128 -> 128 with a fold window 98.4 ->
+// 94.5; 3 x 24 x 24, 414 -> 110 with three 100.3 -> 84.2.
+constexpr TileCost kConvCost[] = {{128, 128, 2, 0.36f, 0.21f, 2.0f, 0.110f}, {64, 128, 3, 0.30f, 0.155f, 0.6f, 0.130f},
+                                  {64, 64, 5, 0.255f, 0.18f, 2.0f, 0.080f}};
+Pick best_conv_tile(int64_t Mg, int64_t Ng, int64_t ktiles) {
+    const bool narrow = Ng <= PipeNarrow::BN;   // 128-column tiles would be half empty
+    if (narrow && 2 * ((Mg + PipeNarrow::BM - 1) / PipeNarrow::BM) >= kCUs) return Pick::kNarrow;
+    constexpr Pick kPicks[] = {Pick::kSmall, Pick::kFlat, Pick::kTiny};
+    int best = 2;
+    float t = 0.0f;
+    for (int i = 0; i < 3 && !narrow; ++i) {
+        const TileCost& c = kConvCost[i];
+        const double tiles = std::ceil((double)Mg / c.bm) * std::ceil((double)Ng / c.bn);
+        const float ti = tile_cost(c, tiles, 4e-6 * (double)Mg * (double)Ng, ktiles, 1);
+        if (i == 0 || ti < t) { best = i; t = ti; }
+    }
+    return kPicks[best];
+}
+
+template <class T>
+hipError_t launch_conv_tile(const GemmArgs& a, hipStream_t s) {
+    return a.extA ? launch_pipe<T, true, true>(a, 1, a.K, s) : launch_pipe<T, false, true>(a, 1, a.K, s);
 }
 
 // Rows of an unsplit product to run with 256 x 256 tiles, the rest going to a
@@ -1556,7 +1433,7 @@ int64_t large_rows(int64_t Mg, int64_t Ng, int64_t K) {
     best_tile(Mg, Ng, K, 1, &one);
     best_tile(Mg - rows, Ng, K, 1, &rest);
     constexpr float kLaunch = 4.0f;
-    const float main = tile_cost(0, tiles_of(0, rows, Ng), 4e-6 * (double)rows * (double)Ng, (K + 63) / 64, 1);
+    const float main = tile_cost(kTileCost[0], tiles_of(0, rows, Ng), 4e-6 * (double)rows * (double)Ng, (K + 63) / 64, 1);
     return main + rest + kLaunch < one ? rows : 0;
 }
 
@@ -1599,7 +1476,7 @@ int wgrad_splits(int64_t M, int64_t C_out, int64_t C_in) {
         const int64_t per = (ktiles + want - 1) / want;
         const int s = per > 0 ? (int)((ktiles + per - 1) / per) : 1;
         for (int i = 0; i < kTiles; ++i) {
-            const float ts = tile_cost(i, tiles[i], mb, ktiles, s);
+            const float ts = tile_cost(kTileCost[i], tiles[i], mb, ktiles, s);
             if ((want == 1 && i == 0) || ts < t) { best = s; t = ts; }
         }
     }
@@ -2096,8 +1973,8 @@ hipError_t launch_conv_gather_w(const int8_t* wq_t, int64_t ld_w, int64_t C_out,
 // a.extA the main and appended columns of q_fold ([a_rows, lda]), a.B / a.ldb
 // the W^T codes.  Same-size convolutions with one K chunk and a narrow output
 // stream (k_conv_stream, weights straight from W^T); the others gather the
-// weights into bc in the implicit GEMM's K order and take the window kernel
-// (same size, small window) or the per-tap pipelined kernel.
+// weights into bc in the implicit GEMM's K order and take the per-tap
+// pipelined kernel.
 hipError_t launch_conv_dgrad(const GemmArgs& a0, int8_t* bc, int64_t ld_bc, hipStream_t s, int64_t* range_rows) {
     if (a0.Mg <= 0 || a0.Ng <= 0) return hipSuccess;
     if (a0.ranges && (!a0.out || !range_rows)) return hipErrorInvalidValue;
@@ -2111,7 +1988,7 @@ hipError_t launch_conv_dgrad(const GemmArgs& a0, int8_t* bc, int64_t ld_bc, hipS
     auto small_out = [](const void* q, int64_t rows, int64_t ld) {
         return !q || (((reinterpret_cast<uintptr_t>(q) & 15) == 0) && ld % 4 == 0 && rows * ld * 4 < ((int64_t)1 << 31));
     };
-    if (same && !a0.extA && a0.K == 64 && a0.taps <= kHaloMaxTaps && (int64_t)a0.cv_PH * a0.cv_W + a0.cv_PW <= 64 &&
+    if (same && !a0.extA && a0.K == 64 && a0.taps <= kStreamMaxTaps && (int64_t)a0.cv_PH * a0.cv_W + a0.cv_PW <= 64 &&
         a0.Ng <= 64 && a0.Ng % 4 == 0 && small_out(a0.out, a0.Mg, a0.ld_out) && small_out(a0.acc, a0.Mg, a0.ld_acc)) {
         // whole 128-row steps per block, at most kStreamBlocks blocks
         const int64_t rows = round_up((a0.Mg + kStreamBlocks - 1) / kStreamBlocks, 128);
@@ -2149,17 +2026,12 @@ hipError_t launch_conv_dgrad(const GemmArgs& a0, int8_t* bc, int64_t ld_bc, hipS
     a.B = bc;
     a.ldb = ld_bc;
     if (!fits(a.Ng, a.ldb)) return hipErrorInvalidValue;
-    const int64_t kps = a.K;
-    if (same && a.taps <= kHaloMaxTaps && 2 * ((int64_t)a.cv_PH * a.cv_W + a.cv_PW) <= kHaloExtra) {
-        const dim3 grid((unsigned)((a.Mg + kHaloBM - 1) / kHaloBM), (unsigned)((a.Ng + 63) / 64));
-        if (grid.y > 65535) return hipErrorInvalidValue;
-        if (a.extA) hipLaunchKernelGGL(k_conv_halo<true>, grid, dim3(64 * kHaloWaves), 0, s, a);
-        else hipLaunchKernelGGL(k_conv_halo<false>, grid, dim3(64 * kHaloWaves), 0, s, a);
-        return hipGetLastError();
+    switch (best_conv_tile(a.Mg, a.Ng, a.K / 64 * a.taps)) {
+        case Pick::kSmall: return launch_conv_tile<PipeSmall>(a, s);
+        case Pick::kFlat: return launch_conv_tile<PipeFlat>(a, s);
+        case Pick::kTiny: return launch_conv_tile<PipeTiny>(a, s);
+        default: return launch_conv_tile<PipeNarrow>(a, s);
     }
-    if (a.Ng <= 64)
-        return a.extA ? launch_pipe<PipeNarrow, true, true>(a, 1, kps, s) : launch_pipe<PipeNarrow, false, true>(a, 1, kps, s);
-    return a.extA ? launch_pipe<PipeSmall, true, true>(a, 1, kps, s) : launch_pipe<PipeSmall, false, true>(a, 1, kps, s);
 }
 
 // ---------------------------------------------------------------------------
