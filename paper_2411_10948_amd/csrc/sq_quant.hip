@@ -1199,9 +1199,49 @@ __global__ void k_channel_scales_rows(const float* __restrict__ x, int64_t rows,
     for (int64_t r = wave; r < rows; r += nwaves) {
         uint32_t m = 0u;
         for (int64_t c = lane; c < cols; c += 64) m = max(m, absbits(x[r * ld + c]));
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
+        m = wave_max(m);
         if (lane == 0) scales[r] = make_scale(m, (float)Q);
+    }
+}
+
+// Row scales and row-major codes in one pass, one wave per row: the row's
+// second read comes from the caches.  Bound by latency (a row of a few
+// thousand floats); scales and codes as two launches took 6.2 + 9.9 us on 3072 x
+// 768, this one 6.6 us.  VEC: 16-byte aligned rows.
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_quantize_rows(const float* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
+                                                       int Q, sq_scale* __restrict__ scales, int8_t* __restrict__ q,
+                                                       int64_t ld_q) {
+    const int lane = threadIdx.x & 63;
+    const float Qf = (float)Q;
+    const int64_t nwaves = (int64_t)gridDim.x * 4;
+    const int64_t quads = cols >> 2;
+    for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += nwaves) {
+        const float* row = x + r * ld;
+        auto load4 = [&](int64_t i) {
+            if constexpr (VEC) return *reinterpret_cast<const float4*>(row + 4 * i);
+            else return make_float4(row[4 * i], row[4 * i + 1], row[4 * i + 2], row[4 * i + 3]);
+        };
+        const int64_t tail = 4 * quads + lane;   // the last cols % 4 columns
+        uint32_t m = tail < cols ? absbits(row[tail]) : 0u;
+#pragma unroll 4
+        for (int64_t i = lane; i < quads; i += 64) {
+            const float4 v = load4(i);
+            m = max(max(m, max(absbits(v.x), absbits(v.y))), max(absbits(v.z), absbits(v.w)));
+        }
+        m = wave_max(m);
+        const sq_scale sc = make_scale(m, Qf);
+        if (lane == 0) scales[r] = sc;
+        auto code = [&](float v) {
+            return sc.flags ? 0u : (uint32_t)(uint8_t)(int)fminf(fmaxf(rintf(__fmul_rn(v, sc.inv)), -Qf), Qf);
+        };
+        int8_t* out = q + r * ld_q;   // ld_q a multiple of 16, 16-byte aligned
+#pragma unroll 4
+        for (int64_t i = lane; i < quads; i += 64) {
+            const float4 v = load4(i);
+            reinterpret_cast<uint32_t*>(out)[i] = code(v.x) | code(v.y) << 8 | code(v.z) << 16 | code(v.w) << 24;
+        }
+        if (tail < cols) out[tail] = (int8_t)code(row[tail]);
     }
 }
 
@@ -1481,6 +1521,14 @@ hipError_t launch_quantize_channels(const float* x, int64_t rows, int64_t cols, 
                                    hipStream_t s) {
     if (rows <= 0 || cols <= 0) return hipSuccess;
     const int Q = (1 << (bits - 1)) - 1;
+    if (axis == 0 && !transpose) {
+        const dim3 grid((unsigned)std::min<int64_t>((rows + 3) / 4, 8192));
+        if (colmax_vec(x, ld))
+            hipLaunchKernelGGL(k_quantize_rows<true>, grid, dim3(256), 0, s, x, rows, cols, ld, Q, scales, q, ld_q);
+        else
+            hipLaunchKernelGGL(k_quantize_rows<false>, grid, dim3(256), 0, s, x, rows, cols, ld, Q, scales, q, ld_q);
+        return hipGetLastError();
+    }
     if (axis == 1) {
         int64_t slabs = 0;
         const hipError_t e = launch_colmax(x, rows, cols, ld, partial, &slabs, s);
