@@ -11,9 +11,13 @@
 //                    k_final_groups over 64-channel groups and, with several
 //                    fold windows, k_final_place; k_colmax_reduce before them
 //                    for channel ranges that come from the producer of dY
-//   k_quantize       scale, round (ties-to-even or Philox stochastic rounding,
+//   quantize         scale, round (ties-to-even or Philox stochastic rounding,
 //                    App. B Eq. "sq"), clamp; writes the shift-folded dgrad
-//                    operand row-major and the codes transposed
+//                    operand row-major and the codes transposed: k_quantize8
+//                    (8 channels a thread), k_quantize_grid (transposed codes
+//                    on the padded pixel grid), k_quantize (any shape and
+//                    alignment); per tensor these also take the scale from the
+//                    abs-max pass's block maxima
 //
 // All fp32 arithmetic is IEEE with round-to-nearest-even and no contraction
 // (the library is built with -ffp-contract=off and the products below use the
