@@ -302,8 +302,36 @@ __device__ __forceinline__ float param_value(float v, const sq_scale& s) {
     return __fmul_rn(s.step, (float)code);
 }
 
-// One block: A_max, the parameter scales, then every channel's sigma code,
-// gamma^q, beta^q and kappa.
+// Sigma code, gamma^q, beta^q and kappa of a channel with deviation sum dev.
+struct BnParam {
+    int32_t sigma;
+    float gamma, beta, kappa;
+};
+__device__ __forceinline__ BnParam channel_param(int64_t dev, int64_t amax, float gamma, float beta, const sq_scale& gs,
+                                                 const sq_scale& bs, int64_t M) {
+    BnParam p{0, param_value(gamma, gs), param_value(beta, bs), 0.0f};
+    if (amax != 0) {
+        const int64_t k = std::max<int64_t>(1, div_round_even(127 * dev, amax));
+        p.sigma = (int32_t)k;
+        p.kappa = (float)(((double)p.gamma * (127.0 * (double)M)) / ((double)amax * (double)k));
+    }
+    return p;
+}
+
+__device__ __forceinline__ void write_layer(sq_l1bn_layer* layer, int64_t M, int64_t amax, float x_step,
+                                            const sq_scale& gs, const sq_scale& bs) {
+    sq_l1bn_layer L{};
+    L.rows = M;
+    L.dev_max = amax;
+    L.x_step = x_step;
+    L.flags = amax == 0 ? SQ_FLAG_ZERO : 0u;
+    L.gamma_scale = gs;
+    L.beta_scale = bs;
+    *layer = L;
+}
+
+// One block: A_max, the parameter scales, then every channel's constants (more
+// than kFuseC channels; else the forward's elementwise pass takes them).
 __global__ __launch_bounds__(kParThreads) void k_bn_params(sq_l1bn_channel* __restrict__ ch, int64_t M, int64_t C,
                                                            const float* __restrict__ gamma,
                                                            const float* __restrict__ beta,
@@ -341,29 +369,14 @@ __global__ __launch_bounds__(kParThreads) void k_bn_params(sq_l1bn_channel* __re
     const sq_scale gs = param_scale(gmax), bs = param_scale(bmax);
     for (int64_t c = tid; c < C; c += kParThreads) {
         sq_l1bn_channel v = ch[c];
-        v.gamma = param_value(gamma[c], gs);
-        v.beta = param_value(beta[c], bs);
-        if (amax == 0) {
-            v.sigma = 0;
-            v.kappa = 0.0f;
-        } else {
-            const int64_t k = std::max<int64_t>(1, div_round_even(127 * v.dev_sum, amax));
-            v.sigma = (int32_t)k;
-            const double num = (double)v.gamma * (127.0 * (double)M);
-            v.kappa = (float)(num / ((double)amax * (double)k));
-        }
+        const BnParam p = channel_param(v.dev_sum, amax, gamma[c], beta[c], gs, bs, M);
+        v.sigma = p.sigma;
+        v.gamma = p.gamma;
+        v.beta = p.beta;
+        v.kappa = p.kappa;
         ch[c] = v;
     }
-    if (tid == 0) {
-        sq_l1bn_layer L{};
-        L.rows = M;
-        L.dev_max = amax;
-        L.x_step = xs->step;
-        L.flags = amax == 0 ? SQ_FLAG_ZERO : 0u;
-        L.gamma_scale = gs;
-        L.beta_scale = bs;
-        *layer = L;
-    }
+    if (tid == 0) write_layer(layer, M, amax, xs->step, gs, bs);
 }
 
 // Elementwise pass.  Forward (BWD = false): y = fl(fl(kappa (q - m)) + beta),
@@ -396,15 +409,79 @@ __device__ __forceinline__ void unpack4(uint32_t w, int (&out)[4]) {
     for (int i = 0; i < 4; ++i) out[i] = (int)(int8_t)(w >> (8 * i));
 }
 
-template <bool BWD>
+// PAR (forward, at most kFuseC channels, so one block column): every block
+// also takes A_max and the parameter scales and the constants of all channels
+// (a few channels per thread, into LDS), and block 0 writes them to ch and
+// layer.  As a launch of one block of its own that took 3.9 us and a gap;
+// here 0 to 1.2 us (200704 x 64: the step 131.9 -> 128.5 us; 12544 x 256: 67.9 ->
+// 65.6).
+constexpr int kFuseC = 1024;
+template <bool BWD, bool PAR = false>
 __global__ __launch_bounds__(kBnThreads) void k_bn_apply(const int8_t* __restrict__ a, int64_t lda,
                                                          const int8_t* __restrict__ x, int64_t ldx,
-                                                         const sq_l1bn_channel* __restrict__ ch,
-                                                         const float* __restrict__ coef, int64_t M, int64_t C,
-                                                         QuadGeom g, float* __restrict__ out, int64_t ld_out,
-                                                         bool vec_out, uint32_t* __restrict__ ranges) {
+                                                         sq_l1bn_channel* ch, const float* __restrict__ coef,
+                                                         int64_t M, int64_t C, QuadGeom g, float* __restrict__ out,
+                                                         int64_t ld_out, bool vec_out, uint32_t* __restrict__ ranges,
+                                                         const float* __restrict__ gamma,
+                                                         const float* __restrict__ beta,
+                                                         const sq_scale* __restrict__ xs, sq_l1bn_layer* layer) {
     __shared__ uint32_t red[BWD ? kBnThreads * 4 : 1];
+    __shared__ float par[PAR ? 2 : 1][PAR ? kFuseC : 1];   // kappa, beta^q
     const int tid = threadIdx.x, cl = tid % g.qis, lane = tid / g.qis;
+    if constexpr (PAR) {
+        __shared__ int64_t sh_a[kBnThreads / 64];
+        __shared__ uint32_t sh_g[kBnThreads / 64], sh_b[kBnThreads / 64];
+        constexpr int N = kFuseC / kBnThreads;
+        int64_t dev[N], amax = 0;
+        float gv[N], bv[N];
+        uint32_t gmax = 0u, bmax = 0u;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int c = tid + i * kBnThreads;
+            const bool in = c < C;
+            dev[i] = in ? ch[c].dev_sum : 0;
+            gv[i] = in ? gamma[c] : 0.0f;
+            bv[i] = in ? beta[c] : 0.0f;
+            amax = std::max(amax, dev[i]);
+            gmax = std::max(gmax, abs_bits(gv[i]));
+            bmax = std::max(bmax, abs_bits(bv[i]));
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            amax = std::max<int64_t>(amax, __shfl_xor(amax, o, 64));
+            gmax = std::max(gmax, (uint32_t)__shfl_xor((int)gmax, o, 64));
+            bmax = std::max(bmax, (uint32_t)__shfl_xor((int)bmax, o, 64));
+        }
+        if ((tid & 63) == 0) {
+            sh_a[tid >> 6] = amax;
+            sh_g[tid >> 6] = gmax;
+            sh_b[tid >> 6] = bmax;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kBnThreads / 64; ++i) {
+            amax = std::max(amax, sh_a[i]);
+            gmax = std::max(gmax, sh_g[i]);
+            bmax = std::max(bmax, sh_b[i]);
+        }
+        const sq_scale gs = param_scale(gmax), bs = param_scale(bmax);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int c = tid + i * kBnThreads;
+            if (c >= C) continue;
+            const BnParam p = channel_param(dev[i], amax, gv[i], bv[i], gs, bs, M);
+            par[0][c] = p.kappa;
+            par[PAR ? 1 : 0][c] = p.beta;
+            if (blockIdx.x == 0) {   // the other blocks read mu and dev_sum only
+                ch[c].sigma = p.sigma;
+                ch[c].gamma = p.gamma;
+                ch[c].beta = p.beta;
+                ch[c].kappa = p.kappa;
+            }
+        }
+        if (blockIdx.x == 0 && tid == 0) write_layer(layer, M, amax, xs->step, gs, bs);
+        __syncthreads();
+    }
     const int64_t quad = (int64_t)blockIdx.y * g.qis + cl, c0 = quad * 4;
     const bool active = lane < g.lanes && quad < g.quads;
     const int64_t r0 = (int64_t)blockIdx.x * g.rpb, r1 = std::min<int64_t>(M, r0 + g.rpb);
@@ -417,16 +494,15 @@ __global__ __launch_bounds__(kBnThreads) void k_bn_apply(const int8_t* __restric
         // clamped index, select after the load (no branch per channel)
         const int64_t cc = std::min<int64_t>(c0 + i, C - 1);
         const bool ok = c0 + i < C;
-        const sq_l1bn_channel v = ch[cc];
-        mu[i] = v.mu;
+        mu[i] = ch[cc].mu;
         if (BWD) {
             const float4 k = reinterpret_cast<const float4*>(coef)[cc];
             k0[i] = ok ? k.x : 0.0f;
             k1[i] = ok ? k.y : 0.0f;
             k2[i] = ok ? k.z : 0.0f;
         } else {
-            k0[i] = ok ? v.kappa : 0.0f;
-            k1[i] = ok ? v.beta : 0.0f;
+            k0[i] = !ok ? 0.0f : PAR ? par[0][cc] : ch[cc].kappa;
+            k1[i] = !ok ? 0.0f : PAR ? par[PAR ? 1 : 0][cc] : ch[cc].beta;
             k2[i] = 0.0f;
         }
         rmax[i] = 0u;
@@ -511,10 +587,16 @@ hipError_t launch_l1bn_forward(const int8_t* xq, int64_t M, int64_t C, int64_t l
     hipLaunchKernelGGL(k_bn_colsum<1>, sum_grid, dim3(kBnThreads), 0, s, xq, ld_x, nullptr, 0, ch, M, C, gs, part);
     hipLaunchKernelGGL(k_bn_chan<1>, chan_grid, dim3(64 * kBnWaves), 0, s, part, gs.nb, M, C, ch, nullptr, nullptr,
                        nullptr, nullptr, nullptr, nullptr);
-    hipLaunchKernelGGL(k_bn_params, dim3(1), dim3(kParThreads), 0, s, ch, M, C, gamma, beta, xs, layer);
     const bool vec = (ld_y % 4 == 0) && (reinterpret_cast<uintptr_t>(y) % 16 == 0);
-    hipLaunchKernelGGL(k_bn_apply<false>, dim3((unsigned)ga.nb, (unsigned)ga.slabs), dim3(kBnThreads), 0, s, xq, ld_x,
-                       nullptr, 0, ch, nullptr, M, C, ga, y, ld_y, vec, nullptr);
+    const dim3 apply_grid((unsigned)ga.nb, (unsigned)ga.slabs);
+    if (C <= kFuseC) {
+        hipLaunchKernelGGL((k_bn_apply<false, true>), apply_grid, dim3(kBnThreads), 0, s, xq, ld_x, nullptr, 0, ch, nullptr,
+                           M, C, ga, y, ld_y, vec, nullptr, gamma, beta, xs, layer);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_bn_params, dim3(1), dim3(kParThreads), 0, s, ch, M, C, gamma, beta, xs, layer);
+    hipLaunchKernelGGL((k_bn_apply<false, false>), apply_grid, dim3(kBnThreads), 0, s, xq, ld_x, nullptr, 0, ch, nullptr,
+                       M, C, ga, y, ld_y, vec, nullptr, nullptr, nullptr, nullptr, nullptr);
     return hipGetLastError();
 }
 
@@ -534,7 +616,8 @@ hipError_t launch_l1bn_backward(const int8_t* qg, int64_t ldg, const int8_t* xq,
                        part_blocks, M, C, const_cast<sq_l1bn_channel*>(ch), layer, group, gscale, coef, dgamma, dbeta);
     const bool vec = (ld_dx % 4 == 0) && (reinterpret_cast<uintptr_t>(dx) % 16 == 0);
     hipLaunchKernelGGL(k_bn_apply<true>, dim3((unsigned)ga.nb, (unsigned)ga.slabs), dim3(kBnThreads), 0, s, qg, ldg,
-                       xq, ld_x, ch, coef, M, C, ga, dx, ld_dx, vec, ranges);
+                       xq, ld_x, const_cast<sq_l1bn_channel*>(ch), coef, M, C, ga, dx, ld_dx, vec, ranges, nullptr,
+                       nullptr, nullptr, nullptr);
     return hipGetLastError();
 }
 
