@@ -21,7 +21,7 @@
 // 256 / (C / 16) rows are in flight per block and each block takes a
 // contiguous range of rows, so every load is a coalesced row segment.  A
 // block reduces its rows in LDS and writes one partial per channel; a second
-// kernel (one wave per channel) adds the partials.  Block partials are int32:
+// kernel (16 channels per block) adds the partials.  Block partials are int32:
 // with M <= 2^24 and at most 512 row blocks a block holds at most 32768 rows,
 // and |qg (q - m)| <= 127 * 254.
 
@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kBnThreads) void k_bn_colsum(const int8_t* __restri
 // kChanPer = 16 consecutive channels, 64 partial rows at a time (a wave reads
 // 4 rows of 64 bytes, 8 loads in flight per thread); lanes of a channel add up
 // by shuffles, waves in LDS.  Bound by latency; with 64 channels per block (one
-// block for the 64-channel layer, 512 partial rows) MEASURED_CHAN.
+// block for the 64-channel layer, 512 partial rows) 8.8 us, so 3.8 to 5.4.
 //   OP 0: mean code.  OP 1: deviation and sign sums.
 //   OP 2: backward constants (a, b, e), dgamma, dbeta.
 constexpr int kChanPer = 16;

@@ -1082,7 +1082,8 @@ __global__ __launch_bounds__(kBlock) void k_quantize_grid(const float* __restric
 // rows, 256 at a time: quant8 leaves a thread the codes of 4 rows of a channel
 // in one word, so with x moved to the same order (byte permutes) each channel's
 // products are one 4-way dot.  Bound by memory (4 + 1 B read, 1 B written per
-// element).  As a quantize pass and a pass over both codes: MEASURED_BNQ.
+// element).  200704 x 64: 17.4 us; as a quantize pass and
+// a pass over both codes 13.8 + 10.2 us.
 constexpr int kBnQThreads = 512, kBnQRows = kBnQThreads / 8 * 4;
 
 // bytes of 4 row words (columns 0 .. 3 each) to 4 column words (rows 0 .. 3 each)
