@@ -256,11 +256,7 @@ sq_status sq_gemm_wgrad_workspace_size(int64_t M, int64_t C_out, int64_t C_in, c
     SQ_TRY(check_dims(M, C_out, "gradient"));
     SQ_TRY(check_dims(C_in, C_in, "activation"));
     if (!bytes) return fail(SQ_ERR_INVALID_ARGUMENT, "bytes is NULL");
-    // a product always reports some workspace, whether this version splits it
-    // or not; sq_gemm_wgrad asks for what it uses
-    *bytes = 0;
-    if (M > 0 && C_out > 0 && C_in > 0)
-        *bytes = std::max<size_t>(256, wgrad_ws_bytes(wgrad_splits(M, C_out, C_in), C_out, C_in));
+    *bytes = M > 0 && C_out > 0 && C_in > 0 ? wgrad_ws_bytes(wgrad_splits(M, C_out, C_in), C_out, C_in) : 0;
     return SQ_OK;
 }
 

@@ -71,6 +71,14 @@ def test_size_queries(sq):
     assert sq.sq_quantize_tensor_workspace_size(10, 3) == 256
 
 
+@pytest.mark.parametrize("M,C_out,C_in,splits", [(256, 1000, 2048, 1), (4096, 1024, 2048, 1), (64, 64, 64, 1), (0, 64, 64, 1),
+                                                 (16384, 3072, 768, 5), (12040, 1280, 1344, 2)])
+def test_wgrad_workspace_is_the_split_partials(sq, M, C_out, C_in, splits):
+    # nothing for a product that is not split (so a test can tell the two apart)
+    need = splits * C_out * C_in * 4 if splits > 1 else 0
+    assert sq.sq_gemm_wgrad_workspace_size(M, C_out, C_in, _params(sq)) == (need + 255) // 256 * 256
+
+
 def _raw(sq):
     return sq.load()
 
