@@ -1304,15 +1304,6 @@ hipError_t launch_pipe(const GemmArgs& a, int splits, int64_t k_per_split, hipSt
     return hipGetLastError();
 }
 
-// One tile shape: with the fold's shifts or without, K whole tiles or not.
-template <class T>
-hipError_t launch_tile(const GemmArgs& a, int splits, int64_t k_per_split, hipStream_t s) {
-    if (a.K % T::BK)
-        return a.extA ? launch_pipe<T, true, false, false, true>(a, splits, k_per_split, s)
-                      : launch_pipe<T, false, false, false, true>(a, splits, k_per_split, s);
-    return a.extA ? launch_pipe<T, true>(a, splits, k_per_split, s) : launch_pipe<T, false>(a, splits, k_per_split, s);
-}
-
 // The direct-load pipeline needs 16-byte aligned rows and byte offsets (rows *
 // ld + K) that fit the 31 bits of its buffer loads.
 bool pipe_ok(const GemmArgs& a) {
@@ -1416,6 +1407,32 @@ Pick best_conv_tile(int64_t Mg, int64_t Ng, int64_t ktiles) {
     return kPicks[best];
 }
 
+// One tile shape: with the fold's shifts or without, K whole tiles or not.
+// RANGES (K whole tiles): with the channel maxima of the output.
+template <class T, bool RANGES = false>
+hipError_t launch_tile(const GemmArgs& a, int splits, int64_t k_per_split, hipStream_t s) {
+    if constexpr (!RANGES) {
+        if (a.K % T::BK)
+            return a.extA ? launch_pipe<T, true, false, false, true>(a, splits, k_per_split, s)
+                          : launch_pipe<T, false, false, false, true>(a, splits, k_per_split, s);
+    }
+    return a.extA ? launch_pipe<T, true, false, RANGES>(a, splits, k_per_split, s)
+                  : launch_pipe<T, false, false, RANGES>(a, splits, k_per_split, s);
+}
+
+template <bool RANGES = false>
+hipError_t launch_pick(Pick p, const GemmArgs& a, int splits, int64_t k_per_split, hipStream_t s) {
+    switch (p) {
+        case Pick::kLarge: return launch_tile<PipeLarge, RANGES>(a, splits, k_per_split, s);
+        case Pick::kTall: return launch_tile<PipeTall, RANGES>(a, splits, k_per_split, s);
+        case Pick::kDuo: return launch_tile<PipeDuo, RANGES>(a, splits, k_per_split, s);
+        case Pick::kMid: return launch_tile<PipeMid, RANGES>(a, splits, k_per_split, s);
+        case Pick::kSmall: return launch_tile<PipeSmall, RANGES>(a, splits, k_per_split, s);
+        case Pick::kFlat: return launch_tile<PipeFlat, RANGES>(a, splits, k_per_split, s);
+        default: return launch_tile<PipeTiny, RANGES>(a, splits, k_per_split, s);
+    }
+}
+
 template <class T>
 hipError_t launch_conv_tile(const GemmArgs& a, hipStream_t s) {
     return a.extA ? launch_pipe<T, true, true>(a, 1, a.K, s) : launch_pipe<T, false, true>(a, 1, a.K, s);
@@ -1483,6 +1500,17 @@ int wgrad_splits(int64_t M, int64_t C_out, int64_t C_in) {
     return best;
 }
 
+// What launch_gemm runs for a product of the pipelined kernel, for tests that
+// pin a tile (not part of the public header): the tile's rows and columns, and
+// the rows of the first of two launches (0: one launch).
+extern "C" void sq_internal_gemm_plan(int64_t Mg, int64_t Ng, int64_t K, int32_t splits, int32_t* bm, int32_t* bn,
+                                      int64_t* first_rows) {
+    const TileCost& c = kTileCost[(int)best_tile(Mg, Ng, K, std::max(1, splits))];
+    *bm = c.bm;
+    *bn = c.bn;
+    *first_rows = splits > 1 ? 0 : large_rows(Mg, Ng, K);
+}
+
 namespace {
 // The product restricted to output rows [r0, Mg) (r0 a multiple of 256):
 // every row-indexed pointer moves to row r0.
@@ -1525,27 +1553,12 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     if (a.ranges) {
         // dX with its channel maxima (producer-side ranges): pipelined kernel, no split
         if (!pipe || a.K % 64 || splits > 1 || !a.out || a.part) return hipErrorInvalidValue;
-        if (p == Pick::kLarge || p == Pick::kTall || p == Pick::kDuo)
-            return a.extA ? launch_pipe<PipeLarge, true, false, true>(a, 1, per * 64, s)
-                          : launch_pipe<PipeLarge, false, false, true>(a, 1, per * 64, s);
-        if (p == Pick::kMid)
-            return a.extA ? launch_pipe<PipeMid, true, false, true>(a, 1, per * 64, s)
-                          : launch_pipe<PipeMid, false, false, true>(a, 1, per * 64, s);
-        return a.extA ? launch_pipe<PipeSmall, true, false, true>(a, 1, per * 64, s)
-                      : launch_pipe<PipeSmall, false, false, true>(a, 1, per * 64, s);
+        return launch_pick<true>(p, a, 1, per * 64, s);
     }
     if (!pipe)
         return p == Pick::kLarge ? launch_cfg<CfgLarge>(a, splits, per * 64, s)
                                  : launch_cfg<CfgSmall>(a, splits, per * 64, s);
-    switch (p) {
-        case Pick::kLarge: return launch_tile<PipeLarge>(a, splits, per * 64, s);
-        case Pick::kTall: return launch_tile<PipeTall>(a, splits, per * 64, s);
-        case Pick::kDuo: return launch_tile<PipeDuo>(a, splits, per * 64, s);
-        case Pick::kMid: return launch_tile<PipeMid>(a, splits, per * 64, s);
-        case Pick::kSmall: return launch_tile<PipeSmall>(a, splits, per * 64, s);
-        case Pick::kFlat: return launch_tile<PipeFlat>(a, splits, per * 64, s);
-        default: return launch_tile<PipeTiny>(a, splits, per * 64, s);
-    }
+    return launch_pick(p, a, splits, per * 64, s);
 }
 
 // Padded pixel grids of the conv wgrad: a thread writes one aligned 16-byte

@@ -71,6 +71,13 @@ def test_size_queries(sq):
     assert sq.sq_quantize_tensor_workspace_size(10, 3) == 256
 
 
+def test_mlp_input_gradient_plan(sq):
+    # 16384 x 768 outputs, K = 3072: 256 tiles of 128 x 384, where 192 of
+    # 256 x 256 would leave a quarter of the CUs idle (with and without ranges)
+    from tests.gemm_plan import gemm_plan
+    assert gemm_plan(sq, 16384, 768, 3072) == (128, 384, 0)
+
+
 @pytest.mark.parametrize("M,C_out,C_in,splits", [(256, 1000, 2048, 1), (4096, 1024, 2048, 1), (64, 64, 64, 1), (0, 64, 64, 1),
                                                  (16384, 3072, 768, 5), (12040, 1280, 1344, 2)])
 def test_wgrad_workspace_is_the_split_partials(sq, M, C_out, C_in, splits):

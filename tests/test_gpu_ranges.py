@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
+from tests.gemm_plan import gemm_plan
 from tests.test_gpu_parity import _dev, _grad, check_quant
 
 pytestmark = pytest.mark.gpu
@@ -22,14 +23,14 @@ def sq():
     return shiftquant
 
 
-RANGE_CASES = [  # M, C_out, C_in, bits, N_G  (tile: large / small / skinny, fold windows)
+RANGE_CASES = [  # M, C_out, C_in, bits, N_G
     (1000, 256, 1024, 4, 4),
     (777, 300, 200, 6, 4),      # appended fold windows, ragged M and C
-    (40, 128, 96, 4, 4),        # a single row tile of the skinny kind
-    (4099, 768, 3072, 6, 4),    # the MLP chain's down-projection, large tiles
+    (40, 128, 96, 4, 4),        # a single row tile
+    (4099, 768, 3072, 6, 4),    # the MLP chain's down-projection
     (65, 64, 48, 8, 3),
-    (8000, 1024, 1536, 6, 4),   # 128 x 384 tiles (192 large tiles would leave CUs idle), fold windows
-    (8000 - 40, 1024, 1536, 4, 4),   # the same tiles, one window, ragged rows
+    (8000, 1024, 1536, 6, 4),   # fold windows
+    (8000 - 40, 1024, 1536, 4, 4),   # one window, ragged rows
 ]
 
 
@@ -72,3 +73,40 @@ def test_dgrad_ranges(sq, case):
     for name in ("q_fold", "q_t", "group", "layout"):
         assert torch.equal(getattr(a, name), getattr(b, name)), name
     assert torch.equal(a.scale, b.scale)
+
+
+RANGE_TILES = [  # M, C_out, C_in: every tile shape, ragged rows and columns
+    (65, 1152, 70, (64, 64)),
+    (65, 320, 65, (64, 128)),
+    (9890, 320, 537, (128, 128)),
+    (5555, 256, 1793, (128, 192)),
+    (11207, 704, 657, (128, 384)),
+    (9795, 256, 1283, (256, 128)),
+    (9830, 3392, 1173, (256, 256)),
+]
+
+
+# the ranged product runs the tile that its plan prices, with and without fold
+# windows: dX as the plain product's, the maxima those of the stored dX
+@pytest.mark.parametrize("M,C_out,C_in,tile", RANGE_TILES)
+@pytest.mark.parametrize("bits", [4, 8])
+def test_dgrad_ranges_every_tile(sq, M, C_out, C_in, tile, bits):
+    import torch
+    print(f"dgrad ranges tile M={M} C_out={C_out} C_in={C_in} b={bits}", flush=True)
+    assert gemm_plan(sq, M, C_in, C_out)[:2] == tile
+    g = torch.Generator(device="cuda").manual_seed(M + bits)
+    dY = torch.randn(M, C_out, generator=g, device="cuda") * torch.exp2(-6 * torch.rand(C_out, generator=g, device="cuda"))
+    c = sq.quantize_grad(dY, bits, 4)
+    wq_t, ws = sq.quantize_tensor(torch.randn(C_out, C_in, generator=g, device="cuda"), 8)
+    _, ref = sq.gemm_dgrad(c, wq_t, ws)
+    slabs = sq.sq_gemm_dgrad_range_slabs(M)
+    dX = torch.full((M, C_in), float("nan"), device="cuda")
+    ranges = torch.full((slabs + 1, C_in), -1, dtype=torch.int32, device="cuda")
+    w = torch.empty(max(256, sq.sq_gemm_dgrad_workspace_size(M, C_out, C_in, c.params)), dtype=torch.uint8, device="cuda")
+    sq.sq_gemm_dgrad_ranged(c.q_fold, c.layout, c.group, c.scale, wq_t, ws, M, C_out, C_in, c.params, None, dX, ranges, w)
+    torch.cuda.synchronize()
+    assert torch.equal(dX, ref)
+    top = torch.zeros(slabs * 32, C_in, device="cuda")
+    top[:M] = dX.abs()
+    assert torch.equal(ranges[:slabs].view(torch.float32), top.view(slabs, 32, C_in).amax(1))
+    assert bool((ranges[slabs] == -1).all())
