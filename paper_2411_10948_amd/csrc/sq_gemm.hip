@@ -1479,21 +1479,29 @@ hipError_t launch_slab_colmax(const float* x, int64_t M, int64_t N, int64_t ld, 
 }
 
 // Split-K factor of the weight-gradient product, at least 4 K tiles per split
-// and none empty.
+// and none empty.  More than 64 only where 64 splits of the smallest tiles
+// leave CUs idle (narrow layers, long token dimensions): 1003520 x 16 x 16
+// 51.7 us at 64 splits, 21.5 at up to 256; 401408 x 32 x 32 25.3, 14.8;
+// 200704 x 64 x 64 16.5, 14.5.  Beyond a block per CU the partials cost what
+// the splits give (200704 x 64 x 256: 20.8 us at 64, 22.2 at 192), and rows
+// that are no multiple of 4 outputs have their partials written and summed one
+// by one, 0.03 us a split (100000 x 64 x 10: 14.9 us at 128, 17.2 at 256).
 int wgrad_splits(int64_t M, int64_t C_out, int64_t C_in) {
     const int64_t ktiles = (M + 63) / 64;
-    static const int kTry[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32, 48, 64};
+    static const int kTry[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32, 48, 64, 96, 128, 192, 256};
     const double mb = 4e-6 * (double)C_out * (double)C_in;
     double tiles[kTiles];
     for (int i = 0; i < kTiles; ++i) tiles[i] = tiles_of(i, C_out, C_in);
     int best = 1;
     float t = 0.0f;
     for (const int want : kTry) {
+        if (want > 64 && 64.0 * tiles[(int)Pick::kTiny] >= (double)kCUs) break;
         if (want > 1 && (4 * (int64_t)want > ktiles || split_cost(mb, want) >= t)) break;
         const int64_t per = (ktiles + want - 1) / want;
         const int s = per > 0 ? (int)((ktiles + per - 1) / per) : 1;
+        const float narrow = want > 64 && C_in % 4 ? 0.03f * (float)(s - 64) : 0.0f;
         for (int i = 0; i < kTiles; ++i) {
-            const float ts = tile_cost(kTileCost[i], tiles[i], mb, ktiles, s);
+            const float ts = tile_cost(kTileCost[i], tiles[i], mb, ktiles, s) + narrow;
             if ((want == 1 && i == 0) || ts < t) { best = s; t = ts; }
         }
     }

@@ -79,7 +79,10 @@ def test_mlp_input_gradient_plan(sq):
 
 
 @pytest.mark.parametrize("M,C_out,C_in,splits", [(256, 1000, 2048, 1), (4096, 1024, 2048, 1), (64, 64, 64, 1), (0, 64, 64, 1),
-                                                 (16384, 3072, 768, 5), (12040, 1280, 1344, 2)])
+                                                 (16384, 3072, 768, 5), (12040, 1280, 1344, 2),
+                                                 # one or two tiles: enough splits for a block on every CU
+                                                 (1003520, 16, 16, 253), (200704, 64, 64, 242), (262144, 128, 64, 256),
+                                                 (200704, 64, 256, 64), (100000, 64, 10, 121), (50000, 16, 17, 87)])
 def test_wgrad_workspace_is_the_split_partials(sq, M, C_out, C_in, splits):
     # nothing for a product that is not split (so a test can tell the two apart)
     need = splits * C_out * C_in * 4 if splits > 1 else 0

@@ -475,10 +475,12 @@ def test_wgrad_large_tiles_split_k(sq, shape):
     check_layer(sq, dY, W, X, 6, 4, dgrad_rows=[2, M - 2], wgrad_rows=[3, C_out - 2], want_acc=False)
 
 
-@pytest.mark.parametrize("shape", [(4096, 40, 200), (8192, 64, 197), (2048, 1, 64), (16384, 64, 576)])
+@pytest.mark.parametrize("shape", [(4096, 40, 200), (8192, 64, 197), (2048, 1, 64), (16384, 64, 576),
+                                   (50000, 16, 17), (70001, 33, 40), (100001, 3, 64)])
 def test_wgrad_narrow_outputs(sq, shape):
     # at most 64 output rows and a token count that is a multiple of 64: the
-    # 64-row tile with split-K, and the reduce with and without 4-aligned rows
+    # 64-row tile with split-K, and the reduce with and without 4-aligned rows;
+    # the last three take more than 64 splits (87, 219 and 224)
     M, C_out, C_in = shape
     rng = np.random.default_rng(C_in)
     dY = _grad(M, C_out, seed=C_out)
