@@ -23,6 +23,7 @@
 // (the library is built with -ffp-contract=off and the products below use the
 // _rn intrinsics), so the codes are a bit-exact function of the inputs.
 #include <algorithm>
+#include <type_traits>
 
 #include "sq_internal.h"
 
@@ -226,53 +227,100 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 }
 
 // ---------------------------------------------------------------------------
-// Second level of the abs-max.  A block of 16 waves takes kFinCh = 64
-// consecutive channels, one per lane: wave w reads the slab maxima of slabs w,
-// w + 16, ... (coalesced 256-byte row segments, 8 in flight) and the waves
-// combine in LDS.  The result is valid in wave 0.
+// Second level of the abs-max.  A block of NW waves takes kFinCh = 64
+// consecutive channels and reads its slab maxima (slabs s0 <= s < s1) with 8
+// loads in flight per thread: four rows of 64 channels per wave and 16-byte
+// load where the rows are aligned, else one row per wave (a 256-byte segment,
+// a channel per lane).  The waves combine in LDS; the result is valid in wave
+// 0, lane c holding channel c.  NW = 0, for many channels in at most 8 slabs:
+// every wave of the block takes 64 channels of its own and all of their slabs.
 // ---------------------------------------------------------------------------
-constexpr int kFinCh = 64, kFinWaves = 16, kFinThreads = 64 * kFinWaves;
+constexpr int kFinCh = 64, kFinWaves = 16, kWideWaves = 4;
+template <int NW>
+constexpr int kFinThreadsOf = 64 * (NW ? NW : kWideWaves);
 
-__device__ __forceinline__ uint32_t slab_max64(const uint32_t* partial, int64_t S, int64_t C,
+// the 64-channel group of this thread's wave
+template <int NW>
+__device__ __forceinline__ int64_t fin_group() {
+    return NW ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kWideWaves + (threadIdx.x >> 6);
+}
+
+__device__ __forceinline__ uint4 max4(const uint4& a, const uint4& b) {
+    return make_uint4(max(a.x, b.x), max(a.y, b.y), max(a.z, b.z), max(a.w, b.w));
+}
+
+template <int NW>
+__device__ __forceinline__ uint32_t slab_max64(const uint32_t* partial, int64_t s0, int64_t s1, int64_t C,
                                                uint32_t (*lanes)[kFinCh]) {
     const int ch = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int64_t c = (int64_t)blockIdx.x * kFinCh + ch;
-    uint32_t a[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-    if (c < C) {
-        int64_t sl = w;
-        for (; sl + 7 * kFinWaves < S; sl += 8 * kFinWaves) {
+    const int64_t c = fin_group<NW>() * kFinCh + ch;
+    constexpr int U = 8;
+    // the rows past the last slab are clamped to it, so the loads issue back
+    // to back (a maximum does not mind a repeated row)
+    if (NW && (C & 3) == 0 && (reinterpret_cast<uintptr_t>(partial) & 15) == 0) {
+        constexpr int step = 4 * (NW ? NW : 1);
+        const int q = threadIdx.x & 15;
+        const int64_t cq = fin_group<NW>() * kFinCh + 4 * q;
+        uint4 r = make_uint4(0u, 0u, 0u, 0u);
+        if (cq < C) {
+            for (int64_t sl = s0 + (threadIdx.x >> 4); sl < s1; sl += U * step) {
+                uint4 v[U];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = max(a[u], partial[(sl + u * kFinWaves) * C + c]);
-        }
-        // rest: the row index clamped to the last slab, so the loads issue
-        // back to back (a maximum does not mind a repeated row)
-        if (sl < S) {
+                for (int u = 0; u < U; ++u)
+                    v[u] = *reinterpret_cast<const uint4*>(partial + min(sl + u * step, s1 - 1) * C + cq);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = max(a[u], partial[min(sl + u * kFinWaves, S - 1) * C + c]);
+                for (int u = 0; u < U; ++u) r = max4(r, v[u]);
+            }
         }
+#pragma unroll
+        for (int o = 16; o < 64; o <<= 1)
+            r = max4(r, make_uint4((uint32_t)__shfl_xor((int)r.x, o, 64), (uint32_t)__shfl_xor((int)r.y, o, 64),
+                                   (uint32_t)__shfl_xor((int)r.z, o, 64), (uint32_t)__shfl_xor((int)r.w, o, 64)));
+        if (ch < 16) *reinterpret_cast<uint4*>(&lanes[w][4 * q]) = r;
+    } else {
+        constexpr int step = NW ? NW : 1;
+        uint32_t r = 0u;
+        if (c < C) {
+            uint32_t v[U] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
+            int64_t sl = s0 + (NW ? w : 0);
+            for (; sl + (U - 1) * step < s1; sl += U * step) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = max(v[u], partial[(sl + u * step) * C + c]);
+            }
+            if (sl < s1) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) v[u] = max(v[u], partial[min(sl + u * step, s1 - 1) * C + c]);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) r = max(r, v[u]);
+        }
+        if constexpr (NW == 0) return r;
+        lanes[w][ch] = r;
     }
-    lanes[w][ch] = max(max(max(a[0], a[1]), max(a[2], a[3])), max(max(a[4], a[5]), max(a[6], a[7])));
     __syncthreads();
     uint32_t r = 0u;
     if (w == 0) {
 #pragma unroll
-        for (int i = 0; i < kFinWaves; ++i) r = max(r, lanes[i][ch]);
+        for (int i = 0; i < NW; ++i) r = max(r, lanes[i][ch]);
     }
     return r;
 }
 
-// Channel ranges rbits[c] and each block's maximum bmax[blockIdx.x], for slab
+// Channel ranges over the slabs [y per, (y + 1) per), y = blockIdx.y, in
+// rbits[y][c], and the maximum of each 64 channels in bmax[y][group], for slab
 // maxima that come from the producer of dY (no block maxima with them).
-__global__ __launch_bounds__(kFinThreads) void k_colmax_reduce(const uint32_t* __restrict__ partial, int64_t S,
-                                                               int64_t C, uint32_t* __restrict__ rbits,
-                                                               uint32_t* __restrict__ bmax) {
-    __shared__ uint32_t lanes[kFinWaves][kFinCh];
-    uint32_t r = slab_max64(partial, S, C, lanes);
-    if (threadIdx.x >= 64) return;
-    const int64_t c = (int64_t)blockIdx.x * kFinCh + threadIdx.x;
-    if (c < C) rbits[c] = r;
+template <int NW>
+__global__ __launch_bounds__(kFinThreadsOf<NW>) void k_colmax_reduce(const uint32_t* __restrict__ partial, int64_t S,
+                                                               int64_t per, int64_t C, uint32_t* __restrict__ rbits,
+                                                               uint32_t* __restrict__ bmax, int64_t nb) {
+    __shared__ __attribute__((aligned(16))) uint32_t lanes[NW ? NW : 1][kFinCh];
+    const int64_t y = blockIdx.y, grp = fin_group<NW>();
+    uint32_t r = slab_max64<NW>(partial, y * per, min(S, (y + 1) * per), C, lanes);
+    if (NW ? threadIdx.x >= 64 : grp >= nb) return;
+    const int64_t c = grp * kFinCh + (threadIdx.x & 63);
+    if (c < C) rbits[y * C + c] = r;
     r = wave_max(r);
-    if (threadIdx.x == 0) bmax[blockIdx.x] = r;
+    if ((threadIdx.x & 63) == 0) bmax[y * nb + grp] = r;
 }
 
 // Group of a channel: the smallest j < N_G - 1 with r_c * 2^(j+1) > r_max,
@@ -315,29 +363,40 @@ __device__ __forceinline__ sq_scale make_scale(uint32_t mb, float Qf) {
 // 22 us (several windows, 768 channels x 169 slabs); these two take
 // 9.4 us (16384 x 768 activations: finalize 21.9 -> 9.4 us).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kFinThreads) void k_final_groups(const uint32_t* partial, int64_t S,
-                                                              const uint32_t* __restrict__ block_max, int64_t nbm,
+template <int NW>
+__global__ __launch_bounds__(kFinThreadsOf<NW>) void k_final_groups(const uint32_t* partial, int64_t S,
+                                                              const uint32_t* block_max, int64_t nbm,
                                                               int64_t C, QuantCfg cfg, uint8_t* __restrict__ group,
                                                               sq_scale* __restrict__ scale,
                                                               int32_t* __restrict__ layout, int64_t ext_max,
                                                               int32_t* hist, int hist_ld) {
-    __shared__ uint32_t lanes[kFinWaves][kFinCh];
-    __shared__ uint32_t wmax[kFinWaves];
+    constexpr int nt = kFinThreadsOf<NW>;
+    __shared__ __attribute__((aligned(16))) uint32_t lanes[NW ? NW : 1][kFinCh];
+    __shared__ uint32_t wmax[nt / 64];
     const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t grp = fin_group<NW>();
     uint32_t mb = 0u;
     if (gridDim.x > 1) {
-        for (int64_t i = tid; i < nbm; i += kFinThreads) mb = max(mb, block_max[i]);
+        if (nbm <= nt) {
+            if (tid < nbm) mb = block_max[tid];
+        } else {
+            for (int64_t i = tid; i < nbm; i += 8 * nt) {   // clamped index: the loads issue back to back
+#pragma unroll
+                for (int u = 0; u < 8; ++u) mb = max(mb, block_max[min(i + u * nt, nbm - 1)]);
+            }
+        }
         mb = wave_max(mb);
         if (lane == 0) wmax[tid >> 6] = mb;
     }
-    const uint32_t rb = slab_max64(partial, S, C, lanes);   // ends in a barrier, which covers wmax too
-    if (tid >= 64) return;
-    if (gridDim.x > 1) mb = wave_max(lane < kFinWaves ? wmax[lane] : 0u);
+    const uint32_t rb = slab_max64<NW>(partial, 0, S, C, lanes);   // ends in a barrier, which covers wmax too
+    if (NW == 0) __syncthreads();
+    if (NW ? tid >= 64 : grp * kFinCh >= C) return;
+    if (gridDim.x > 1) mb = wave_max(lane < nt / 64 ? wmax[lane] : 0u);
     else mb = wave_max(rb);
     const sq_scale sc = make_scale(mb, (float)cfg.Q);
-    if (blockIdx.x == 0 && lane == 0) *scale = sc;
+    if (grp == 0 && lane == 0) *scale = sc;
     const int Sh = cfg.num_groups - 1;   // largest shift
-    const int64_t c = (int64_t)blockIdx.x * kFinCh + lane;
+    const int64_t c = grp * kFinCh + lane;
     int sh = -1;
     if (c < C) {
         const int g = sc.flags ? Sh : group_of(__uint_as_float(rb), sc.r_max, cfg.num_groups);
@@ -348,7 +407,7 @@ __global__ __launch_bounds__(kFinThreads) void k_final_groups(const uint32_t* pa
         // every shift fits int8 (N_G - 1 <= T): one window at base 0, the
         // code of channel c stored as code << sh_c in its own column
         if (c < C) layout[kLayoutHeader + c] = sh;
-        if (blockIdx.x == 0 && lane < kLayoutHeader) {
+        if (grp == 0 && lane < kLayoutHeader) {
             int v = 0;
             if (lane == kLayNR) v = 1;
             else if (lane == kLayBase) v = (int)fold_ext_base(C);
@@ -363,7 +422,7 @@ __global__ __launch_bounds__(kFinThreads) void k_final_groups(const uint32_t* pa
         const int m = __popcll(__ballot(sh == q));
         if (lane == q) n = m;
     }
-    if (lane < kMaxRegions) hist[(int64_t)blockIdx.x * hist_ld + lane] = n;
+    if (lane < kMaxRegions) hist[grp * hist_ld + lane] = n;
 }
 
 // Shift windows of the fold (the layout is documented in sq_internal.h), held
@@ -441,10 +500,25 @@ __global__ __launch_bounds__(kPlaceThreads) void k_final_place(const uint8_t* __
     // (thread t sums shift t % 8 over the groups t / 8 mod 32), then those of
     // the earlier waves
     int vt = 0, vb = 0;
-    for (int64_t b = tid / kMaxRegions; b < nb; b += kPlaceThreads / kMaxRegions) {
-        const int h = hist[b * hist_ld + tid % kMaxRegions];
-        vt += h;
-        vb += b < first ? h : 0;
+    constexpr int64_t kStep = kPlaceThreads / kMaxRegions;
+    if (nb <= kStep) {
+        const int64_t b = tid / kMaxRegions;
+        if (b < nb) {
+            vt = hist[b * hist_ld + tid % kMaxRegions];
+            vb = b < first ? vt : 0;
+        }
+    } else {
+        for (int64_t b0 = tid / kMaxRegions; b0 < nb; b0 += 8 * kStep) {   // 8 loads in flight
+            int h[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) h[u] = hist[min(b0 + u * kStep, nb - 1) * hist_ld + tid % kMaxRegions];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int64_t b = b0 + u * kStep;
+                vt += b < nb ? h[u] : 0;
+                vb += b < min(first, nb) ? h[u] : 0;
+            }
+        }
     }
     int vw = 0;
     for (int w = 0; w < wave; ++w)
@@ -1345,12 +1419,31 @@ hipError_t launch_colmax(const float* x, int64_t M, int64_t C, int64_t ld, uint3
     return hipGetLastError();
 }
 
+// Second-level blocks: 16 waves for 64 channels; 4 where those read the slabs
+// and the block maxima in a batch of loads or two; a wave for 64 channels where
+// there are many in few slabs (8 x 262144, 6 bits: 83.8 us with 16 waves, 55.4
+// with 4, 52.6 with one; below 32768 channels 4 and one are equal).
+enum class Fin { kBlock16, kBlock4, kWide };
+static Fin fin_kind(int64_t slabs, int64_t nbm, int64_t nb) {
+    if (slabs <= 8 && nb >= 512) return Fin::kWide;
+    return slabs <= 32 && nbm <= 2048 ? Fin::kBlock4 : Fin::kBlock16;
+}
+
 static hipError_t launch_groups_place(const uint32_t* partial, int64_t slabs, const uint32_t* block_max, int64_t nbm,
                                       int64_t C, const QuantCfg& cfg, uint8_t* group, sq_scale* scale, int32_t* layout,
                                       int64_t ext_max, int32_t* hist, int hist_ld, hipStream_t s) {
     const int64_t nb = fin_blocks(C);
-    hipLaunchKernelGGL(k_final_groups, dim3((unsigned)nb), dim3(kFinThreads), 0, s, partial, slabs, block_max, nbm, C,
-                       cfg, group, scale, layout, ext_max, hist, hist_ld);
+    auto groups = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        const int64_t blocks = NW ? nb : (nb + kWideWaves - 1) / kWideWaves;
+        hipLaunchKernelGGL(k_final_groups<NW>, dim3((unsigned)blocks), dim3(kFinThreadsOf<NW>), 0, s, partial, slabs,
+                           block_max, nbm, C, cfg, group, scale, layout, ext_max, hist, hist_ld);
+    };
+    switch (fin_kind(slabs, nbm, nb)) {
+        case Fin::kWide: groups(std::integral_constant<int, 0>()); break;
+        case Fin::kBlock4: groups(std::integral_constant<int, 4>()); break;
+        case Fin::kBlock16: groups(std::integral_constant<int, kFinWaves>()); break;
+    }
     if (ext_max > 0)
         hipLaunchKernelGGL(k_final_place, dim3((unsigned)((nb + 3) / 4)), dim3(kPlaceThreads), 0, s, group, hist,
                            hist_ld, nb, C, cfg, layout, ext_max);
@@ -1366,7 +1459,17 @@ hipError_t launch_finalize_ranges(const uint32_t* ranges, int64_t slabs, int64_t
     int32_t* hist = reinterpret_cast<int32_t*>(ws);
     if (nb == 1)   // the group kernel's one block sees every channel
         return launch_groups_place(ranges, slabs, nullptr, 0, C, cfg, group, scale, layout, ext_max, hist, kFinCh, s);
-    hipLaunchKernelGGL(k_colmax_reduce, dim3((unsigned)nb), dim3(kFinThreads), 0, s, ranges, slabs, C, ws, bmax);
+    auto reduce = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        const int64_t blocks = NW ? nb : (nb + kWideWaves - 1) / kWideWaves;
+        hipLaunchKernelGGL(k_colmax_reduce<NW>, dim3((unsigned)blocks), dim3(kFinThreadsOf<NW>), 0, s, ranges, slabs,
+                           slabs, C, ws, bmax, nb);
+    };
+    switch (fin_kind(slabs, 0, nb)) {
+        case Fin::kWide: reduce(std::integral_constant<int, 0>()); break;
+        case Fin::kBlock4: reduce(std::integral_constant<int, 4>()); break;
+        case Fin::kBlock16: reduce(std::integral_constant<int, kFinWaves>()); break;
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_groups_place(ws, 1, bmax, nb, C, cfg, group, scale, layout, ext_max, hist, kFinCh, s);

@@ -37,3 +37,21 @@ def test_finalize_group_edges(sq, C, bits, ng):
     check_quant(sq, a, dY, bits, ng, 0, 0, 0)
     for name in ("q_fold", "q_t", "group", "layout", "scale"):
         assert torch.equal(getattr(a, name), getattr(b, name)), name
+
+
+# channel counts whose shift counts take more than one batch of loads (above
+# 16384) and, from 32705 in at most 8 slabs, a wave per 64 channels
+@pytest.mark.parametrize("M,C", [(9, 16385), (8, 32704), (8, 32705), (9, 40000), (5, 70001)])
+@pytest.mark.parametrize("bits,ng", [(4, 4), (6, 4)])
+def test_finalize_many_channels(sq, M, C, bits, ng):
+    import torch
+    print(f"finalize M={M} C={C} b={bits}", flush=True)
+    rng = np.random.default_rng(M + C + bits)
+    dY = (rng.uniform(-1, 1, (M, C)) * 2.0 ** -rng.uniform(0, 9, C)).astype(np.float32)
+    d = _dev(dY)
+    a = sq.quantize_grad(d, bits, ng)
+    b = sq.quantize_grad_from_ranges(d, d.abs().view(torch.int32).contiguous(), bits, ng)
+    torch.cuda.synchronize()
+    check_quant(sq, a, dY, bits, ng, 0, 0, 0)
+    for name in ("q_fold", "q_t", "group", "layout", "scale"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
