@@ -888,8 +888,8 @@ static sq_status quantize_grad_conv_impl(const float* dY, int64_t N, int64_t H, 
     const int64_t ext_max = fold_ext_max(C_out, cfg);
     if (ranges) {
         if (C_out > 0)
-            SQ_TRY(hip_status(launch_finalize_ranges(ranges, range_slabs, C_out, cfg, partial, group, scale, layout,
-                                                     ext_max, s),
+            SQ_TRY(hip_status(launch_finalize_ranges(ranges, range_slabs, C_out, cfg, partial,
+                                                     colmax_workspace_words(M, C_out), group, scale, layout, ext_max, s),
                               "finalize"));
     } else {
         SQ_TRY(hip_status(launch_colmax_finalize_grad(dY, M, C_out, ld_dY, cfg, partial, group, scale, layout,
@@ -1047,7 +1047,8 @@ sq_status sq_quantize_grad_from_ranges(const float* dY, int64_t M, int64_t C_out
     uint32_t* rbits = static_cast<uint32_t*>(workspace);
     const int64_t ext_max = fold_ext_max(C_out, cfg);
     if (C_out > 0)
-        SQ_TRY(hip_status(launch_finalize_ranges(ranges, range_slabs, C_out, cfg, rbits, group, scale, layout, ext_max, s),
+        SQ_TRY(hip_status(launch_finalize_ranges(ranges, range_slabs, C_out, cfg, rbits, colmax_workspace_words(M, C_out),
+                                                 group, scale, layout, ext_max, s),
                           "finalize"));
     SQ_TRY(hip_status(launch_quantize(dY, M, C_out, ld_dY, group, scale, cfg, q_fold, ld_fold, q_t, ld_t,
                                       layout + kLayoutHeader + ext_max, s, PadGrid(), tiled_of(p)),

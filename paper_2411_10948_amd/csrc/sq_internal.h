@@ -92,9 +92,11 @@ hipError_t launch_colmax(const float* x, int64_t M, int64_t C, int64_t ld, uint3
 hipError_t launch_colmax_finalize_grad(const float* x, int64_t M, int64_t C, int64_t ld, const QuantCfg& cfg,
                                        uint32_t* ws, uint8_t* group, sq_scale* scale, int32_t* layout,
                                        int64_t ext_max, hipStream_t s);
-// finalize alone, from the producer's partial maxima ranges [slabs, C]
+// finalize alone, from the producer's partial maxima ranges [slabs, C], over
+// the scratch ws of `words` (colmax_workspace_words) words
 hipError_t launch_finalize_ranges(const uint32_t* ranges, int64_t slabs, int64_t C, const QuantCfg& cfg, uint32_t* ws,
-                                  uint8_t* group, sq_scale* scale, int32_t* layout, int64_t ext_max, hipStream_t s);
+                                  int64_t words, uint8_t* group, sq_scale* scale, int32_t* layout, int64_t ext_max,
+                                  hipStream_t s);
 // Padded pixel grid of the transposed codes (conv wgrad): row m = (n, oh, ow)
 // of an Ho x Wo output grid goes to column n HpWp + oh Wp + ow; Wo = 0: plain
 // (column m).  Every value below 2^32.

@@ -236,6 +236,7 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 // every wave of the block takes 64 channels of its own and all of their slabs.
 // ---------------------------------------------------------------------------
 constexpr int kFinCh = 64, kFinWaves = 16, kWideWaves = 4;
+constexpr int64_t kFinRows = 8 * 4 * kFinWaves;   // slabs that a block reads in one batch of 16-byte loads
 template <int NW>
 constexpr int kFinThreadsOf = 64 * (NW ? NW : kWideWaves);
 
@@ -1419,6 +1420,7 @@ hipError_t launch_colmax(const float* x, int64_t M, int64_t C, int64_t ld, uint3
     return hipGetLastError();
 }
 
+constexpr int64_t kDirectRanges = 16384;   // ranges that a block of 16 waves reads in two batches of loads
 // Second-level blocks: 16 waves for 64 channels; 4 where those read the slabs
 // and the block maxima in a batch of loads or two; a wave for 64 channels where
 // there are many in few slabs (8 x 262144, 6 bits: 83.8 us with 16 waves, 55.4
@@ -1450,29 +1452,44 @@ static hipError_t launch_groups_place(const uint32_t* partial, int64_t slabs, co
     return hipGetLastError();
 }
 
+// ws, `words` long: at least channel ranges, kMaxRegions words, group maxima.
 hipError_t launch_finalize_ranges(const uint32_t* ranges, int64_t slabs, int64_t C, const QuantCfg& cfg, uint32_t* ws,
-                                  uint8_t* group, sq_scale* scale, int32_t* layout, int64_t ext_max, hipStream_t s) {
-    // ws: channel ranges, group maxima.  A group's shift counts take the place
-    // of its own channel ranges, which its block has read by then.
+                                  int64_t words, uint8_t* group, sq_scale* scale, int32_t* layout, int64_t ext_max,
+                                  hipStream_t s) {
     const int64_t nb = fin_blocks(C);
-    uint32_t* bmax = ws + C + kMaxRegions;
     int32_t* hist = reinterpret_cast<int32_t*>(ws);
-    if (nb == 1)   // the group kernel's one block sees every channel
-        return launch_groups_place(ranges, slabs, nullptr, 0, C, cfg, group, scale, layout, ext_max, hist, kFinCh, s);
+    // few ranges: the group kernel takes r_max from all of them (one launch
+    // fewer: 256 x 256 in one window 10.0 -> 7.9 us)
+    if (slabs * C <= kDirectRanges || (nb == 1 && slabs <= kFinRows))
+        return launch_groups_place(ranges, slabs, ranges, slabs * C, C, cfg, group, scale, layout, ext_max, hist,
+                                   kMaxRegions, s);
+    // Otherwise a reduction before it, over gy parts of the slabs where they
+    // are many for their channels and the scratch holds the parts (200704 x 64,
+    // 6272 slabs, the call: 35.8 us with one block for all of them, 23.2).
+    int64_t gy = std::min({slabs / (C % 4 ? kFinRows / 4 : kFinRows), 512 / nb, (int64_t)64, (words - kMaxRegions * nb) / (C + nb)});
+    gy = std::max<int64_t>(gy, 1);
+    const int64_t per = (slabs + gy - 1) / gy;
+    gy = (slabs + per - 1) / per;
+    // ws: shift counts, part ranges, group maxima of the parts; or, with one
+    // part, channel ranges, group maxima: a group's shift counts then take the
+    // place of its own channel ranges, which its block has read by then
+    uint32_t* parts = gy > 1 ? ws + kMaxRegions * nb : ws;
+    uint32_t* bmax = gy > 1 ? parts + gy * C : ws + C + kMaxRegions;
     auto reduce = [&](auto nw) {
         constexpr int NW = decltype(nw)::value;
         const int64_t blocks = NW ? nb : (nb + kWideWaves - 1) / kWideWaves;
-        hipLaunchKernelGGL(k_colmax_reduce<NW>, dim3((unsigned)blocks), dim3(kFinThreadsOf<NW>), 0, s, ranges, slabs,
-                           slabs, C, ws, bmax, nb);
+        hipLaunchKernelGGL(k_colmax_reduce<NW>, dim3((unsigned)blocks, (unsigned)gy), dim3(kFinThreadsOf<NW>), 0, s,
+                           ranges, slabs, per, C, parts, bmax, nb);
     };
-    switch (fin_kind(slabs, 0, nb)) {
+    switch (fin_kind(per, 0, nb)) {
         case Fin::kWide: reduce(std::integral_constant<int, 0>()); break;
         case Fin::kBlock4: reduce(std::integral_constant<int, 4>()); break;
         case Fin::kBlock16: reduce(std::integral_constant<int, kFinWaves>()); break;
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_groups_place(ws, 1, bmax, nb, C, cfg, group, scale, layout, ext_max, hist, kFinCh, s);
+    return launch_groups_place(parts, gy, bmax, gy * nb, C, cfg, group, scale, layout, ext_max, hist,
+                               gy > 1 ? kMaxRegions : kFinCh, s);
 }
 
 hipError_t launch_colmax_finalize_grad(const float* x, int64_t M, int64_t C, int64_t ld, const QuantCfg& cfg,

@@ -40,10 +40,13 @@ def test_finalize_group_edges(sq, C, bits, ng):
 
 
 # channel counts whose shift counts take more than one batch of loads (above
-# 16384) and, from 32705 in at most 8 slabs, a wave per 64 channels
-@pytest.mark.parametrize("M,C", [(9, 16385), (8, 32704), (8, 32705), (9, 40000), (5, 70001)])
+# 16384) and, from 32705 in at most 8 slabs, a wave per 64 channels; many slabs
+# (here a range per row: a part of them per block where the scratch holds the
+# parts) on both sides of the direct path's limits (512 slabs, 16384 ranges)
+@pytest.mark.parametrize("M,C", [(9, 16385), (8, 32704), (8, 32705), (9, 40000), (5, 70001),
+                                 (512, 1), (513, 1), (700, 3), (6000, 64), (128, 128), (129, 128), (3001, 130), (2000, 1025)])
 @pytest.mark.parametrize("bits,ng", [(4, 4), (6, 4)])
-def test_finalize_many_channels(sq, M, C, bits, ng):
+def test_finalize_many_channels_or_slabs(sq, M, C, bits, ng):
     import torch
     print(f"finalize M={M} C={C} b={bits}", flush=True)
     rng = np.random.default_rng(M + C + bits)
