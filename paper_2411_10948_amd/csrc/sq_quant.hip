@@ -1260,8 +1260,9 @@ __global__ __launch_bounds__(kBnQThreads) void k_quantize_bn(const float* __rest
 // ---------------------------------------------------------------------------
 // Per-channel quantization of a weight matrix (one scale per row or per
 // column; the forward pass quantizes weights per output channel and loss
-// propagation per input channel, Sec. 5.1).  Weights are quantized once per
-// step, off the backward hot path, so these kernels are plain.
+// propagation per input channel, Sec. 5.1).  The forward's row-major codes per
+// row have a kernel of their own (k_quantize_rows); the other forms, off the
+// training step's path, are plain.
 // ---------------------------------------------------------------------------
 // column scales from the colmax slab maxima
 __global__ void k_channel_scales_cols(const uint32_t* __restrict__ partial, int64_t S, int64_t C, int Q,
@@ -1284,19 +1285,22 @@ __global__ void k_channel_scales_rows(const float* __restrict__ x, int64_t rows,
     }
 }
 
-// Row scales and row-major codes in one pass, one wave per row: the row's
-// second read comes from the caches.  Bound by latency (a row of a few
-// thousand floats); scales and codes as two launches took 6.2 + 9.9 us on 3072 x
-// 768, this one 6.6 us.  VEC: 16-byte aligned rows.
-template <bool VEC>
+// Row scales and row-major codes in one pass: the row's second read comes from
+// the caches.  LPR lanes take a row (4 to 64, its quads of columns, so that
+// short rows fill the wave; fixed at compile time, the loops of long rows were
+// 15 to 20 % slower otherwise).  Bound by latency (a row of a few thousand
+// floats); scales and codes as two launches took 6.2 + 9.9 us on 3072 x 768,
+// this one 6.6 us; 100000 x 16 two launches 18.5 us, a wave per row 22.7, four
+// lanes per row 4.5.  VEC: 16-byte aligned rows.
+template <bool VEC, int LPR>
 __global__ __launch_bounds__(256) void k_quantize_rows(const float* __restrict__ x, int64_t rows, int64_t cols, int64_t ld,
                                                        int Q, sq_scale* __restrict__ scales, int8_t* __restrict__ q,
                                                        int64_t ld_q) {
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x % LPR;
     const float Qf = (float)Q;
-    const int64_t nwaves = (int64_t)gridDim.x * 4;
+    constexpr int kRows = 256 / LPR;   // rows per block and step
     const int64_t quads = cols >> 2;
-    for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < rows; r += nwaves) {
+    for (int64_t r = (int64_t)blockIdx.x * kRows + threadIdx.x / LPR; r < rows; r += (int64_t)gridDim.x * kRows) {
         const float* row = x + r * ld;
         auto load4 = [&](int64_t i) {
             if constexpr (VEC) return *reinterpret_cast<const float4*>(row + 4 * i);
@@ -1305,11 +1309,13 @@ __global__ __launch_bounds__(256) void k_quantize_rows(const float* __restrict__
         const int64_t tail = 4 * quads + lane;   // the last cols % 4 columns
         uint32_t m = tail < cols ? absbits(row[tail]) : 0u;
 #pragma unroll 4
-        for (int64_t i = lane; i < quads; i += 64) {
+        for (int64_t i = lane; i < quads; i += LPR) {
             const float4 v = load4(i);
             m = max(max(m, max(absbits(v.x), absbits(v.y))), max(absbits(v.z), absbits(v.w)));
         }
-        m = wave_max(m);
+        // the lanes of a row enter and leave this loop together
+#pragma unroll
+        for (int o = LPR / 2; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o, 64));
         const sq_scale sc = make_scale(m, Qf);
         if (lane == 0) scales[r] = sc;
         auto code = [&](float v) {
@@ -1317,7 +1323,7 @@ __global__ __launch_bounds__(256) void k_quantize_rows(const float* __restrict__
         };
         int8_t* out = q + r * ld_q;   // ld_q a multiple of 16, 16-byte aligned
 #pragma unroll 4
-        for (int64_t i = lane; i < quads; i += 64) {
+        for (int64_t i = lane; i < quads; i += LPR) {
             const float4 v = load4(i);
             reinterpret_cast<uint32_t*>(out)[i] = code(v.x) | code(v.y) << 8 | code(v.z) << 16 | code(v.w) << 24;
         }
@@ -1647,11 +1653,19 @@ hipError_t launch_quantize_channels(const float* x, int64_t rows, int64_t cols, 
     if (rows <= 0 || cols <= 0) return hipSuccess;
     const int Q = (1 << (bits - 1)) - 1;
     if (axis == 0 && !transpose) {
-        const dim3 grid((unsigned)std::min<int64_t>((rows + 3) / 4, 8192));
-        if (colmax_vec(x, ld))
-            hipLaunchKernelGGL(k_quantize_rows<true>, grid, dim3(256), 0, s, x, rows, cols, ld, Q, scales, q, ld_q);
-        else
-            hipLaunchKernelGGL(k_quantize_rows<false>, grid, dim3(256), 0, s, x, rows, cols, ld, Q, scales, q, ld_q);
+        auto run = [&](auto lpr) {
+            constexpr int LPR = decltype(lpr)::value, kRows = 256 / LPR;
+            const dim3 grid((unsigned)std::min<int64_t>((rows + kRows - 1) / kRows, 8192));
+            if (colmax_vec(x, ld))
+                hipLaunchKernelGGL((k_quantize_rows<true, LPR>), grid, dim3(256), 0, s, x, rows, cols, ld, Q, scales, q, ld_q);
+            else
+                hipLaunchKernelGGL((k_quantize_rows<false, LPR>), grid, dim3(256), 0, s, x, rows, cols, ld, Q, scales, q, ld_q);
+        };
+        if (cols <= 16) run(std::integral_constant<int, 4>());
+        else if (cols <= 32) run(std::integral_constant<int, 8>());
+        else if (cols <= 64) run(std::integral_constant<int, 16>());
+        else if (cols <= 128) run(std::integral_constant<int, 32>());
+        else run(std::integral_constant<int, 64>());
         return hipGetLastError();
     }
     if (axis == 1) {

@@ -19,7 +19,8 @@ def sq():
     return shiftquant
 
 
-@pytest.mark.parametrize("rows,cols", [(1, 1), (5, 3), (7, 4), (9, 63), (4, 255), (6, 257), (3, 1000), (33, 2051)])
+@pytest.mark.parametrize("rows,cols", [(1, 1), (5, 3), (7, 4), (9, 63), (4, 255), (6, 257), (3, 1000), (33, 2051),
+                                       (130, 2), (129, 16), (67, 17), (200, 33), (131, 64), (35, 70), (21, 128)])   # several rows per wave
 @pytest.mark.parametrize("pad", [0, 1, 4])
 def test_quantize_rows_edges(sq, rows, cols, pad):
     import torch
