@@ -1337,7 +1337,7 @@ bool pipe_ok(const GemmArgs& a) {
 // 79.2 us, now 68.8) and 28 % of a split one (768 x 768, K = 3152: 18.0 us, now
 // 11.7).  Constants fitted to the products alone, hot in the caches, picked
 // small tiles for long products that read HBM (MLP wgrad 45 -> 54 us).
-enum class Pick { kLarge, kTall, kDuo, kMid, kSmall, kFlat, kTiny, kNarrow };
+enum class Pick { kLarge, kTall, kDuo, kMid, kSmall, kFlat, kTiny, kNarrow, kStaged };
 struct TileCost {
     int bm, bn, per_cu;
     float lat, thr, round, mb;
@@ -1380,6 +1380,39 @@ Pick best_tile(int64_t Mg, int64_t Ng, int64_t K, int splits, float* cost = null
     }
     if (cost) *cost = t;
     return (Pick)best;
+}
+
+// Tile of an unsplit product of many rows with a short K, which the model
+// (fitted to longer ones) prices wrongly: such a launch is bound by its blocks'
+// prologues and its stores, so fewer or lighter blocks win.  kStaged: the
+// register-staged kernel's 128 x 128 (40 KB of LDS, direct stores), not for
+// tile-major operands or ranges; ext: with appended fold windows.  us, the
+// model's tile -> this rule's:
+//   400000 x 16, K = 16: 35.1 -> 17.3 staged; x 48, K = 64: 25.6 -> 24.6 staged,
+//   K = 128: 26.7 tiny (staged 30.7); x 128, K = 16: 40.8 -> 37.3 staged, but
+//   71.3 -> 62.4 duo with windows (staged 77.8); x 64, K = 64: 26.0 tiny, but
+//   100000 rows 13.3 -> 9.6 narrow (tiny 10.3)
+//   100000 x 96, K = 32: 15.1 -> 12.7 duo (staged 14.0); x 160, K = 48: 22.2 ->
+//   19.0 staged, 29.5 -> 24.8 with windows; 40000 x 160: 11.3 (staged 12.3)
+//   200000 x 304, K = 48: 54.1 -> 44.3 staged; K = 128: 70.6 -> 55.8 duo;
+//   100000 x 640, K = 64: 61.7 -> 47.4 duo (staged 58.7); 56176 x 1088, K = 64,
+//   windows: 73.1 -> 57.5 duo, without 49.3 (duo 46.2; 33000 x 3000 101 for 87)
+//   20000 rows: the model's tile is the best or within 0.3 us of it
+Pick product_tile(int64_t Mg, int64_t Ng, int64_t K, int splits, bool ext, bool staged_ok) {
+    constexpr int64_t kManyRows = 32768, kVeryManyRows = 262144;
+    const Pick p = best_tile(Mg, Ng, K, splits);
+    if (splits > 1 || Mg < kManyRows) return p;
+    if (Ng > 128) {
+        const double mb = 4e-6 * (double)Mg * (double)Ng;
+        if (K > 128 || mb < 32.0) return p;
+        if (Ng > 768) return mb > 220.0 && ext && Ng <= 2048 ? Pick::kDuo : p;
+        if (K > 64 ? mb > 200.0 : mb > 220.0 && (ext || Ng >= 512)) return Pick::kDuo;
+        return staged_ok && K <= 64 ? Pick::kStaged : p;
+    }
+    const bool wide_ok = Ng > 64 && Mg > kVeryManyRows && (!ext || Ng <= 96);
+    if (staged_ok && ((Ng <= 32 && K <= 128) || (K <= 64 && (Ng <= 48 || wide_ok)))) return Pick::kStaged;
+    if (Ng <= 64) return Mg <= kVeryManyRows ? Pick::kNarrow : Pick::kTiny;
+    return K <= 128 ? Pick::kDuo : p;
 }
 
 // Tile of the per-tap convolution: at most 64 columns take 256 x 64 where that
@@ -1429,6 +1462,7 @@ hipError_t launch_pick(Pick p, const GemmArgs& a, int splits, int64_t k_per_spli
         case Pick::kMid: return launch_tile<PipeMid, RANGES>(a, splits, k_per_split, s);
         case Pick::kSmall: return launch_tile<PipeSmall, RANGES>(a, splits, k_per_split, s);
         case Pick::kFlat: return launch_tile<PipeFlat, RANGES>(a, splits, k_per_split, s);
+        case Pick::kNarrow: return launch_tile<PipeNarrow, RANGES>(a, splits, k_per_split, s);
         default: return launch_tile<PipeTiny, RANGES>(a, splits, k_per_split, s);
     }
 }
@@ -1508,14 +1542,16 @@ int wgrad_splits(int64_t M, int64_t C_out, int64_t C_in) {
     return best;
 }
 
-// What launch_gemm runs for a product of the pipelined kernel, for tests that
-// pin a tile (not part of the public header): the tile's rows and columns, and
-// the rows of the first of two launches (0: one launch).
-extern "C" void sq_internal_gemm_plan(int64_t Mg, int64_t Ng, int64_t K, int32_t splits, int32_t* bm, int32_t* bn,
-                                      int64_t* first_rows) {
-    const TileCost& c = kTileCost[(int)best_tile(Mg, Ng, K, std::max(1, splits))];
-    *bm = c.bm;
-    *bn = c.bn;
+// What launch_gemm runs for a product of row-major operands, for tests that pin
+// a tile (not part of the public header): the tile's rows and columns (0: the
+// register-staged kernel), and the rows of the first of two launches (0: one
+// launch).  ext: with appended fold windows.
+extern "C" void sq_internal_gemm_plan(int64_t Mg, int64_t Ng, int64_t K, int32_t splits, int32_t ext, int32_t* bm,
+                                      int32_t* bn, int64_t* first_rows) {
+    const Pick p = product_tile(Mg, Ng, K, std::max(1, splits), ext != 0, true);
+    const bool narrow = p == Pick::kNarrow;
+    *bm = p == Pick::kStaged ? 0 : narrow ? PipeNarrow::BM : kTileCost[(int)p].bm;
+    *bn = p == Pick::kStaged ? 0 : narrow ? PipeNarrow::BN : kTileCost[(int)p].bn;
     *first_rows = splits > 1 ? 0 : large_rows(Mg, Ng, K);
 }
 
@@ -1543,7 +1579,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     // tile-major operands: the pipelined kernel only, no convolution
     if (a.tiled && (!pipe || a.taps || a.kseg)) return hipErrorInvalidValue;
     if (a.kseg && (!pipe || a.splits > 1 || a.layout)) return hipErrorInvalidValue;   // pipelined kernel only
-    const Pick p = best_tile(a.Mg, a.Ng, a.K, std::max(1, a.splits));
+    const bool staged_ok = !a.tiled && !a.kseg && !a.ranges;
+    const Pick p = product_tile(a.Mg, a.Ng, a.K, std::max(1, a.splits), a.extA != nullptr, staged_ok);
     if (pipe && a.splits <= 1 && !a.ranges && !a.part && !a.taps && !a.kseg) {
         const int64_t rows = large_rows(a.Mg, a.Ng, a.K);
         if (rows > 0) {
@@ -1563,7 +1600,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
         if (!pipe || a.K % 64 || splits > 1 || !a.out || a.part) return hipErrorInvalidValue;
         return launch_pick<true>(p, a, 1, per * 64, s);
     }
-    if (!pipe)
+    if (!pipe || p == Pick::kStaged)
         return p == Pick::kLarge ? launch_cfg<CfgLarge>(a, splits, per * 64, s)
                                  : launch_cfg<CfgSmall>(a, splits, per * 64, s);
     return launch_pick(p, a, splits, per * 64, s);

@@ -78,6 +78,19 @@ def test_mlp_input_gradient_plan(sq):
     assert gemm_plan(sq, 16384, 768, 3072) == (128, 384, 0)
 
 
+def test_narrow_product_plan(sq):
+    # many rows, a short K: bound by the blocks' prologues and the stores
+    from tests.gemm_plan import gemm_plan
+    assert gemm_plan(sq, 400000, 32, 32) == (0, 0, 0)          # register-staged
+    assert gemm_plan(sq, 100000, 10, 64) == (0, 0, 0)
+    assert gemm_plan(sq, 100000, 64, 64) == (256, 64, 0)
+    assert gemm_plan(sq, 400000, 64, 64) == (64, 64, 0)
+    assert gemm_plan(sq, 400000, 128, 32) == (0, 0, 0)
+    assert gemm_plan(sq, 400000, 128, 32, ext=True) == (256, 128, 0)
+    assert gemm_plan(sq, 200000, 304, 48) == (0, 0, 0)
+    assert gemm_plan(sq, 200000, 304, 128) == (256, 128, 0)
+
+
 @pytest.mark.parametrize("M,C_out,C_in,splits", [(256, 1000, 2048, 1), (4096, 1024, 2048, 1), (64, 64, 64, 1), (0, 64, 64, 1),
                                                  (16384, 3072, 768, 5), (12040, 1280, 1344, 2),
                                                  # one or two tiles: enough splits for a block on every CU

@@ -3,6 +3,8 @@ columns and inner dimensions and with appended fold windows: both backward
 products of a layer against the exact products of its codes."""
 import pytest
 
+from tests.gemm_plan import gemm_plan
+
 pytestmark = pytest.mark.gpu
 
 
@@ -28,6 +30,54 @@ LAYERS = [  # M, C_out, C_in: tile of dX; tile and splits of dW
     (257, 100, 200),        # 64 x 128; 64 x 128
     (3000, 768, 768),       # 64 x 128; 64 x 64
 ]
+
+
+# many rows, short inner dimensions: dX tile of row-major codes (0: the
+# register-staged kernel) without and with appended fold windows
+STAGED, WIDE = (0, 0), (256, 128)
+NARROW = [
+    (32767, 16, 16, (64, 128), (64, 128)),
+    (32768, 10, 8, STAGED, STAGED),
+    (33001, 128, 32, STAGED, STAGED),
+    (33001, 64, 48, STAGED, STAGED),
+    (262145, 30, 96, STAGED, STAGED),
+    (262145, 64, 97, STAGED, WIDE),
+    (70001, 48, 129, STAGED, STAGED),
+    (190001, 17, 300, STAGED, WIDE),
+    (40001, 129, 32, (256, 64), (256, 64)),
+    (33333, 65, 48, (256, 64), (256, 64)),
+    (32769, 200, 64, (256, 64), (256, 64)),
+    (262145, 96, 49, (64, 64), (64, 64)),
+    (50001, 128, 65, WIDE, WIDE),
+    (40000, 100, 128, WIDE, WIDE),
+    (190001, 65, 300, WIDE, WIDE),
+]
+
+
+@pytest.mark.parametrize("M,C_out,C_in,tile,tile_ext", NARROW)
+@pytest.mark.parametrize("bits,tiled", [(4, False), (6, False), (6, True)])
+def test_narrow_products(sq, M, C_out, C_in, tile, tile_ext, bits, tiled):
+    assert gemm_plan(sq, M, C_in, C_out) == (*tile, 0)
+    assert gemm_plan(sq, M, C_in, C_out, ext=True) == (*tile_ext, 0)
+    test_every_tile_and_split(sq, M, C_out, C_in, bits, tiled)
+
+
+# the forward's per-column scales on the register-staged kernel
+@pytest.mark.parametrize("M,C_in,C_out", [(33001, 70, 30), (32768, 64, 41)])
+@pytest.mark.parametrize("bits", [4, 8])
+def test_narrow_forward(sq, M, C_in, C_out, bits):
+    import torch
+    print(f"narrow forward M={M} C_in={C_in} C_out={C_out} b={bits}", flush=True)
+    assert gemm_plan(sq, M, C_out, C_in) == (0, 0, 0)
+    g = torch.Generator(device="cuda").manual_seed(M + C_out + bits)
+    x = torch.randn(M, C_in, generator=g, device="cuda") * torch.exp2(-6 * torch.rand(C_in, generator=g, device="cuda"))
+    c = sq.quantize_grad(x, bits, 4)
+    wq, ws = sq.quantize_channels(torch.randn(C_out, C_in, generator=g, device="cuda"), 8)
+    A, Y = sq.gemm_forward(c, wq, ws, want_acc=True)
+    torch.cuda.synchronize()
+    ref = ((c.codes().double() * torch.exp2(3.0 - c.group.double())) @ wq[:, :C_in].t().double()).to(torch.int32)
+    assert torch.equal(A, ref)
+    assert torch.equal(Y, ref.float() * ((c.scale[2] * ws[:, 2]) * 0.125)[None, :])
 
 
 @pytest.mark.parametrize("M,C_out,C_in", LAYERS)

@@ -83,6 +83,7 @@ RANGE_TILES = [  # M, C_out, C_in: every tile shape, ragged rows and columns
     (11207, 704, 657, (128, 384)),
     (9795, 256, 1283, (256, 128)),
     (9830, 3392, 1173, (256, 256)),
+    (40001, 192, 61, (256, 64)),
 ]
 
 
