@@ -15,9 +15,9 @@
 //                    App. B Eq. "sq"), clamp; writes the shift-folded dgrad
 //                    operand row-major and the codes transposed: k_quantize8
 //                    (8 channels a thread), k_quantize_grid (transposed codes
-//                    on the padded pixel grid), k_quantize (any shape and
-//                    alignment); per tensor these also take the scale from the
-//                    abs-max pass's block maxima
+//                    on the padded pixel grid; k_quantize8 for some widths),
+//                    k_quantize (any shape and alignment); per tensor these
+//                    also take the scale from the abs-max pass's block maxima
 //
 // All fp32 arithmetic is IEEE with round-to-nearest-even and no contraction
 // (the library is built with -ffp-contract=off and the products below use the
@@ -951,15 +951,16 @@ __device__ __forceinline__ void store_ext8(const Chan8& ch, const uint32_t (&col
     }
 }
 
-// Row-major or tile-major (TL) codes: tiles of 128 rows x 64 channels.
-template <bool SR, bool TL>
+// Row-major or tile-major (TL) codes: tiles of 128 rows x 64 channels.  GRID:
+// q_t on the padded pixel grid (Wo and off multiples of 8; see launch_quantize).
+template <bool SR, bool TL, bool GRID = false>
 __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ x, int64_t M, int64_t C, int64_t ld,
                                                       const uint8_t* __restrict__ group,
                                                       const sq_scale* __restrict__ scale, QuantCfg cfg,
                                                       int8_t* __restrict__ q_fold, int64_t ld_fold,
                                                       int8_t* __restrict__ q_t, int64_t ld_t,
                                                       const int32_t* __restrict__ desc, int64_t ext_base,
-                                                      int meta_vec, TensorMax tm) {
+                                                      int meta_vec, TensorMax tm, PadGrid pg) {
     constexpr int TR = 128, TC = 64, TW = TR / 4 + 1;   // LDS words per channel row (padded)
     __shared__ uint32_t tq[TC * TW];
     __shared__ uint32_t sh_max[4];
@@ -1020,6 +1021,25 @@ __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ 
                 if (TL) {
                     *reinterpret_cast<uint4*>(q_t + tiled_off(c, mm, ld_t)) = lo;
                     *reinterpret_cast<uint4*>(q_t + tiled_off(c, mm + 16, ld_t)) = hi;
+                } else if (GRID) {
+                    // 4 groups of 8 pixels, none across an image row: 8-byte stores
+                    const uint32_t p0 = (uint32_t)mm;
+                    uint32_t n = p0 / pg.HoWo, rem = p0 - n * pg.HoWo, oh = rem / pg.Wo, ow = rem - oh * pg.Wo;
+                    int8_t* row = q_t + c * ld_t + pg.off;
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        if (mm + 8 * g < M)
+                            *reinterpret_cast<uint2*>(row + (int64_t)n * pg.HpWp + (int64_t)oh * pg.Wp + ow) =
+                                make_uint2(src[2 * g], src[2 * g + 1]);
+                        ow += 8;
+                        if (ow == pg.Wo) {
+                            ow = 0;
+                            if (++oh * pg.Wo == pg.HoWo) {
+                                oh = 0;
+                                ++n;
+                            }
+                        }
+                    }
                 } else if (mm + 32 <= M) {
                     *reinterpret_cast<uint4*>(q_t + c * ld_t + mm) = lo;
                     *reinterpret_cast<uint4*>(q_t + c * ld_t + mm + 16) = hi;
@@ -1044,8 +1064,9 @@ __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ 
 // and 1 or 2 B written per code).  Against byte stores per pixel (k_quantize):
 // 64 x 28 x 28 x 128 input 24.5 -> 9.8 us, 6-bit stochastic gradient 29.5 ->
 // 15.6 us; 64 x 14 x 14 x 256 15.2 -> 7.9 and 17.2 -> 8.6 us.  Against 8-byte
-// stores with the straddling words put together (widths a multiple of 8):
-// 64 x 56 x 56 x 64 input 17.6 -> 14.8 us, gradient 17.2 -> 18.2 us.
+// stores with the straddling words of an input put together (widths a multiple
+// of 8): 64 x 56 x 56 x 64 input 17.6 -> 14.8 us; where 8-byte stores win,
+// launch_quantize takes k_quantize8.
 struct GridTiles {
     uint32_t rows;             // image rows per tile
     uint32_t segs;             // tiles per image row (1 unless Wo > 128)
@@ -1577,8 +1598,21 @@ hipError_t launch_quantize(const float* x, int64_t M, int64_t C, int64_t ld, con
     // groups (8 bytes) and descriptors (2 x 16 bytes) of 8 channels load as
     // vectors when aligned
     const int mv = ((reinterpret_cast<uintptr_t>(group) & 7) == 0 && (reinterpret_cast<uintptr_t>(desc) & 15) == 0);
+    // Padded grid: tiles of whole grid rows (k_quantize_grid), or, where image
+    // rows and their places are multiples of 8 pixels, k_quantize8's 128
+    // consecutive pixels with 8-byte stores.  The latter where whole rows fill
+    // too little of a tile, and for stochastic codes (bound by their Philox
+    // words) without appended fold windows.  us, whole-row tiles -> pixels, 200704
+    // pixels: 32 channels 144 wide, 4 bits 43.5 -> 33.9, stochastic 57.0 -> 40.6;
+    // 64 channels 48 wide, 4 bits 33.8 -> 33.3, 6 bits (windows) 40.0 -> 41.9;
+    // 56 wide, stochastic, 4 bits 36.4 -> 35.3, 6 bits 42.1 -> 43.1.
     GridTiles gt{};
-    if (vec && C % 8 == 0 && pg.Wo && q_t && grid_tiles(M, pg, gt)) {
+    const bool on_grid = vec && C % 8 == 0 && pg.Wo && q_t && grid_tiles(M, pg, gt);
+    const bool windows = group && cfg.num_groups - 1 > cfg.T;
+    const uint64_t used = (uint64_t)gt.rows * pg.Wo * 100, slots = (uint64_t)128 * gt.segs;
+    const bool grid8 = on_grid && pg.Wo % 8 == 0 && pg.off % 8 == 0 &&
+                       (windows ? used < 70 * slots : sr || used < 80 * slots);
+    if (on_grid && !grid8) {
         const int64_t tiles = (int64_t)((gt.NH + gt.rows - 1) / gt.rows) * gt.segs * ((C + 63) / 64);
         const dim3 gg((unsigned)std::min<int64_t>(tiles, kQuantMaxBlocks));
         if (sr) hipLaunchKernelGGL(k_quantize_grid<true>, gg, dim3(kBlock), 0, s, x, M, C, ld, group, scale, cfg, q_fold,
@@ -1587,16 +1621,15 @@ hipError_t launch_quantize(const float* x, int64_t M, int64_t C, int64_t ld, con
                                 ld_fold, q_t, ld_t, desc, eb, mv, pg, gt, tm);
         return hipGetLastError();
     }
-    if (vec && C % 8 == 0 && !pg.Wo) {
+    if (grid8 || (vec && C % 8 == 0 && !pg.Wo)) {
         const dim3 g8((unsigned)std::min<int64_t>(((C + 63) / 64) * ((M + 127) / 128), kQuantMaxBlocks));
-        if (sr && tiled) hipLaunchKernelGGL((k_quantize8<true, true>), g8, dim3(kBlock), 0, s, x, M, C, ld, group, scale,
-                                            cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, mv, tm);
-        else if (sr) hipLaunchKernelGGL((k_quantize8<true, false>), g8, dim3(kBlock), 0, s, x, M, C, ld, group, scale,
-                                        cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, mv, tm);
-        else if (tiled) hipLaunchKernelGGL((k_quantize8<false, true>), g8, dim3(kBlock), 0, s, x, M, C, ld, group,
-                                           scale, cfg, q_fold, ld_fold, q_t, ld_t, desc, eb, mv, tm);
-        else hipLaunchKernelGGL((k_quantize8<false, false>), g8, dim3(kBlock), 0, s, x, M, C, ld, group, scale, cfg,
-                                q_fold, ld_fold, q_t, ld_t, desc, eb, mv, tm);
+        auto run = [&](auto k) {
+            hipLaunchKernelGGL(k, g8, dim3(kBlock), 0, s, x, M, C, ld, group, scale, cfg, q_fold, ld_fold, q_t, ld_t, desc,
+                               eb, mv, tm, pg);
+        };
+        if (grid8) run(sr ? k_quantize8<true, false, true> : k_quantize8<false, false, true>);
+        else if (tiled) run(sr ? k_quantize8<true, true> : k_quantize8<false, true>);
+        else run(sr ? k_quantize8<true, false> : k_quantize8<false, false>);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)std::min<int64_t>(n_tiles(tc, tr), kQuantMaxBlocks));

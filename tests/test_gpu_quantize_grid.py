@@ -1,5 +1,5 @@
 """The quantizers that write transposed codes onto the padded pixel grid
-(k_quantize_grid) at the edges of their tiles: widths around the divisors of
+(k_quantize_grid, k_quantize8) at the edges of their tiles: widths around the divisors of
 128, the longest single-tile width, several tiles per image row, tiles that
 span images, leads of 0 to 7 columns and channel counts around 64.  Every byte
 of both grids against the oracle's codes laid out by numpy, and the folded
@@ -37,6 +37,10 @@ CASES = [  # N, H, W, C, KH, KW, PH, PW
     (2, 2, 43, 24, 5, 15, 2, 7), (2, 3, 64, 8, 1, 3, 0, 1), (1, 2, 127, 40, 3, 3, 1, 1), (2, 3, 128, 8, 3, 1, 1, 0),
     (1, 3, 129, 64, 3, 3, 1, 1), (2, 2, 126, 8, 3, 5, 1, 2), (1, 2, 257, 136, 3, 3, 1, 1), (1, 1, 300, 8, 1, 7, 0, 3),
     (9, 1, 9, 8, 1, 3, 0, 1),
+    # 128 consecutive pixels a tile: rows that whole-row tiles fill badly, and
+    # (stochastic) any multiple of 8; tiles of many images; the last tile ragged
+    (2, 3, 72, 72, 3, 3, 1, 1), (1, 3, 144, 64, 3, 3, 1, 1), (2, 3, 48, 8, 3, 1, 1, 0), (7, 3, 8, 136, 3, 3, 1, 1),
+    (1, 1, 80, 40, 1, 1, 0, 0), (2, 2, 200, 24, 3, 3, 1, 1),
 ]
 
 
