@@ -915,16 +915,19 @@ __device__ __forceinline__ Chan8 load_chan8(const uint8_t* __restrict__ group, c
 // the 4 rows; fold[i], row i's folded codes of the main columns.  The bytes
 // are built as code + 128 (unsigned), then flipped back to two's complement
 // with one xor per word.  idx: the logical index of row 0's first element.
-template <bool SR>
-__device__ __forceinline__ void quant8(const float4 (&a)[4], const float4 (&b)[4], const bool (&ok)[4], int64_t idx,
-                                       int64_t C, const Chan8& ch, const QuantCfg& cfg, uint32_t (&colw)[8],
-                                       uint2 (&fold)[4]) {
+// row(i, a, b): the values of row i; emit(i, f): its folded codes, while bits
+// 8 i of colw[j] hold code + 128.
+template <bool SR, class Row, class Emit>
+__device__ __forceinline__ void quant8(Row row, Emit emit, const bool (&ok)[4], int64_t idx, int64_t C, const Chan8& ch,
+                                       const QuantCfg& cfg, uint32_t (&colw)[8]) {
     const float Qf = (float)cfg.Q;
 #pragma unroll
     for (int j = 0; j < 8; ++j) colw[j] = 0u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float v[8] = {a[i].x, a[i].y, a[i].z, a[i].w, b[i].x, b[i].y, b[i].z, b[i].w};
+        float4 a, b;
+        row(i, a, b);
+        const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
         U4 w{0u, 0u, 0u, 0u};
         if (SR && ok[i]) w = philox_block((uint64_t)(idx + i * C) >> 3, cfg);
         uint32_t lo = 0u, hi = 0u;
@@ -937,10 +940,19 @@ __device__ __forceinline__ void quant8(const float4 (&a)[4], const float4 (&b)[4
             if (j < 4) lo = __builtin_amdgcn_cvt_pk_u8_f32(qf, j, lo);
             else hi = __builtin_amdgcn_cvt_pk_u8_f32(qf, j - 4, hi);
         }
-        fold[i] = make_uint2(lo ^ 0x80808080u, hi ^ 0x80808080u);
+        emit(i, make_uint2(lo ^ 0x80808080u, hi ^ 0x80808080u));
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) colw[j] ^= 0x80808080u;
+}
+
+// The same with the rows loaded ahead and the folded codes kept.
+template <bool SR>
+__device__ __forceinline__ void quant8(const float4 (&a)[4], const float4 (&b)[4], const bool (&ok)[4], int64_t idx,
+                                       int64_t C, const Chan8& ch, const QuantCfg& cfg, uint32_t (&colw)[8],
+                                       uint2 (&fold)[4]) {
+    quant8<SR>([&](int i, float4& ra, float4& rb) { ra = a[i]; rb = b[i]; }, [&](int i, uint2 f) { fold[i] = f; }, ok, idx,
+               C, ch, cfg, colw);
 }
 
 // Row i's codes of the appended channels, at their columns ext_base + pos.
@@ -955,7 +967,10 @@ __device__ __forceinline__ void store_ext8(const Chan8& ch, const uint32_t (&col
 
 // Row-major or tile-major (TL) codes: tiles of 128 rows x 64 channels.  GRID:
 // q_t on the padded pixel grid (Wo and off multiples of 8; see launch_quantize).
-template <bool SR, bool TL, bool GRID = false>
+// AHEAD: a thread loads its 4 rows first and stores their folded codes last;
+// else it takes row after row, which needs 20 registers less and lets the other
+// waves' memory accesses run under the Philox words of stochastic codes.
+template <bool SR, bool TL, bool GRID, bool AHEAD>
 __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ x, int64_t M, int64_t C, int64_t ld,
                                                       const uint8_t* __restrict__ group,
                                                       const sq_scale* __restrict__ scale, QuantCfg cfg,
@@ -979,12 +994,15 @@ __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ 
         const int64_t ct = tile % ctiles, rt = tile / ctiles;
         const int64_t c0 = ct * TC + 8 * g8, m0 = rt * TR + 4 * rq;
         const bool cin = c0 < C;   // C % 8 == 0: all 8 channels or none
-        float4 a[4], b[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        auto load = [&](int i, float4& a, float4& b) {
             const float* src = x + min(m0 + i, M - 1) * ld + min(c0, C - 8);
-            a[i] = *reinterpret_cast<const float4*>(src);
-            b[i] = *reinterpret_cast<const float4*>(src + 4);
+            a = *reinterpret_cast<const float4*>(src);
+            b = *reinterpret_cast<const float4*>(src + 4);
+        };
+        float4 a[4], b[4];
+        if constexpr (AHEAD) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) load(i, a[i], b[i]);
         }
         if (tile == blockIdx.x) sc = tm.block_max ? tensor_scale(tm, tmax, (float)cfg.Q, sh_max) : *scale;
         const Chan8 ch = load_chan8(group, desc, c0, cin, meta_vec, sc.inv);
@@ -992,22 +1010,46 @@ __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ 
 #pragma unroll
         for (int i = 0; i < 4; ++i) ok[i] = cin && sc.flags == 0u && m0 + i < M;
         uint32_t colw[8];
-        uint2 fold[4];
-        quant8<SR>(a, b, ok, m0 * C + c0, C, ch, cfg, colw, fold);
-        if (q_fold) {
+        if constexpr (AHEAD) {
+            uint2 fold[4];
+            quant8<SR>(a, b, ok, m0 * C + c0, C, ch, cfg, colw, fold);
+            if (q_fold) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int64_t m = m0 + i;
-                if (m >= M) continue;
-                if (cin) {
-                    if (ch.any_ext)
-                        store_ext8(ch, colw, i, [&](int pos) { return q_fold + at_fold(m, ext_base + pos); });
-                    *reinterpret_cast<uint2*>(q_fold + at_fold(m, c0)) = fold[i];
-                } else if (TL && c0 < ext_base) {
-                    // K padding of the main columns
-                    *reinterpret_cast<uint2*>(q_fold + at_fold(m, c0)) = make_uint2(0u, 0u);
+                for (int i = 0; i < 4; ++i) {
+                    const int64_t m = m0 + i;
+                    if (m >= M) continue;
+                    if (cin) {
+                        if (ch.any_ext)
+                            store_ext8(ch, colw, i, [&](int pos) { return q_fold + at_fold(m, ext_base + pos); });
+                        *reinterpret_cast<uint2*>(q_fold + at_fold(m, c0)) = fold[i];
+                    } else if (TL && c0 < ext_base) {
+                        // K padding of the main columns
+                        *reinterpret_cast<uint2*>(q_fold + at_fold(m, c0)) = make_uint2(0u, 0u);
+                    }
                 }
             }
+        } else {
+            auto row = [&](int i, float4& ra, float4& rb) {
+                ra = rb = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (ok[i]) load(i, ra, rb);
+            };
+            auto emit = [&](int i, uint2 f) {
+                const int64_t m = m0 + i;
+                if (!q_fold || m >= M) return;
+                if (cin) {
+                    if (ch.any_ext) {
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const int pos = (ch.dw[j] >> 4) - 1, code = (int)((colw[j] >> (8 * i)) & 0xFFu) - 128;
+                            if (pos >= 0) q_fold[at_fold(m, ext_base + pos)] = (int8_t)(code * (1 << (ch.dw[j] & 15)));
+                        }
+                    }
+                    *reinterpret_cast<uint2*>(q_fold + at_fold(m, c0)) = f;
+                } else if (TL && c0 < ext_base) {
+                    *reinterpret_cast<uint2*>(q_fold + at_fold(m, c0)) = make_uint2(0u, 0u);
+                }
+            };
+            quant8<SR>(row, emit, ok, m0 * C + c0, C, ch, cfg, colw);
         }
         if (q_t) {
 #pragma unroll
@@ -1629,9 +1671,15 @@ hipError_t launch_quantize(const float* x, int64_t M, int64_t C, int64_t ld, con
             hipLaunchKernelGGL(k, g8, dim3(kBlock), 0, s, x, M, C, ld, group, scale, cfg, q_fold, ld_fold, q_t, ld_t, desc,
                                eb, mv, tm, pg);
         };
-        if (grid8) run(sr ? k_quantize8<true, false, true> : k_quantize8<false, false, true>);
-        else if (tiled) run(sr ? k_quantize8<true, true> : k_quantize8<false, true>);
-        else run(sr ? k_quantize8<true, false> : k_quantize8<false, false>);
+        // stochastic codes row by row (see k_quantize8), but not with appended
+        // windows beyond the last-level cache, where the reads are the bound
+        const bool ahead = !sr || (windows && (uint64_t)M * (uint64_t)ld * sizeof(float) > kLastLevelCacheBytes);
+        if (grid8) run(!sr ? k_quantize8<false, false, true, true>
+                       : ahead ? k_quantize8<true, false, true, true> : k_quantize8<true, false, true, false>);
+        else if (tiled) run(!sr ? k_quantize8<false, true, false, true>
+                            : ahead ? k_quantize8<true, true, false, true> : k_quantize8<true, true, false, false>);
+        else run(!sr ? k_quantize8<false, false, false, true>
+                 : ahead ? k_quantize8<true, false, false, true> : k_quantize8<true, false, false, false>);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)std::min<int64_t>(n_tiles(tc, tr), kQuantMaxBlocks));
