@@ -934,6 +934,169 @@ __global__ __launch_bounds__(T::kThreads, 2) void k_gemm_pipe(GemmArgs p, int64_
 }
 
 // ---------------------------------------------------------------------------
+// Input gradient of a "same" stride-1 convolution (Ho = H, Wo = W) with the
+// rows of q_fold staged once per K chunk.  Tap (r, s) of input pixel p reads
+// q_fold row p + d, d = (PH - r) W + (PW - s), so the rows a tile of BM
+// pixels needs for all taps form the contiguous window [p0 - E, p0 + BM + E),
+// E = PH W + PW.  Per 64-column chunk of the fold's flat K sequence the block
+// loads that window and the chunk's weights of every tap into LDS once, then
+// runs one round of MFMAs per tap on rows of the window shifted by d.  A tap
+// whose output pixel lies outside the image (its row belongs to another image
+// row or image) adds nothing: that lane's operand fragment is cleared.  The
+// K order (chunk-major, tap-minor) and the Horner shifts at region starts are
+// those of the per-tap kernel.  Bound by LDS and by its unpipelined staging,
+// which several rounds of blocks hide; the window is read once, where the
+// per-tap kernel's 256 x 64 tiles read it once per tap.  launch_conv_dgrad says
+// which of the two a narrow output takes.
+// ---------------------------------------------------------------------------
+constexpr int kHaloBM = 256, kHaloExtra = 128, kHaloWaves = 4, kHaloMaxTaps = 9;
+
+template <bool HORNER>
+__global__ __launch_bounds__(64 * kHaloWaves) void k_conv_halo(GemmArgs p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int BM = kHaloBM, BN = 64, BK = 64, WR = kHaloBM + kHaloExtra;   // window rows
+    constexpr int kA = WR * BK;
+    __shared__ __attribute__((aligned(1024))) int8_t smem[kA + kHaloMaxTaps * BN * BK];
+    using MF = Mfma<16>;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    const int64_t m0 = (int64_t)blockIdx.x * BM, n0 = (int64_t)blockIdx.y * BN;
+    const int taps = p.taps, KW = p.cv_KW, H = (int)p.cv_H, W = (int)p.cv_W;
+    const int E = p.cv_PH * W + p.cv_PW;
+    const FoldView fv = fold_view(p, BK);
+    const int n_main = (int)(p.K / BK);
+    const int n_chunks = fv.n_ext + n_main;
+
+    constexpr int kRsrcFlags = 0x00020000;   // raw byte buffer, gfx9 data format
+    auto rsrc = [&](const int8_t* base, int64_t rows, int64_t ld) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(base), (short)0,
+                                                 (int)min(rows * ld, (int64_t)0x7FFFFFFF), kRsrcFlags);
+    };
+    const __amdgpu_buffer_rsrc_t rA = rsrc(p.A, p.a_rows, p.lda), rB = rsrc(p.B, p.Ng, p.ldb);
+    const int lr = lane >> 2;
+    // window rows: instruction i of this wave fills rows (i * waves + wv) * 16 .. + 15;
+    // rows before the tensor get an offset past the end of the buffer (zeros)
+    constexpr int kWin = WR / 16 / kHaloWaves;
+    uint32_t offW[kWin];
+#pragma unroll
+    for (int i = 0; i < kWin; ++i) {
+        const int w = (i * kHaloWaves + wv) * 16 + lr;
+        const int64_t g = m0 - E + w;
+        offW[i] = g >= 0 ? (uint32_t)(g * p.lda) + 16u * (uint32_t)((lane & 3) ^ swz(w)) : 0x80000000u;
+    }
+    // weights: this wave fills rows wv * 16 .. + 15 of each tap's 64-row block
+    const int brow = wv * 16 + lr;
+    const uint32_t offBw = (uint32_t)(min(n0 + brow, p.Ng - 1) * p.ldb);
+
+    // the input pixel of each of this lane's 4 accumulator rows (one per
+    // 16-row MFMA block of the wave's 64 rows)
+    const int lrow = lane % 16, lc = lane / 16;
+    int ih[4], iw[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t pix = min(m0 + wv * 64 + i * 16 + lrow, p.Mg - 1);
+        const int hw = (int)(pix % ((int64_t)H * W));
+        ih[i] = hw / W;
+        iw[i] = hw - ih[i] * W;
+    }
+
+    v4i acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+
+    HornerSteps hs(p);
+    for (int f = 0; f < n_chunks; ++f) {
+        // stage the chunk: the row window of q_fold and every tap's weights
+        const bool ext = HORNER && fv.is_ext(f, n_main);
+        const int kc = ext ? (int)fv.ext_col(f, n_main) : (f - fv.h_tiles) * BK;
+        const __amdgpu_buffer_rsrc_t ra = ext ? rsrc(p.extA, p.a_rows, p.ld_extA) : rA;
+        __syncthreads();   // the previous chunk's reads of LDS are done
+#pragma unroll
+        for (int i = 0; i < kWin; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_void_t*)(smem + (i * kHaloWaves + wv) * 1024), 16,
+                                                     offW[i], kc, 0, 0);
+        for (int tau = 0; tau < taps; ++tau) {
+            const int row = tau * BN + brow;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rB, (lds_void_t*)(smem + kA + (tau * BN + wv * 16) * BK), 16,
+                offBw + 16u * (uint32_t)((lane & 3) ^ swz(row)), (f * taps + tau) * BK, 0, 0);
+        }
+        wait_vm<0>();
+        __syncthreads();
+        if (HORNER && (int64_t)f * BK == hs.col) {
+            const int sft = hs.advance();
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] = acc[i][j] << sft;
+        }
+        for (int tau = 0, tr = 0, ts = 0; tau < taps; ++tau) {
+            const int d = (p.cv_PH - tr) * W + (p.cv_PW - ts);
+            v4i fa[4], fb[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int w = wv * 64 + i * 16 + lrow + E + d;
+                const v4i v = *reinterpret_cast<const v4i*>(&smem[w * BK + 16 * (lc ^ swz(w))]);
+                const int oh = ih[i] + p.cv_PH - tr, ow = iw[i] + p.cv_PW - ts;
+                const bool ok = (unsigned)oh < (unsigned)H && (unsigned)ow < (unsigned)W;
+                fa[i] = ok ? v : v4i{0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = tau * BN + j * 16 + lrow;
+                fb[j] = *reinterpret_cast<const v4i*>(&smem[kA + r * BK + 16 * (lc ^ swz(r))]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[i][j] = MF::run(fb[j], fa[i], acc[i][j]);
+            if (++ts == KW) { ts = 0; ++tr; }
+        }
+    }
+
+    // epilogue: alpha = step_G * step_W * 2^-(N_G - 1), the fold's final shift
+    const int fsh = HORNER ? fv.fshift : 0;
+    float alpha = 0.0f;
+    if (p.out) {
+        const sq_scale gs = *p.gs, os = *p.os;
+        alpha = __fmul_rn(__fmul_rn(gs.step, os.step), pow2f(-(p.num_groups - 1)));
+    }
+    const bool vec_acc = p.acc && ((p.ld_acc & 3) == 0) && ((reinterpret_cast<uintptr_t>(p.acc) & 15) == 0);
+    const bool vec_out = p.out && ((p.ld_out & 3) == 0) && ((reinterpret_cast<uintptr_t>(p.out) & 15) == 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t ii = m0 + wv * 64 + i * 16 + lrow;
+        if (ii >= p.Mg) continue;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t jj = n0 + j * 16 + lc * 4;
+            if (jj >= p.Ng) continue;
+            const int vv[4] = {acc[i][j][0] << fsh, acc[i][j][1] << fsh, acc[i][j][2] << fsh, acc[i][j][3] << fsh};
+            const bool full = jj + 4 <= p.Ng;
+            if (p.acc) {
+                int32_t* dst = p.acc + ii * p.ld_acc + jj;
+                if (vec_acc && full) *reinterpret_cast<int4*>(dst) = make_int4(vv[0], vv[1], vv[2], vv[3]);
+                else
+                    for (int e = 0; e < 4; ++e)
+                        if (jj + e < p.Ng) dst[e] = vv[e];
+            }
+            if (p.out) {
+                float* dst = p.out + ii * p.ld_out + jj;
+                const float ff[4] = {__fmul_rn((float)vv[0], alpha), __fmul_rn((float)vv[1], alpha),
+                                     __fmul_rn((float)vv[2], alpha), __fmul_rn((float)vv[3], alpha)};
+                if (vec_out && full) *reinterpret_cast<float4*>(dst) = make_float4(ff[0], ff[1], ff[2], ff[3]);
+                else
+                    for (int e = 0; e < 4; ++e)
+                        if (jj + e < p.Ng) dst[e] = ff[e];
+            }
+        }
+    }
+#endif
+}
+
+// ---------------------------------------------------------------------------
 // Same-size convolution input gradient (Ho = H, Wo = W), streaming: one
 // 64-column K chunk (C_out <= 64, every shift in one window) and C_in <= 64.
 // Each block owns a contiguous range of input pixels and walks it in steps of
@@ -1427,7 +1590,7 @@ constexpr TileCost kConvCost[] = {{128, 128, 2, 0.36f, 0.21f, 2.0f, 0.110f}, {64
                                   {64, 64, 5, 0.255f, 0.18f, 2.0f, 0.080f}};
 Pick best_conv_tile(int64_t Mg, int64_t Ng, int64_t ktiles) {
     const bool narrow = Ng <= PipeNarrow::BN;   // 128-column tiles would be half empty
-    if (narrow && 2 * ((Mg + PipeNarrow::BM - 1) / PipeNarrow::BM) >= kCUs) return Pick::kNarrow;
+    if (narrow && 4 * ((Mg + PipeNarrow::BM - 1) / PipeNarrow::BM) >= 3 * kCUs) return Pick::kNarrow;
     constexpr Pick kPicks[] = {Pick::kSmall, Pick::kFlat, Pick::kTiny};
     int best = 2;
     float t = 0.0f;
@@ -2084,6 +2247,20 @@ hipError_t launch_conv_dgrad(const GemmArgs& a0, int8_t* bc, int64_t ld_bc, hipS
     a.B = bc;
     a.ldb = ld_bc;
     if (!fits(a.Ng, a.ldb)) return hipErrorInvalidValue;
+    // Windows of 7 to 9 taps and narrow outputs of many rows: us, per-tap kernel
+    // -> staged window: 64 x 56 x 56, 128 -> 64 channels 40.9 -> 39.2, with fold
+    // windows 55.7 -> 50.6, 128 -> 16 48.5 -> 39.3; 84 x 28 x 28, 128 -> 64 20.1 ->
+    // 21.5, with windows 27.7 -> 26.4, 256 -> 16 24.3 -> 22.8; 64 x 28 x 28, 256 -> 32
+    // with windows 27.8 -> 25.4; 64 x 56 x 56 and 3 x 1 taps 35.7 -> 41.5, 1 x 7
+    // taps 44.5 -> 39.4.
+    const int64_t halo_rows = a.extA ? 49152 : a.Ng <= 48 ? 65536 : 98304;
+    if (same && a.Ng <= 64 && a.Mg >= halo_rows && a.taps >= 7 && a.taps <= kHaloMaxTaps &&
+        2 * ((int64_t)a.cv_PH * a.cv_W + a.cv_PW) <= kHaloExtra) {
+        const dim3 grid((unsigned)((a.Mg + kHaloBM - 1) / kHaloBM));
+        if (a.extA) hipLaunchKernelGGL(k_conv_halo<true>, grid, dim3(64 * kHaloWaves), 0, s, a);
+        else hipLaunchKernelGGL(k_conv_halo<false>, grid, dim3(64 * kHaloWaves), 0, s, a);
+        return hipGetLastError();
+    }
     switch (best_conv_tile(a.Mg, a.Ng, a.K / 64 * a.taps)) {
         case Pick::kSmall: return launch_conv_tile<PipeSmall>(a, s);
         case Pick::kFlat: return launch_conv_tile<PipeFlat>(a, s);

@@ -1,7 +1,7 @@
-"""The per-tap conv input gradient on each of its tile shapes, at the edges of
-its tap masks: windows up to 15 x 15, one-sided padding, images smaller than the
-window, rows of several images in one tile, and all fold cases, against the
-oracle."""
+"""The conv input gradient of the per-tap kernel, on each of its tile shapes, and
+of the staged window, at the edges of their tap masks: windows up to 15 x 15,
+one-sided padding, images smaller than the window, rows of several images in one
+tile, and all fold cases, against the oracle."""
 import numpy as np
 import pytest
 
@@ -28,7 +28,14 @@ CASES = [  # N, H, W, C_out, C_in, KH, KW, PH, PW, bits
     (5, 7, 7, 130, 200, 3, 3, 1, 1, 8),       # images of 49 pixels
     (40, 14, 14, 72, 136, 3, 3, 1, 1, 6),     # 64 x 128 tiles
     (64, 20, 20, 66, 136, 3, 3, 0, 2, 4),     # 128 x 128 tiles, unequal padding
-    (16, 50, 45, 80, 24, 3, 3, 1, 1, 6),      # 256 x 64 tiles
+    (16, 50, 45, 80, 24, 3, 3, 1, 1, 6),      # a narrow output, 64 x 64 tiles
+    (9, 90, 66, 70, 24, 3, 3, 1, 1, 6),       # 256 x 64 tiles
+    # the staged window: its widest rows, images smaller than a tile with several
+    # fold windows, 9 taps in a row, every dimension ragged
+    (12, 90, 62, 70, 33, 3, 3, 1, 1, 4),
+    (4099, 4, 4, 129, 20, 3, 3, 1, 1, 8),
+    (260, 16, 16, 65, 64, 1, 9, 0, 4, 6),
+    (20, 62, 55, 64, 63, 1, 7, 0, 3, 8),
 ]
 
 
