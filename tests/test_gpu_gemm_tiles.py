@@ -80,6 +80,71 @@ def test_narrow_forward(sq, M, C_in, C_out, bits):
     assert torch.equal(Y, ref.float() * ((c.scale[2] * ws[:, 2]) * 0.125)[None, :])
 
 
+# 256 x 256 tiles with every dimension ragged, and products that take two
+# launches, the rows of whole rounds of large tiles and the rest: plan of dX, dW
+LARGE = [
+    (10976, 3394, 1025, (256, 256, 0), (128, 128, 0)),
+    (3332, 3488, 3658, (256, 256, 0), (256, 256, 0)),
+    (4386, 1538, 4048, (128, 128, 4096), (128, 128, 0)),
+    (1565, 9733, 1748, (128, 128, 0), (128, 128, 9216)),
+    (3233, 3131, 5768, (128, 384, 2816), (128, 384, 2816)),
+]
+
+
+@pytest.mark.parametrize("M,C_out,C_in,plan_dx,plan_dw", LARGE)
+@pytest.mark.parametrize("bits,tiled", [(4, False), (6, True), (8, False)])
+def test_large_tiles_and_row_splits(sq, M, C_out, C_in, plan_dx, plan_dw, bits, tiled):
+    assert gemm_plan(sq, M, C_in, C_out) == plan_dx
+    assert gemm_plan(sq, C_out, C_in, M) == plan_dw
+    assert sq.sq_gemm_wgrad_workspace_size(M, C_out, C_in, sq.Params.make(bits)) == 0   # K not split
+    test_every_tile_and_split(sq, M, C_out, C_in, bits, tiled)
+
+
+# code matrices of 2^31 bytes and more (long rows), past the pipelined kernel's
+# offsets: the register-staged kernel's two tiles, with fold windows, K split
+# and the ranged product's separate maxima
+@pytest.mark.parametrize("M,C_out,C_in,bits,ld_fold,ld_t", [
+    (130, 40, 200, 8, 1 << 24, 1 << 26),
+    (3332, 3488, 3658, 4, 655360, 655360),
+    (20001, 130, 72, 6, 114688, 1 << 24),
+])
+def test_operands_past_31_bits(sq, M, C_out, C_in, bits, ld_fold, ld_t):
+    import torch
+    print(f"past 31 bits M={M} C_out={C_out} C_in={C_in} b={bits}", flush=True)
+    assert M * ld_fold >= 1 << 31 and C_out * ld_t >= 1 << 31
+    g = torch.Generator(device="cuda").manual_seed(M + bits)
+    dY = torch.randn(M, C_out, generator=g, device="cuda") * torch.exp2(-6 * torch.rand(C_out, generator=g, device="cuda"))
+    c = sq.quantize_grad(dY, bits, 4)
+    wq_t, ws = sq.quantize_tensor(torch.randn(C_out, C_in, generator=g, device="cuda"), 8)
+    xq_t, xs = sq.quantize_tensor(torch.randn(M, C_in, generator=g, device="cuda"), 8)
+
+    def far(t, ld):   # the same codes in rows of ld bytes
+        out = torch.empty((t.shape[0], ld), dtype=torch.int8, device="cuda")
+        out[:, :t.shape[1]] = t
+        return out
+
+    q_fold, q_t = c.q_fold, c.q_t
+    A0, dX0 = sq.gemm_dgrad(c, wq_t, ws, want_acc=True)
+    B0, dW0 = sq.gemm_wgrad(c, xq_t, xs, want_acc=True)
+    c.q_fold = far(q_fold, ld_fold)
+    A, dX = sq.gemm_dgrad(c, wq_t, ws, want_acc=True)
+    ranges = torch.empty(sq.sq_gemm_dgrad_range_slabs(M), C_in, dtype=torch.int32, device="cuda")
+    dX_r = torch.empty_like(dX)
+    w = torch.empty(max(256, sq.sq_gemm_dgrad_workspace_size(M, C_out, C_in, c.params)), dtype=torch.uint8, device="cuda")
+    sq.sq_gemm_dgrad_ranged(c.q_fold, c.layout, c.group, c.scale, wq_t, ws, M, C_out, C_in, c.params, None, dX_r, ranges, w)
+    c.q_fold, c.q_t = q_fold, far(q_t, ld_t)
+    B, dW = sq.gemm_wgrad(c, xq_t, xs, want_acc=True)
+    torch.cuda.synchronize()
+    q = q_t[:, :M].t().double()
+    assert torch.equal(A, ((q * torch.exp2(3.0 - c.group.double())) @ wq_t[:, :C_out].t().double()).to(torch.int32))
+    assert torch.equal(B, (q.t().contiguous() @ xq_t[:, :M].t().double()).to(torch.int32))
+    assert torch.equal(A, A0) and torch.equal(B, B0)
+    assert torch.equal(dX, dX0) and torch.equal(dX_r, dX0) and torch.equal(dW, dW0)
+    top = torch.zeros(ranges.shape[0] * 32, C_in, device="cuda")
+    top[:M] = dX.abs()
+    assert torch.equal(ranges.view(torch.float32), top.view(-1, 32, C_in).amax(1))
+
+
 @pytest.mark.parametrize("M,C_out,C_in", LAYERS)
 @pytest.mark.parametrize("bits,tiled", [(4, False), (6, True), (8, False)])
 def test_every_tile_and_split(sq, M, C_out, C_in, bits, tiled):
