@@ -112,9 +112,9 @@ sq_status check_dims(int64_t rows, int64_t cols, const char* what) {
     return SQ_OK;
 }
 
-// quantizer scratch: slab maxima [slabs, C] followed by the channel ranges [C]
+// quantizer scratch: outputs of the abs-max pass (slab and block maxima) and the
+// finalize's shift counts, or partial channel ranges, group maxima and counts
 size_t quant_ws_bytes(int64_t M, int64_t C) { return (size_t)round_up(std::max<int64_t>(colmax_workspace_words(M, C), 1) * 4, 256); }
-
 
 // split-K partials of the weight gradient
 size_t wgrad_ws_bytes(int splits, int64_t C_out, int64_t C_in) {

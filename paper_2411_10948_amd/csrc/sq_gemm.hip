@@ -1,22 +1,25 @@
 // Integer GEMMs of the ShiftQuant backward pass for gfx950.
 //
-// One kernel template serves both products as C[i, j] = sum_k A[i, k] * B[j, k]
-// with both operands K-contiguous int8:
+// Both products are C[i, j] = sum_k A[i, k] * B[j, k] with both operands
+// K-contiguous int8:
 //   dgrad: A = shift-folded gradient codes [M, C_out(+appended)],
 //          B = W^T codes [C_in, C_out]              -> dX [M, C_in]
 //   wgrad: A = transposed gradient codes [C_out, M],
 //          B = X^T codes [C_in, M]                   -> dW [C_out, C_in]
-// int32 accumulation on the matrix cores (v_mfma_i32_32x32x32_i8 or
-// v_mfma_i32_16x16x64_i8), block tiles of WM x WN waves, K tiles of BK bytes
-// double-buffered in LDS (rows padded by 16 bytes, which keeps the 16-byte
-// fragment reads free of bank conflicts), and the dequantization of
-// Eq. "dq_mm_f" fused into the epilogue.
+// int32 accumulation on the matrix cores (v_mfma_i32_16x16x64_i8, in one
+// configuration v_mfma_i32_32x32x32_i8), the dequantization of Eq. "dq_mm_f"
+// fused into the epilogue.  k_gemm_pipe, the pipelined kernel, takes nearly all
+// products, with a tile and K split by a cost model; k_gemm, register-staged,
+// those of many rows with a short K (product_tile) and operands past 31-bit
+// offsets: block tiles of WM x WN waves, K tiles of BK bytes double-buffered in
+// LDS (rows padded by 16 bytes, which keeps the 16-byte fragment reads free of
+// bank conflicts).
 //
 // ShiftMM (Sec. 3.2) shifts every product by the shift of its inner index
 // before accumulation.  The quantizer stores each channel's code already
 // shifted within a window of shifts that fits int8; channels of the windows
-// other than the main one sit in appended K columns.  This kernel visits the
-// windows in descending order and shifts the accumulator left by the
+// other than the main one sit in appended K columns.  The kernels visit the
+// windows in descending order and shift the accumulator left by the
 // difference of window bases at each window start and by the last base at the
 // end (Horner's rule), so the result equals sum_c code * w << (N_G - 1 - g_c)
 // exactly.
@@ -55,7 +58,7 @@ struct TileCfg {
 };
 
 // The configurations the library launches.
-using CfgSmall = TileCfg<128, 128, 64, 2, 2, 32>;   // small/skinny outputs, split-K
+using CfgSmall = TileCfg<128, 128, 64, 2, 2, 32>;   // 40 KB of LDS: four blocks per CU
 using CfgLarge = TileCfg<256, 256, 64, 4, 2, 16>;   // large products (matrix-core bound)
 
 // Zero the bytes of a 16-byte chunk at positions >= nvalid (0 < nvalid < 16).
@@ -407,7 +410,7 @@ __global__ __launch_bounds__(T::kThreads) void k_gemm(GemmArgs p, int64_t tiles_
 }
 
 // ---------------------------------------------------------------------------
-// Pipelined variant for K-aligned operands: 64-byte K tiles move from global
+// Pipelined kernel: 64-byte K tiles move from global
 // memory straight into a ring of STAGES LDS buffers with the gfx950 direct
 // loads (buffer_load_dwordx4 ... lds, 16 bytes per lane, a fixed per-lane
 // offset and a scalar K offset), so STAGES - 1 tiles are in flight without
@@ -422,7 +425,8 @@ __global__ __launch_bounds__(T::kThreads) void k_gemm(GemmArgs p, int64_t tiles_
 // HORNER = false compiles out the accumulator shifts of the fold (wgrad, and
 // dgrads whose fold has one window), which lets the accumulators live in the
 // matrix-core registers for the whole loop.
-// Requirements (checked by the launcher): lda/ldb multiples of 16, 16-byte aligned operands, offsets below 2^31.
+// Requirements (checked by the launcher): lda/ldb multiples of 16, 16-byte aligned
+// operands, offsets below 2^31.
 // ---------------------------------------------------------------------------
 template <int BM_, int BN_, int WM_, int WN_, int MF_, int STAGES_>
 struct PipeCfg {
@@ -796,8 +800,8 @@ __global__ __launch_bounds__(T::kThreads, 2) void k_gemm_pipe(GemmArgs p, int64_
     // would cover 16 rows x 64 bytes: half lines.  Each 16-row fragment row of
     // the wave therefore goes through LDS (the ring, free after the last
     // barrier; a region per wave, whose LDS operations complete in order) and
-    // leaves as whole 128-byte lines (16384 x 3072 outputs, K = 768: 93.9 -> 90.5
-    // us; the 8192 x 11008 x 4096 step, whose dW stores are nontemporal: 715.9
+    // leaves as whole 128-byte lines (the 16384 x 768 -> 3072 forward step 158.7 ->
+    // 152.7 us; the 8192 x 11008 x 4096 step, whose dW stores are nontemporal: 715.9
     // -> 698.9 us).
     const int fsh = HORNER ? fv.fshift : 0;
     const bool nt = p.epi_mode == 1;   // dW: see store_f4

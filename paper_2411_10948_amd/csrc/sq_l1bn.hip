@@ -414,7 +414,9 @@ __device__ __forceinline__ void unpack4(uint32_t w, int (&out)[4]) {
 // (a few channels per thread, into LDS), and block 0 writes them to ch and
 // layer.  As a launch of one block of its own that took 3.9 us and a gap;
 // here 0 to 1.2 us (200704 x 64: the step 131.9 -> 128.5 us; 12544 x 256: 67.9 ->
-// 65.6).
+// 65.6; the forward alone at 12544 x 512 33.9 -> 31.0, 16384 x 768 44.4 -> 41.6,
+// 800 x 1024 38.3 -> 35.4, 12544 x 1024 46.2 -> 43.0, where a thread takes 4
+// channels; more would not fit one block column).
 constexpr int kFuseC = 1024;
 template <bool BWD, bool PAR = false>
 __global__ __launch_bounds__(kBnThreads) void k_bn_apply(const int8_t* __restrict__ a, int64_t lda,

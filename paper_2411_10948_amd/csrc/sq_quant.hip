@@ -603,8 +603,9 @@ __global__ __launch_bounds__(kPlaceThreads) void k_final_place(const uint8_t* __
 }
 
 // Scale of a per-tensor quantization, taken by every block of the quantize
-// pass from the abs-max pass's block maxima (at most about 520 words, unless
-// there are more than 130,000 channels); block 0 writes it out.  A launch of
+// pass from the abs-max pass's block maxima (at most about 520 words up to
+// 131,072 channels, or 32,768 where the rows are not 16-byte aligned, then one per
+// 256 or 64 channels); block 0 writes it out.  A launch of
 // its own for this took 2.1 to 3.9 us and a gap.  In two parts, so that the
 // block maxima are loaded first and combined while the tile's rows are in
 // flight.  sh: 4 words of LDS.
