@@ -292,6 +292,23 @@ def test_quantize_tensor_parity(sq, transpose, shape, bits):
     assert h["bits"][:3] == [_f32bits(s_ref["r_max"]), _f32bits(s_ref["inv0"]), _f32bits(s_ref["d0"])]
 
 
+# rows that are not 16-byte aligned and very wide: a block maximum per 64
+# columns, 4096 of them or more, so that a launch of its own takes the largest
+@pytest.mark.parametrize("cols,at", [(262143, 262142), (262145, 262144), (262145, 0), (300001, 299999)])
+@pytest.mark.parametrize("transpose", [0, 1])
+def test_quantize_tensor_many_maxima(sq, cols, at, transpose):
+    import torch
+    rng = np.random.default_rng(cols + at)
+    T = (rng.standard_normal((2, cols)) * 0.02).astype(np.float32)
+    T[at % 2, at] = -3.5
+    q, s = sq.quantize_tensor(_dev(T), 8, transpose=bool(transpose))
+    torch.cuda.synchronize()
+    q_ref, s_ref = oracle.quantize_tensor(T, 8)
+    got = q[:, :2].t() if transpose else q[:, :cols]
+    assert np.array_equal(got.cpu().numpy(), q_ref)
+    assert sq.scale_to_host(s)["bits"][:3] == [_f32bits(s_ref["r_max"]), _f32bits(s_ref["inv0"]), _f32bits(s_ref["d0"])]
+
+
 # ---------------------------------------------------------------------------
 # GEMMs on small layers (several tiles, ragged tails, every fold case)
 # ---------------------------------------------------------------------------
