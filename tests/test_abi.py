@@ -78,6 +78,15 @@ def test_mlp_input_gradient_plan(sq):
     assert gemm_plan(sq, 16384, 768, 3072) == (128, 384, 0)
 
 
+def test_long_product_plan(sq):
+    # 256 x 256 over 256 x 128 for a long K, unless the last round is nearly empty
+    from tests.gemm_plan import gemm_plan
+    assert gemm_plan(sq, 8192, 11008, 4096)[0:2] == (256, 256)
+    assert gemm_plan(sq, 9856, 8064, 2944, ext=True)[0:2] == (256, 256)
+    assert gemm_plan(sq, 14466, 2161, 1971) == (256, 128, 0)
+    assert gemm_plan(sq, 16384, 3072, 768) == (256, 128, 0)
+
+
 def test_narrow_product_plan(sq):
     # many rows, a short K: bound by the blocks' prologues and the stores
     from tests.gemm_plan import gemm_plan

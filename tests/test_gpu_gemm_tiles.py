@@ -19,7 +19,7 @@ def sq():
 
 LAYERS = [  # M, C_out, C_in: tile of dX; tile and splits of dW
     (8200, 1100, 4096),     # 128 x 192; 128 x 192
-    (8192, 2100, 4096),     # 256 x 128; 128 x 384
+    (8192, 2100, 4096),     # 256 x 256; 128 x 384
     (16384, 3072, 768),     # 128 x 384; 128 x 384 in 5
     (12544, 256, 1024),     # 256 x 128; 64 x 64 in 8
     (16000, 780, 770),      # 256 x 128; 128 x 128 in 5
