@@ -1500,8 +1500,8 @@ bool pipe_ok(const GemmArgs& a) {
 // products alone, each with every tile and split: a pick costs 0.8 % of a step
 // (1.5 % of a product) more than the best of them.  Rules on the number of
 // 256 x 256 tiles, with 128 x 128 tiles below 128 of them, cost 16 % of a
-// product (K = 4096, 256 x 1024: 20.6 us, now 11.8; 16384 x 3072, K = 768:
-// 79.2 us, now 68.8) and 28 % of a split one (768 x 768, K = 3152: 18.0 us, now
+// product (K = 4096, 256 x 1024: 20.6 us, now 11.8; 16384 x 3072, K = 768, the
+// call: 73.0 us, now 65.1, with a fold window 86.0, 75.9) and 28 % of a split one (768 x 768, K = 3152: 18.0 us, now
 // 11.7).  Constants fitted to the products alone, hot in the caches, picked
 // small tiles for long products that read HBM (MLP wgrad 45 -> 54 us).
 enum class Pick { kLarge, kTall, kDuo, kMid, kSmall, kFlat, kTiny, kNarrow, kStaged };
@@ -1566,7 +1566,9 @@ Pick best_tile(int64_t Mg, int64_t Ng, int64_t K, int splits, float* cost = null
 // (fitted to longer ones) prices wrongly: such a launch is bound by its blocks'
 // prologues and its stores, so fewer or lighter blocks win.  kStaged: the
 // register-staged kernel's 128 x 128 (40 KB of LDS, direct stores), not for
-// tile-major operands or ranges; ext: with appended fold windows.  us, the
+// tile-major operands or ranges, nor for more than 16 columns in rows that are not
+// 16-byte aligned, whose direct stores go word by word (254302 x 241, K = 64: 180 us,
+// 64 x 128 106; x 10 18.4, 64 x 64 24.0); ext: with appended fold windows.  us, the
 // model's tile -> this rule's:
 //   400000 x 16, K = 16: 35.1 -> 17.3 staged; x 48, K = 64: 25.6 -> 24.6 staged,
 //   K = 128: 26.7 tiny (staged 30.7); x 128, K = 16: 40.8 -> 37.3 staged, but
@@ -1592,7 +1594,9 @@ Pick product_tile(int64_t Mg, int64_t Ng, int64_t K, int splits, bool ext, bool 
     const bool wide_ok = Ng > 64 && Mg > kVeryManyRows && (!ext || Ng <= 96);
     if (staged_ok && ((Ng <= 32 && K <= 128) || (K <= 64 && (Ng <= 48 || wide_ok)))) return Pick::kStaged;
     if (Ng <= 64) return Mg <= kVeryManyRows ? Pick::kNarrow : Pick::kTiny;
-    return K <= 128 ? Pick::kDuo : p;
+    // enough rows for a 256 x 128 tile on every CU (40488 x 128, K = 64, windows: 15.0
+    // us, 128 x 128 14.1)
+    return K <= 128 && Mg > PipeDuo::BM * (kCUs - 1) ? Pick::kDuo : p;
 }
 
 // Tile of the per-tap convolution: at most 64 columns take 256 x 64 where that
@@ -1722,13 +1726,13 @@ int wgrad_splits(int64_t M, int64_t C_out, int64_t C_in) {
     return best;
 }
 
-// What launch_gemm runs for a product of row-major operands, for tests that pin
-// a tile (not part of the public header): the tile's rows and columns (0: the
+// What launch_gemm runs for row-major operands and dense outputs, for tests that
+// pin a tile (not part of the public header): the tile's rows and columns (0: the
 // register-staged kernel), and the rows of the first of two launches (0: one
 // launch).  ext: with appended fold windows.
 extern "C" void sq_internal_gemm_plan(int64_t Mg, int64_t Ng, int64_t K, int32_t splits, int32_t ext, int32_t* bm,
                                       int32_t* bn, int64_t* first_rows) {
-    const Pick p = product_tile(Mg, Ng, K, std::max(1, splits), ext != 0, true);
+    const Pick p = product_tile(Mg, Ng, K, std::max(1, splits), ext != 0, Ng <= 16 || Ng % 4 == 0);
     const bool narrow = p == Pick::kNarrow;
     *bm = p == Pick::kStaged ? 0 : narrow ? PipeNarrow::BM : kTileCost[(int)p].bm;
     *bn = p == Pick::kStaged ? 0 : narrow ? PipeNarrow::BN : kTileCost[(int)p].bn;
@@ -1759,7 +1763,9 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
     // tile-major operands: the pipelined kernel only, no convolution
     if (a.tiled && (!pipe || a.taps || a.kseg)) return hipErrorInvalidValue;
     if (a.kseg && (!pipe || a.splits > 1 || a.layout)) return hipErrorInvalidValue;   // pipelined kernel only
-    const bool staged_ok = !a.tiled && !a.kseg && !a.ranges;
+    auto quads = [](const void* q, int64_t ld) { return !q || (ld % 4 == 0 && (reinterpret_cast<uintptr_t>(q) & 15) == 0); };
+    const bool staged_ok = !a.tiled && !a.kseg && !a.ranges &&
+                           (a.Ng <= 16 || (quads(a.out, a.ld_out) && quads(a.acc, a.ld_acc)));
     const Pick p = product_tile(a.Mg, a.Ng, a.K, std::max(1, a.splits), a.extA != nullptr, staged_ok);
     if (pipe && a.splits <= 1 && !a.ranges && !a.part && !a.taps && !a.kseg) {
         const int64_t rows = large_rows(a.Mg, a.Ng, a.K);

@@ -41,15 +41,19 @@ NARROW = [
     (33001, 128, 32, STAGED, STAGED),
     (33001, 64, 48, STAGED, STAGED),
     (262145, 30, 96, STAGED, STAGED),
-    (262145, 64, 97, STAGED, WIDE),
-    (70001, 48, 129, STAGED, STAGED),
+    (262145, 64, 100, STAGED, WIDE),
+    (262145, 64, 97, WIDE, WIDE),             # rows that are not 16-byte aligned
+    (70001, 48, 132, STAGED, STAGED),
+    (70001, 64, 129, (64, 128), (64, 128)),
+    (33001, 64, 30, (256, 64), (256, 64)),
+    (33001, 64, 13, STAGED, STAGED),
     (190001, 17, 300, STAGED, WIDE),
     (40001, 129, 32, (256, 64), (256, 64)),
     (33333, 65, 48, (256, 64), (256, 64)),
     (32769, 200, 64, (256, 64), (256, 64)),
     (262145, 96, 49, (64, 64), (64, 64)),
-    (50001, 128, 65, WIDE, WIDE),
-    (40000, 100, 128, WIDE, WIDE),
+    (70001, 128, 65, WIDE, WIDE),
+    (65281, 100, 128, WIDE, WIDE),
     (190001, 65, 300, WIDE, WIDE),
 ]
 
@@ -63,7 +67,7 @@ def test_narrow_products(sq, M, C_out, C_in, tile, tile_ext, bits, tiled):
 
 
 # the forward's per-column scales on the register-staged kernel
-@pytest.mark.parametrize("M,C_in,C_out", [(33001, 70, 30), (32768, 64, 41)])
+@pytest.mark.parametrize("M,C_in,C_out", [(33001, 70, 32), (32768, 64, 44)])
 @pytest.mark.parametrize("bits", [4, 8])
 def test_narrow_forward(sq, M, C_in, C_out, bits):
     import torch
