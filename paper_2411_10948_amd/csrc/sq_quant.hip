@@ -985,7 +985,7 @@ __device__ __forceinline__ void store_ext8(const Chan8& ch, const uint32_t (&col
 // q_t on the padded pixel grid (Wo and off multiples of 8; see launch_quantize).
 // AHEAD: a thread loads its 4 rows first and stores their folded codes last;
 // else it takes row after row, which needs 20 registers less and lets the other
-// waves' memory accesses run under the Philox words of stochastic codes.
+// waves' memory accesses run under this one's arithmetic (launch_quantize).
 template <bool SR, bool TL, bool GRID, bool AHEAD>
 __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ x, int64_t M, int64_t C, int64_t ld,
                                                       const uint8_t* __restrict__ group,
@@ -1694,17 +1694,23 @@ hipError_t launch_quantize(const float* x, int64_t M, int64_t C, int64_t ld, con
             hipLaunchKernelGGL(k, g8, dim3(kBlock), 0, s, x, M, C, ld, group, scale, cfg, q_fold, ld_fold, q_t, ld_t, desc,
                                eb, mv, tm, pg);
         };
-        // stochastic codes row by row (see k_quantize8), but not with appended
-        // windows near and beyond the last-level cache, where the accesses are
-        // the bound (6 bits, tile-major, ahead / by row: 16384 x 3072 112.4 /
-        // 120.7 us; 16384 x 768 39.9 / 39.1)
-        const bool ahead = !sr || (windows && (uint64_t)M * (uint64_t)ld * sizeof(float) > kLastLevelCacheBytes / 4 * 3);
+        // Row by row or loads ahead (see k_quantize8), us, ahead / by row: small
+        // tensors are a round of blocks or less, where the loads' latency is all
+        // there is (197 x 768, 6 bits 17.5 / 19.0); near and beyond the last-level
+        // cache the accesses are the bound (16384 x 3072, 6 bits, tile-major 113.3 /
+        // 119.6, stochastic 112.4 / 120.7); between them the registers are (200704 x
+        // 64 30.2 / 28.6, stochastic 31.2 / 29.6; 1376 x 4864 21.4 / 20.0).
+        // Stochastic codes without appended windows: by row (8192 x 11008 182.3 /
+        // 176.6; 256 x 256 13.8 / 13.8).
+        const uint64_t bytes = (uint64_t)M * (uint64_t)ld * sizeof(float);
+        const bool ahead = sr ? windows && bytes > kLastLevelCacheBytes / 4 * 3
+                              : grid8 || bytes < (16ull << 20) || bytes > kLastLevelCacheBytes * 3 / 8;
         if (grid8) run(!sr ? k_quantize8<false, false, true, true>
                        : ahead ? k_quantize8<true, false, true, true> : k_quantize8<true, false, true, false>);
-        else if (tiled) run(!sr ? k_quantize8<false, true, false, true>
-                            : ahead ? k_quantize8<true, true, false, true> : k_quantize8<true, true, false, false>);
-        else run(!sr ? k_quantize8<false, false, false, true>
-                 : ahead ? k_quantize8<true, false, false, true> : k_quantize8<true, false, false, false>);
+        else if (tiled && sr) run(ahead ? k_quantize8<true, true, false, true> : k_quantize8<true, true, false, false>);
+        else if (tiled) run(ahead ? k_quantize8<false, true, false, true> : k_quantize8<false, true, false, false>);
+        else if (sr) run(ahead ? k_quantize8<true, false, false, true> : k_quantize8<true, false, false, false>);
+        else run(ahead ? k_quantize8<false, false, false, true> : k_quantize8<false, false, false, false>);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)std::min<int64_t>(n_tiles(tc, tr), kQuantMaxBlocks));

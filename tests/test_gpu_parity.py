@@ -292,6 +292,26 @@ def test_quantize_tensor_parity(sq, transpose, shape, bits):
     assert h["bits"][:3] == [_f32bits(s_ref["r_max"]), _f32bits(s_ref["inv0"]), _f32bits(s_ref["d0"])]
 
 
+# gradients of 16 MB and more, whose rows a thread takes one by one, ragged in
+# rows and channels; tile-major codes as the row-major ones, which the oracle pins
+@pytest.mark.parametrize("M,C", [(4201, 1000), (65537, 72)])
+@pytest.mark.parametrize("bits,mode", [(4, 0), (6, 0), (4, 1), (6, 1)])
+def test_quantize_grad_row_by_row(sq, M, C, bits, mode):
+    import torch
+    assert M * C * 4 >= 16 << 20
+    print(f"row by row M={M} C={C} b={bits} mode={mode}", flush=True)
+    dY = _grad(M, C, seed=C + bits)
+    a = sq.quantize_grad(_dev(dY), bits, 4, mode, 3, 1)
+    b = sq.quantize_grad(_dev(dY), bits, 4, mode, 3, 1, tiled=True)
+    torch.cuda.synchronize()
+    check_quant(sq, a, dY, bits, 4, mode, 3, 1)
+    assert torch.equal(a.codes(), b.codes())
+    ext = int(a.layout[1])   # appended columns in use
+    used = (a.layout[32:32 + ext] >= 0).nonzero().flatten() + int(a.layout[2])
+    rows = b.fold_rows()
+    assert torch.equal(a.q_fold[:, :C], rows[:M, :C]) and torch.equal(a.q_fold[:, used], rows[:M, used])
+
+
 # rows that are not 16-byte aligned and very wide: a block maximum per 64
 # columns, 4096 of them or more, so that a launch of its own takes the largest
 @pytest.mark.parametrize("cols,at", [(262143, 262142), (262145, 262144), (262145, 0), (300001, 299999)])
