@@ -66,6 +66,23 @@ def test_narrow_products(sq, M, C_out, C_in, tile, tile_ext, bits, tiled):
     test_every_tile_and_split(sq, M, C_out, C_in, bits, tiled)
 
 
+# the GEMM-based comparison's products (a K segment per group) on those tiles
+@pytest.mark.parametrize("M,C_out,C_in", [(33001, 96, 40), (262145, 70, 61), (70001, 130, 100)])
+@pytest.mark.parametrize("bits", [4, 8])
+def test_narrow_grouped(sq, M, C_out, C_in, bits):
+    import torch
+    print(f"narrow grouped M={M} C_out={C_out} C_in={C_in} b={bits}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(M + C_out + bits)
+    dY = torch.randn(M, C_out, generator=g, device="cuda") * torch.exp2(-6 * torch.rand(C_out, generator=g, device="cuda"))
+    c = sq.quantize_grad(dY, bits, 4)
+    wq_t, ws = sq.quantize_tensor(torch.randn(C_out, C_in, generator=g, device="cuda"), 8)
+    A, dX = sq.gemm_dgrad_grouped(c, wq_t, ws, want_acc=True)
+    torch.cuda.synchronize()
+    ref = ((c.codes().double() * torch.exp2(3.0 - c.group.double())) @ wq_t[:, :C_out].t().double()).to(torch.int32)
+    assert torch.equal(A, ref)
+    assert torch.equal(dX, ref.float() * (c.scale[2] * ws[2] * 0.125))
+
+
 # the forward's per-column scales on the register-staged kernel
 @pytest.mark.parametrize("M,C_in,C_out", [(33001, 70, 32), (32768, 64, 44)])
 @pytest.mark.parametrize("bits", [4, 8])
