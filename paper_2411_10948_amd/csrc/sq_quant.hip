@@ -1011,7 +1011,7 @@ __global__ __launch_bounds__(kBlock) void k_quantize8(const float* __restrict__ 
         const int64_t c0 = ct * TC + 8 * g8, m0 = rt * TR + 4 * rq;
         const bool cin = c0 < C;   // C % 8 == 0: all 8 channels or none
         auto load = [&](int i, float4& a, float4& b) {
-            const float* src = x + min(m0 + i, M - 1) * ld + min(c0, C - 8);
+            const float* src = x + min(m0 + i, M - 1) * ld + (cin ? c0 : C - 8);
             a = *reinterpret_cast<const float4*>(src);
             b = *reinterpret_cast<const float4*>(src + 4);
         };
@@ -1173,7 +1173,7 @@ __global__ __launch_bounds__(kBlock) void k_quantize_grid(const float* __restric
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int p = min(max(4 * rq + i, p_lo), p_hi - 1);
-            const float* src = x + (m_base + p) * ld + min(c0, C - 8);
+            const float* src = x + (m_base + p) * ld + (cin ? c0 : C - 8);
             a[i] = *reinterpret_cast<const float4*>(src);
             b[i] = *reinterpret_cast<const float4*>(src + 4);
         }
@@ -1266,7 +1266,7 @@ __global__ __launch_bounds__(kBnQThreads) void k_quantize_bn(const float* __rest
     const int tid = threadIdx.x, g8 = tid & 7, rq = tid >> 3;
     const int64_t c0 = (int64_t)blockIdx.y * 64 + 8 * g8;
     const bool cin = c0 < C;
-    const int64_t cs = min(c0, C - 8);
+    const int64_t cs = cin ? c0 : C - 8;
     const int64_t r_end = min(M, ((int64_t)blockIdx.x + 1) * rows_per_block);
     int g1[8], g2[8];
 #pragma unroll
@@ -1700,11 +1700,12 @@ hipError_t launch_quantize(const float* x, int64_t M, int64_t C, int64_t ld, con
         // cache the accesses are the bound (16384 x 3072, 6 bits, tile-major 113.3 /
         // 119.6, stochastic 112.4 / 120.7); between them the registers are (200704 x
         // 64 30.2 / 28.6, stochastic 31.2 / 29.6; 1376 x 4864 21.4 / 20.0).
+        // Per-tensor codes, one layout only: ahead (12544 x 1024 22.9 / 23.8).
         // Stochastic codes without appended windows: by row (8192 x 11008 182.3 /
         // 176.6; 256 x 256 13.8 / 13.8).
         const uint64_t bytes = (uint64_t)M * (uint64_t)ld * sizeof(float);
         const bool ahead = sr ? windows && bytes > kLastLevelCacheBytes / 4 * 3
-                              : grid8 || bytes < (16ull << 20) || bytes > kLastLevelCacheBytes * 3 / 8;
+                              : grid8 || !group || bytes < (16ull << 20) || bytes > kLastLevelCacheBytes * 3 / 8;
         if (grid8) run(!sr ? k_quantize8<false, false, true, true>
                        : ahead ? k_quantize8<true, false, true, true> : k_quantize8<true, false, true, false>);
         else if (tiled && sr) run(ahead ? k_quantize8<true, true, false, true> : k_quantize8<true, true, false, false>);
